@@ -10,13 +10,19 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcaps.so")
 
 SOURCES = ["caps_api.hip", "caps_build.hip", "caps_search.hip", "caps_mfma.hip", "caps_router.hip", "caps_server.hip", "caps_io.hip", "caps_util.hip", "caps_static.hip"]
-# caps_scan_inst.hip once per (precision, kind): the matrix-core scan
-# instantiations, compiled in parallel (CAPS_PREC_BF16 = 1, FP8 = 2, FP16 = 3;
-# kinds: approximate keys, exact main pass, exact rescue pass, exact main pass
-# with survivor counts, seed lists)
-INSTANCES = [(f"caps_scan_{name}_{kind}", ["-DCAPS_INST_PREC=%d" % prec, "-DCAPS_INST_KIND=%d" % kd])
-             for name, prec in (("bf16", 1), ("fp8", 2), ("fp16", 3))
-             for kind, kd in (("approx", 0), ("exact", 1), ("rescue", 2), ("exactcnt", 3), ("seed", 4))]
+# The matrix-core scan instantiations, compiled in parallel (CAPS_PREC_BF16 = 1,
+# FP8 = 2, FP16 = 3): caps_scan_inst.hip once per precision and kind (0
+# approximate keys, also per row length; 1 exact main pass; 2 rescue pass; 3
+# exact main pass with survivor counts), caps_x32_inst.hip once per precision,
+# without and with label tests.  The longest compilations first.
+_PRECS = (("bf16", 1), ("fp8", 2), ("fp16", 3))
+INSTANCES = [("caps_scan_inst.hip", f"caps_scan_{name}_approx{ns}",
+              [f"-DCAPS_INST_PREC={prec}", "-DCAPS_INST_KIND=0", f"-DCAPS_INST_NS={ns}"])
+             for name, prec in _PRECS for ns in (8, 4, 2, 1)]
+INSTANCES += [("caps_scan_inst.hip", f"caps_scan_{name}_{kind}", [f"-DCAPS_INST_PREC={prec}", f"-DCAPS_INST_KIND={kd}"])
+              for kind, kd in (("rescue", 2), ("exact", 1), ("exactcnt", 3)) for name, prec in _PRECS]
+INSTANCES += [("caps_x32_inst.hip", f"caps_x32_{name}_{lab}", [f"-DCAPS_INST_PREC={prec}", f"-DCAPS_INST_LAB={lab}"])
+              for name, prec in _PRECS for lab in (1, 0)]
 
 # -ffp-contract=off: every fused multiply-add in the kernels is written out
 # explicitly (fmaf); the compiler must not fuse anything else, so that the
@@ -55,8 +61,8 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     procs = []
-    jobs = [(src, src.replace(".hip", ".o"), []) for src in SOURCES]
-    jobs += [("caps_scan_inst.hip", name + ".o", defs) for name, defs in INSTANCES]
+    jobs = [(src, name + ".o", defs) for src, name, defs in INSTANCES]
+    jobs += [(src, src.replace(".hip", ".o"), []) for src in SOURCES]
     objs_all = []
     for src, oname, defs in jobs:
         obj = os.path.join(objdir, oname)

@@ -184,6 +184,7 @@ struct LowpScan {
     int32_t nb, m, r;             // r: keys kept per (query, probe)
     int kind;                     // 0 approximate keys, 1 exact main pass, 2 exact rescue pass, 4 seed lists
                                   // (approximate keys of the seed probes on 32 x 32 blocks)
+    int seed_mh;                  // kind 4: keys per lane (half of a probe's rows), 1 or 4
     int stage;                    // profiling stage of the launch (CAPS_STAGE_SCAN or _SEED)
     int64_t max_tiles;
     const int4 *tiles;            // per tile: partition, first entry, entries (0: none)

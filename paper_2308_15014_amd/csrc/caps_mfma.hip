@@ -26,6 +26,7 @@
 #include <algorithm>
 
 #include "caps_mfma.h"
+#include "caps_x32.h"
 
 namespace caps {
 
@@ -397,11 +398,28 @@ __global__ __launch_bounds__(256) void k_merge_rerank(const uint64_t *__restrict
 }
 
 // ------------------------------------------------------------------ host
-template <int EX>
+template <int PREC, int KIND>
+static LowpFn pick_ns(int ns, bool lab, int r) {
+    switch (ns) {
+    case 1: return pick_lab<PREC, 1, KIND>(lab, r);
+    case 2: return pick_lab<PREC, 2, KIND>(lab, r);
+    case 4: return pick_lab<PREC, 4, KIND>(lab, r);
+    default: return pick_lab<PREC, 8, KIND>(lab, r);
+    }
+}
+
+template <int KIND>
 static LowpFn pick_prec(int prec, int ns, bool lab, int r) {
-    if (prec == CAPS_PREC_BF16) return pick_ns<CAPS_PREC_BF16, EX>(ns, lab, r);
-    if (prec == CAPS_PREC_FP16) return pick_ns<CAPS_PREC_FP16, EX>(ns, lab, r);
-    return pick_ns<CAPS_PREC_FP8, EX>(ns, lab, r);
+    if (prec == CAPS_PREC_BF16) return pick_ns<CAPS_PREC_BF16, KIND>(ns, lab, r);
+    if (prec == CAPS_PREC_FP16) return pick_ns<CAPS_PREC_FP16, KIND>(ns, lab, r);
+    return pick_ns<CAPS_PREC_FP8, KIND>(ns, lab, r);
+}
+
+template <bool LAB>
+static LowpFn pick_x32_prec(int prec, int ns, int mode) {
+    if (prec == CAPS_PREC_BF16) return pick_x32<CAPS_PREC_BF16, LAB>(ns, mode);
+    if (prec == CAPS_PREC_FP16) return pick_x32<CAPS_PREC_FP16, LAB>(ns, mode);
+    return pick_x32<CAPS_PREC_FP8, LAB>(ns, mode);
 }
 
 // workgroups of the rescue pass (32 per compute unit): enough to spread a
@@ -465,13 +483,14 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     A.gam = (float)(8.0 * ix->dpad) * 0x1p-24f;
     // the variant with the filter's slow path: label tests, disjunctions
     const bool lab = ix->sch.label_vocab > 0 || S.disj;
-    const LowpFn fn = S.kind == 0   ? pick_prec<0>(ix->prec, ix->dpad / 32, lab, S.r)
-                      : S.kind == 4 ? pick_prec<4>(ix->prec, ix->dpad / 32, lab, S.r)
-                      : S.kind == 1 ? (S.nsurv ? pick_prec<3>(ix->prec, ix->dpad / 32, lab, S.r)
-                                               : pick_prec<1>(ix->prec, ix->dpad / 32, lab, S.r))
-                                    : pick_prec<2>(ix->prec, ix->dpad / 32, lab, S.r);
-    // (the 32 x 32 main pass holds its arrays in static LDS)
-    const bool x32 = (S.kind == 1 || S.kind == 4) && lowp_x32_kernel(ix->prec, ix->dpad / 32, lab);
+    const int ns = ix->dpad / 32;
+    // (the 32 x 32 scan holds its arrays in static LDS)
+    const bool x32 = S.kind == 4 || (S.kind == 1 && x32_kernel(ns, lab, S.nsurv != nullptr));
+    const int xmode = S.kind == 4 ? (S.seed_mh == 1 ? 2 : 3) : S.nsurv ? 1 : 0;
+    const LowpFn fn = x32 ? (lab ? pick_x32_prec<true>(ix->prec, ns, xmode) : pick_x32_prec<false>(ix->prec, ns, xmode))
+                      : S.kind == 0 ? pick_prec<0>(ix->prec, ns, lab, S.r)
+                      : S.kind == 1 ? (S.nsurv ? pick_prec<3>(ix->prec, ns, lab, S.r) : pick_prec<1>(ix->prec, ns, lab, S.r))
+                                    : pick_prec<2>(ix->prec, ns, lab, S.r);
     const size_t lds = x32 ? 0 : lowp_scan_lds(ix, S.r, S.kind, S.disj);
     {
         const caps_status ls = set_kernel_lds((const void *)fn, lds, ix->device);
@@ -505,12 +524,21 @@ caps_status lowp_merge(const Index *ix, const float *q, int32_t nb, const uint32
 
 int lowp_qb() { return kLQB; }
 
-int lowp_qb_main(const Index *ix, bool disj) {
-    return lowp_x32_kernel(ix->prec, ix->dpad / 32, ix->sch.label_vocab > 0 || disj) ? kXQB : kLQB;
+int lowp_qb_main(const Index *ix, bool disj, bool count) {
+    return x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, count) ? kXQB : kLQB;
 }
 
-bool lowp_seed_x32(const Index *ix, bool disj, int r) {
-    return r >= 2 && lowp_x32_kernel(ix->prec, ix->dpad / 32, ix->sch.label_vocab > 0 || disj);
+// Keys each lane of the 32 x 32 seed pass keeps (half of a partition's rows
+// and one query), or 0 where the seed round runs k_scan_mfma's approximate
+// kind.  Lists of two keys per seed probe are enough when they hold twice k
+// (longer lists cost more insertions than their tighter bound saved: 4 and 10
+// keys ran 0.34 and 0.44 ms per 10k-query step against 0.28 ms with the same
+// main pass); with fewer seed probes or a longer result list, lists of eight
+// keys where those can hold k; else the full lists of r.
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed) {
+    if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false)) return 0;
+    if (r >= 2 && s_seed >= k) return 1;
+    return r >= 8 && 8 * s_seed >= k ? 4 : 0;
 }
 
 }  // namespace caps

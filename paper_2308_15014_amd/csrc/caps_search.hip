@@ -1508,8 +1508,8 @@ struct Arena {
 };
 
 int lowp_qb();
-int lowp_qb_main(const Index *ix, bool disj);
-bool lowp_seed_x32(const Index *ix, bool disj, int r);
+int lowp_qb_main(const Index *ix, bool disj, bool count);
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed);
 
 struct SearchWs {
     uint8_t *qlow;
@@ -1886,9 +1886,11 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 if (r0 >= r1) continue;
                 // tile width of this round: the exact main pass and the seed lists may
                 // run 128-entry tiles
-                const bool seed_x32 = mfma && !lowp && seeded_exact && round == 0 && lowp_seed_x32(ix, disj, r);
-                const int qbr = mfma && !lowp && (!(seeded_exact && round == 0) || seed_x32) ? lowp_qb_main(ix, disj)
-                                                                                            : qb;
+                const bool seed_pass = seeded_exact && round == 0;
+                const int seed_mh = seed_pass ? lowp_seed_x32(ix, disj, r, k, s_seed) : 0;
+                const int qbr = !mfma || lowp             ? qb
+                                : seed_pass && !seed_mh   ? qb
+                                                          : lowp_qb_main(ix, disj, !seed_pass && out_nsurv);
                 prof_begin(CAPS_STAGE_SELECT, st);
                 const unsigned ggrid = (unsigned)((ngrp + kXcds - 1) / kXcds * kXcds);   // XCD-mapped groups
                 hipLaunchKernelGGL(k_bucket_hist, dim3(ggrid), dim3(kBucketT), sizeof(int32_t) * (size_t)b, st, probes, sel,
@@ -1917,12 +1919,12 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 CAPS_HIP(hipGetLastError());
                 prof_end(CAPS_STAGE_SELECT, st);
                 if (mfma) {
-                    const bool seed_pass = seeded_exact && round == 0;
                     LowpScan S{};
                     S.nb = nb;
                     S.m = m;
                     S.r = r;
-                    S.kind = seed_x32 ? 4 : lowp || seed_pass ? 0 : 1;
+                    S.kind = seed_mh ? 4 : lowp || seed_pass ? 0 : 1;
+                    S.seed_mh = seed_mh;
                     S.stage = seed_pass ? CAPS_STAGE_SEED : CAPS_STAGE_SCAN;
                     S.max_tiles = grid;
                     S.tiles = W.tiles;

@@ -1,0 +1,53 @@
+"""The 32 x 32 matrix-core scan in every storage format, row length, filter kind
+and seed-list length: exact results (ids and distance bits) against the oracle,
+with tiles past 128 entries, ragged chunk tails and rings that fill inside a tile."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def caps():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2308_15014_amd as caps
+    caps.lib()
+    return caps
+
+
+CASES = [
+    # seed, prec, d, metric, vocabs, label_vocab, max_labels, disjunctive, k, m
+    (600, "fp8", 24, 0, (), 12, 8, False, 10, 12),      # one step per row
+    (601, "fp8", 128, 1, (4, 5), 30, 8, True, 10, 12),  # OR terms over dense values and labels
+    (602, "fp16", 33, 0, (3,), 200, 24, False, 5, 7),   # wide slot rows
+    (603, "bf16", 100, 1, (), 6, 4, False, 33, 9),      # long seed lists (four keys per lane)
+    (604, "fp16", 128, 0, (4, 3), 0, 8, True, 10, 12),  # disjunctions without labels
+    (605, "fp8", 65, 0, (3, 3), 0, 8, False, 20, 12),   # FP8 without labels
+    (606, "bf16", 128, 0, (2,), 3, 2, False, 64, 3),    # too few seed probes for the seed lists
+    (607, "bf16", 31, 0, (2, 2), 5, 3, False, 1, 12),   # k = 1
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_x32_equals_oracle(caps, orc, case):
+    seed, prec, d, metric, voc, lv, ml, disj, k, m = case
+    w = synth.make_tiny(seed, n=7001, d=d, n_q=301, vocabs=voc, label_vocab=lv, metric=metric, b=12, h=2, cmin=0, cmax=2,
+                        max_labels=ml)
+    co, ca, cv = w.con_off, w.con_attr, w.con_val
+    if disj:
+        co, ca, cv = synth.draw_disjunctions(np.random.default_rng(seed), w.n_q, w.n, w.dense, w.label_off, w.labels, 1,
+                                             3, 0, 2)
+    oi = orc.build_from_workload(w, iters=2)
+    ix = caps.Index.from_workload(w, kmeans_iters=2, precision=prec)
+    r = orc.search(oi, w.q, co, ca, cv, k, m, disjunctive=disj)
+    for counters in (False, True):
+        got = ix.search(w.q, co, ca, cv, k, m, disjunctive=disj, counters=counters)
+        assert np.array_equal(got[0].cpu().numpy(), r.ids)
+        assert np.array_equal(got[1].cpu().numpy().view(np.uint32), r.dist.view(np.uint32))
+        if counters:
+            assert np.array_equal(got[2].cpu().numpy(), r.n_cand) and np.array_equal(got[3].cpu().numpy(), r.n_surv)
+    ix.close()
