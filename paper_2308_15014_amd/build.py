@@ -43,14 +43,25 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def _deps(path: str, seen: set) -> set:
+    """A source and the library's own headers it includes, directly or not."""
+    path = os.path.normpath(path)
+    if path not in seen:
+        seen.add(path)
+        with open(path) as f:
+            for line in f:
+                if line.startswith('#include "'):
+                    _deps(os.path.join(os.path.dirname(path), line.split('"')[1]), seen)
+    return seen
+
+
 def _stale(obj: str, src: str) -> bool:
-    """An object is stale when it is older than its source or any header
-    of the library (every source includes some of them)."""
+    """An object is stale when it is older than its source, one of the
+    library's headers that it includes, or this file (its flags)."""
     if not os.path.exists(obj):
         return True
     t = os.path.getmtime(obj)
-    deps = [os.path.join(CSRC, src), os.path.join(HERE, "..", "include", "caps.h")]
-    deps += [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
+    deps = _deps(os.path.join(CSRC, src), {os.path.abspath(__file__)})
     return any(os.path.getmtime(f) > t for f in deps)
 
 

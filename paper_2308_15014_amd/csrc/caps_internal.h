@@ -62,7 +62,7 @@ struct alignas(16) QDesc {
     int32_t pad;
 };
 
-struct Index {
+struct IndexData {
     int device = 0;
     int64_t n = 0;
     int32_t d = 0, b = 0, h = 0, metric = 0;
@@ -92,8 +92,10 @@ struct Index {
     float *lnrm = nullptr;      // n upper bounds on |x~|, CSR order
     void *clow = nullptr;       // b x dpad centroid copy in the same format (precision-mode routing)
     float *cscale = nullptr;    // b per-centroid FP8 scales
-    std::vector<int32_t> h_offs;
     struct Router *router = nullptr;   // learned router (owned), if trained or set
+};
+struct Index : IndexData {
+    std::vector<int32_t> h_offs;
 };
 
 // Learned router state (caps_router.hip): a two-layer perceptron on
@@ -134,6 +136,9 @@ caps_status build_index(Index *ix, const float *x, int64_t n, int32_t d, const u
                         const caps_build_params *p, hipStream_t st);
 
 // ---- search (caps_search.hip)
+// internal bit of caps_search_params.flags: no BF16 copy of an FP32 index in
+// the workspace (the server, whose batches share a budget, sets it)
+constexpr int32_t kSearchNoCopy = 1 << 30;
 struct SearchExtra {
     uint64_t *surv_mask = nullptr;   // debug: per query, survivor bits over CSR positions (device)
     void *ws = nullptr;              // caller workspace: the search allocates nothing
@@ -176,6 +181,10 @@ caps_status lowp_qquant(const Index *ix, const float *q, int32_t nb, void *qlow,
 // low-precision rows (and their FP32 norms and error norms) of n FP32 rows
 caps_status quantize_rows(const Index *ix, const float *x, int64_t n, void *lvec, float *scale, float *xnorm,
                           float *lerr, float *lnrm, hipStream_t st);
+// BF16 copy of FP32 rows for one search: codes (dpad elements a row), |x|^2 and
+// the error norms of the exact bound
+caps_status search_copy(const float *x, int64_t n, int32_t d, int32_t dpad, uint16_t *lvec, float *xnorm, float *lerr,
+                        float *lnrm, hipStream_t st);
 // dynamic insertion of n_new points (HOST arrays, validated by the caller)
 caps_status insert_points(Index *ix, const float *x, int64_t n_new, const uint32_t *dense, const int64_t *label_off,
                           const uint32_t *labels, hipStream_t st);

@@ -26,53 +26,10 @@
 #include <algorithm>
 
 #include "caps_mfma.h"
+#include "caps_query.h"
 #include "caps_x32.h"
 
 namespace caps {
-
-// ------------------------------------------------------------------ rounding
-__device__ inline uint16_t f16_rne_sat(float f) {
-    f = fminf(fmaxf(f, -65504.0f), 65504.0f);
-    return __builtin_bit_cast(uint16_t, (_Float16)f);
-}
-
-// OCP E4M3 (bias 7, max 448, 0x7F/0xFF are NaN): round to nearest even,
-// saturating to +-448.
-__device__ inline uint8_t e4m3_rne_sat(float v) {
-    const uint8_t sign = v < 0.0f ? 0x80 : 0x00;
-    const float a = fabsf(v);
-    if (!(a < 448.0f)) return sign | 0x7E;
-    if (a < 0.015625f) {   // below the smallest normal 2^-6: quantum 2^-9
-        const int qi = (int)rintf(a * 512.0f);
-        return qi == 0 ? (uint8_t)0 : (uint8_t)(sign | qi);   // single zero; 8 is the smallest normal
-    }
-    int e2;
-    (void)frexpf(a, &e2);
-    int e = e2 - 1;                       // a in [2^e, 2^(e+1))
-    int q = (int)rintf(ldexpf(a, 3 - e)); // in [8, 16]
-    if (q == 16) {
-        e += 1;
-        q = 8;
-    }
-    return sign | (uint8_t)(((e + 7) << 3) | (q - 8));
-}
-
-// Value of an E4M3 code (finite codes only).
-__device__ inline double e4m3_value(uint8_t c) {
-    const int e = (c >> 3) & 15, m = c & 7;
-    const double v = e == 0 ? ldexp((double)m, -9) : ldexp((double)(8 + m), e - 10);
-    return (c & 0x80) ? -v : v;
-}
-
-// FP64 -> FP32 rounded towards +inf / -inf (inputs >= 0).
-__device__ inline float f32_up(double v) {
-    const float f = (float)v;
-    return (double)f < v ? nextafterf(f, __builtin_huge_valf()) : f;
-}
-__device__ inline float f32_down(double v) {
-    const float f = (float)v;
-    return (double)f > v ? nextafterf(f, 0.0f) : f;
-}
 
 // Rounds row r (d coordinates) into `out` (dpad elements) and returns the
 // FP8 scale (1 otherwise); e2 / a2 receive, in FP64, sum (r_j - r~_j)^2 and
@@ -112,9 +69,6 @@ __device__ inline float quantize_row(const float *r, int d, int dpad, int prec, 
     return s;
 }
 
-// relative slack covering the FP64 sums and square roots above
-constexpr double kNormSlack = 1.0 + 0x1p-40;
-
 // ------------------------------------------------------------------ build
 // One thread per point: |x|^2 (sequential fma), rounded copy, FP8 scale and
 // the error norms |x - x~| and |x~| (rounded up).
@@ -133,6 +87,83 @@ __global__ void k_quantize(const float *__restrict__ x, int64_t n, int32_t d, in
     if (prec == CAPS_PREC_FP8) scale[i] = s;
     lerr[i] = f32_up(sqrt(e2) * kNormSlack);
     lnrm[i] = f32_up(sqrt(a2) * kNormSlack);
+}
+
+// The BF16 copy that a large search on an FP32 index makes in its workspace:
+// 16 lanes per row, four coordinates per lane and step, norms in FP32.  The
+// error norm is the square root of a sum of d squares, each with at most d + 2
+// roundings, and a square below the smallest normal number may come out as 0:
+// both are covered by the factor 1 + 2^-10 and the term d 2^-125.  HBM bound
+// (4 d + 2 dpad bytes a row): 1M x 128 in 0.19 ms (4.2 TB/s), against 2.7 ms
+// for 0.5M rows with k_quantize's thread per row.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_search_copy(const float *__restrict__ x, int64_t n, int32_t d, int32_t dpad,
+                                                     uint16_t *__restrict__ out, float *__restrict__ xnorm,
+                                                     float *__restrict__ lerr, float *__restrict__ lnrm) {
+    const int l16 = threadIdx.x & 15;
+    const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (i >= n) return;   // (whole groups of 16 lanes)
+    const float *r = x + i * d;
+    uint16_t *o = out + i * dpad;
+    float nx = 0.0f, e2 = 0.0f, a2 = 0.0f;
+    uint2 code[4];   // dpad <= 256: at most four steps of 64 coordinates
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const int j = 64 * s + 4 * l16;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (VEC) {
+            if (j < d) {
+                const float4 f = *reinterpret_cast<const float4 *>(r + j);
+                v[0] = f.x;
+                v[1] = f.y;
+                v[2] = f.z;
+                v[3] = f.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; c++)
+                if (j + c < d) v[c] = r[j + c];
+        }
+        uint32_t h[4];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            h[c] = bf16_rne(v[c]);
+            const float u = __uint_as_float(h[c] << 16), e = v[c] - u;
+            nx = fmaf(v[c], v[c], nx);
+            e2 = fmaf(e, e, e2);
+            a2 = fmaf(u, u, a2);
+        }
+        code[s] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    }
+#pragma unroll
+    for (int w = 8; w >= 1; w >>= 1) {
+        nx += __shfl_xor(nx, w, 64);
+        e2 += __shfl_xor(e2, w, 64);
+        a2 += __shfl_xor(a2, w, 64);
+    }
+    const bool ok = nx < kNormMax && a2 < kNormMax;   // (false for NaN too)
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const int j = 64 * s + 4 * l16;
+        if (j < dpad) *reinterpret_cast<uint2 *>(o + j) = ok ? code[s] : make_uint2(0u, 0u);
+    }
+    if (l16 == 0) {
+        const float tiny = (float)d * 0x1p-125f, up = 1.0f + 0x1p-10f;
+        xnorm[i] = ok ? nx : 0.0f;
+        lerr[i] = ok ? sqrtf(e2 + tiny) * up : __builtin_huge_valf();
+        lnrm[i] = ok ? sqrtf(a2 + tiny) * up : __builtin_huge_valf();
+    }
+}
+
+caps_status search_copy(const float *x, int64_t n, int32_t d, int32_t dpad, uint16_t *lvec, float *xnorm, float *lerr,
+                        float *lnrm, hipStream_t st) {
+    const dim3 g((unsigned)((n + 15) / 16));
+    if (d % 4 == 0)
+        hipLaunchKernelGGL(k_search_copy<true>, g, dim3(256), 0, st, x, n, d, dpad, lvec, xnorm, lerr, lnrm);
+    else
+        hipLaunchKernelGGL(k_search_copy<false>, g, dim3(256), 0, st, x, n, d, dpad, lvec, xnorm, lerr, lnrm);
+    CAPS_HIP(hipGetLastError());
+    return CAPS_OK;
 }
 
 static int esize_of(int prec) { return prec == CAPS_PREC_FP8 ? 1 : 2; }
@@ -173,58 +204,14 @@ caps_status build_lowp(Index *ix, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ queries
-// One wave per query: rounded copy (the codes of quantize_row, element by
-// element), FP8 scale and qaux = {|q| (up), |q|^2 (down), |q - q~| (up),
-// |q~| (up)}; the FP64 sums are reduced across the wave (their order does
-// not matter: kNormSlack covers any order).
+// One wave per query.
 __global__ __launch_bounds__(256) void k_qquant(const float *__restrict__ q, int32_t nq, int32_t d, int32_t dpad,
                                                 int32_t prec, void *__restrict__ out, float *__restrict__ scale,
                                                 float *__restrict__ qaux) {
     const int lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= nq) return;
-    const float *r = q + i * d;
-    float s = 1.0f;
-    if (prec == CAPS_PREC_FP8) {
-        float amax = 0.0f;
-        for (int j = lane; j < d; j += 64) amax = fmaxf(amax, fabsf(r[j]));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-        s = amax > 0.0f ? amax / 448.0f : 1.0f;
-    }
-    double e2 = 0.0, a2 = 0.0, n2 = 0.0;
-    for (int j = lane; j < dpad; j += 64) {
-        const float x = j < d ? r[j] : 0.0f;
-        double v;
-        if (prec == CAPS_PREC_FP8) {
-            const uint8_t c = j < d ? e4m3_rne_sat(x / s) : (uint8_t)0;
-            reinterpret_cast<uint8_t *>(out)[i * dpad + j] = c;
-            v = (double)s * e4m3_value(c);
-        } else {
-            const uint16_t c = j < d ? (prec == CAPS_PREC_BF16 ? bf16_rne(x) : f16_rne_sat(x)) : (uint16_t)0;
-            reinterpret_cast<uint16_t *>(out)[i * dpad + j] = c;
-            v = prec == CAPS_PREC_BF16 ? (double)__builtin_bit_cast(float, (uint32_t)c << 16)
-                                       : (double)__builtin_bit_cast(_Float16, c);
-        }
-        if (j < d) {
-            e2 += ((double)x - v) * ((double)x - v);
-            a2 += v * v;
-            n2 += (double)x * (double)x;
-        }
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        e2 += __shfl_xor(e2, o, 64);
-        a2 += __shfl_xor(a2, o, 64);
-        n2 += __shfl_xor(n2, o, 64);
-    }
-    if (lane == 0) {
-        scale[i] = s;
-        qaux[4 * i + 0] = f32_up(sqrt(n2) * kNormSlack);
-        qaux[4 * i + 1] = f32_down(n2 / kNormSlack);
-        qaux[4 * i + 2] = f32_up(sqrt(e2) * kNormSlack);
-        qaux[4 * i + 3] = f32_up(sqrt(a2) * kNormSlack);
-    }
+    qquant_row(q + i * d, i, d, dpad, prec, out, scale, qaux);
 }
 
 // ------------------------------------------------------------------ routing

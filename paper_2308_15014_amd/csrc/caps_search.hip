@@ -18,61 +18,17 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "caps_device.h"
 #include "caps_internal.h"
 #include "caps_mfma.h"
+#include "caps_query.h"
 
 namespace caps {
 
 
 // ------------------------------------------------------------------ prep
-__device__ inline void qd_clear(QDesc &r) {
-    r.dmask = 0;
-    r.dval = 0;
-    r.flags = 0;
-    r.nlab = 0;
-    r.lsig = 0;
-    for (int i = 0; i < kMaxLabels; i++) r.lab[i] = 0xFFFF;
-    r.nterm = 1;
-    r.pad = 0;
-}
-
-// Adds constraint pair (a, v) to the AND-term r: a dense value becomes a
-// packed field under dmask, a label joins the label list and signature; a
-// pair outside the vocabularies, a second value of one dense attribute or a
-// ninth label makes the term unsatisfiable.
-__device__ inline void qd_add(QDesc &r, const Schema &sch, int32_t a, int32_t v) {
-    if (a < 0 || a > sch.n_dense) {
-        r.flags |= kQUnsat;
-        return;
-    }
-    if (a < sch.n_dense) {
-        if (v < 0 || v >= sch.dense_vocab[a]) {
-            r.flags |= kQUnsat;
-            return;
-        }
-        const uint32_t fm = (uint32_t)(((1ull << sch.field_bits[a]) - 1ull) << sch.field_shift[a]);
-        const uint32_t fv = (uint32_t)v << sch.field_shift[a];
-        if ((r.dmask & fm) && ((r.dval & fm) != fv)) r.flags |= kQUnsat;
-        r.dmask |= fm;
-        r.dval = (r.dval & ~fm) | fv;
-        return;
-    }
-    if (sch.label_vocab == 0 || v < 0 || v >= sch.label_vocab) {
-        r.flags |= kQUnsat;
-        return;
-    }
-    for (int i = 0; i < r.nlab; i++)
-        if (r.lab[i] == (uint16_t)v) return;   // duplicate: AND is idempotent
-    if (r.nlab == kMaxLabels) {
-        r.flags |= kQUnsat;
-        return;
-    }
-    r.lab[r.nlab++] = (uint16_t)v;
-    r.lsig |= 1ull << label_sig_bit((uint32_t)v);
-}
-
 // One thread per query.  Without `disj` every pair is ANDed (a pair with a
 // negative attribute, CAPS_OR included, makes the query unsatisfiable).
 // With `disj` the pairs with attr == CAPS_OR separate AND-terms: the
@@ -116,20 +72,7 @@ __global__ __launch_bounds__(128) void k_qprep(const int32_t *__restrict__ con_o
     } else if (nsat == 1) {
         r = tq[0];
     } else {
-        uint32_t all = ~0u, diff = 0;
-        for (int t = 0; t < nsat; t++) {
-            all &= tq[t].dmask;
-            diff |= tq[t].dval ^ tq[0].dval;
-        }
-        uint32_t keep = 0;
-        for (int a = 0; a < sch.n_dense; a++) {
-            const uint32_t fm = (uint32_t)(((1ull << sch.field_bits[a]) - 1ull) << sch.field_shift[a]);
-            if ((all & fm) == fm && !(diff & fm)) keep |= fm;
-        }
-        r.dmask = keep;
-        r.dval = tq[0].dval & keep;
-        r.flags = kQOr;
-        r.nterm = nsat;
+        qd_summary(r, sch, tq, nsat);
     }
     out[q] = r;
 }
@@ -430,66 +373,6 @@ static void launch_topm(const float *scores, int32_t nb, int32_t b, int32_t pb, 
 }
 
 // ------------------------------------------------------------------ selection
-__device__ inline void tag_decode(const Schema &s, int32_t tok, int &attr, int32_t &val) {
-    if (tok < s.dense_off[s.n_dense]) {
-        int a = 0;
-        while (a + 1 < s.n_dense && tok >= s.dense_off[a + 1]) a++;
-        attr = a;
-        val = tok - s.dense_off[a];
-    } else {
-        attr = s.n_dense;
-        val = tok - s.dense_off[s.n_dense];
-    }
-}
-
-// Exact rule: J* = first tagged level whose tag the query holds (h if none);
-// scan level j < h iff j <= J*, tagged, and its tag does not contradict a
-// dense constraint; scan the remainder iff J* = h.  rule 1: only level J*.
-__device__ inline uint32_t choose_levels(const Schema &s, const QDesc &qd, const int32_t *tags, int h,
-                                         int rule) {
-    if (qd.flags & (kQUnsat | kQNonFinite)) return 0u;
-    int js = h;
-    uint32_t ok = 0;
-    for (int j = 0; j < h; j++) {
-        const int32_t t = tags[j];
-        if (t < 0) continue;
-        int a;
-        int32_t v;
-        tag_decode(s, t, a, v);
-        bool held, conflict = false;
-        if (a < s.n_dense) {
-            const uint32_t fm = (uint32_t)(((1ull << s.field_bits[a]) - 1ull) << s.field_shift[a]);
-            const bool constrained = (qd.dmask & fm) != 0;
-            const bool same = ((qd.dval & fm) >> s.field_shift[a]) == (uint32_t)v;
-            held = constrained && same;
-            conflict = constrained && !same;
-        } else {
-            held = false;
-            for (int i = 0; i < qd.nlab; i++) held |= qd.lab[i] == (uint16_t)v;
-        }
-        if (!conflict) ok |= 1u << j;
-        if (held) {
-            js = j;
-            break;
-        }
-    }
-    if (rule == 1) return 1u << js;
-    uint32_t mask = ok & ((js >= 31) ? 0xFFFFFFFFu : ((2u << js) - 1u));
-    if (js == h) mask |= 1u << h;
-    return mask;
-}
-
-// A query's levels: the union over its terms for a disjunction (Section 5.3:
-// several sub-partitions per partition join the candidate set).
-__device__ inline uint32_t choose_query_levels(const Schema &s, const QDesc &qd, const QDesc *terms,
-                                               const int32_t *tags, int h, int rule) {
-    if (qd.flags & (kQUnsat | kQNonFinite)) return 0u;
-    if (!(qd.flags & kQOr)) return choose_levels(s, qd, tags, h, rule);
-    uint32_t mask = 0;
-    for (int t = 0; t < qd.nterm; t++) mask |= choose_levels(s, terms[t], tags, h, rule);
-    return mask;
-}
-
 __global__ void k_select(const int32_t *__restrict__ probes, int32_t nq, int32_t m,
                          const QDesc *__restrict__ qd, const QDesc *__restrict__ qterms, Schema sch,
                          const int32_t *__restrict__ tags, int32_t h, const int32_t *__restrict__ offs, int32_t rule,
@@ -1265,20 +1148,27 @@ struct Deferred {
 };
 
 // Deferred pairs kept per query by the exact matrix-core scan (a query with
-// more goes to the rescue pass).
-constexpr int32_t kDeferCap = 512;
+// more goes to the rescue pass, which scans its tiles again: 170 us on a 10k
+// batch with a handful of such queries).  Seed probes of 1/24 of the probes
+// let about 24 k pairs through in the two-byte formats, and eight times as
+// many in FP8, whose rounding errors widen the bound by 0.7 standard
+// deviations of the scores on unit vectors (4096 queries x 1M x 96, k = 10:
+// most queries defer 600..1900 pairs; with lists of 512 the rescue pass took
+// 2.71 ms of a 7.0 ms search).
+inline int32_t defer_cap(int32_t prec, int32_t k) { return prec == CAPS_PREC_FP8 || k > 16 ? 2048 : 1024; }
 // Pairs rescored first (those with the smallest test scores): k and half
 // again, at least 16, at most 64 (one per lane).
 __device__ inline int merge_first(int k) { return min(64, max(16, k + (k >> 1))); }
 
-template <int KM>
+// EP: pairs per lane of a full deferred list (cap / 64).
+template <int KM, int EP>
 __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ partials,
                                                const int32_t *__restrict__ pcnt,
                                                const uint32_t *__restrict__ sel, const int32_t *__restrict__ cand,
                                                int32_t nq, int32_t m, int32_t k, int32_t metric,
                                                int32_t *__restrict__ ids, float *__restrict__ dist,
                                                int32_t *__restrict__ ncand, Deferred D) {
-    __shared__ uint64_t mbuf[4][64], mkb[4][64];   // per wave: round 1's pairs and keys
+    __shared__ uint64_t mbuf[4][128], mkb[4][64];   // per wave: pairs to rescore, round 1's keys
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (q >= nq) return;
@@ -1313,10 +1203,13 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
             // where scores tie, at most 64); the k-th of their exact keys, K, is
             // at or above the final k-th key, so round 2 needs only the pairs
             // that pass the test at bound K.  (first >= k: K is finite.)
-            constexpr int EP = kDeferCap / 64;
-            uint64_t e[EP];   // pair lane + 64 j (~0: none)
+            // (the code below for lists of up to NP x 64 pairs; short lists, the
+            // usual case, hold theirs in a quarter of the registers)
+            auto rounds = [&](auto np_c) {
+            constexpr int NP = decltype(np_c)::value;
+            uint64_t e[NP];   // pair lane + 64 j (~0: none)
 #pragma unroll
-            for (int j = 0; j < EP; j++) {
+            for (int j = 0; j < NP; j++) {
                 const int i = j * 64 + lane;
                 e[j] = i < n ? src[i] : ~0ull;
             }
@@ -1324,13 +1217,13 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
             // T: the first-th smallest test score key (bisection over its
             // bits, stopped once the range holds a single key)
             uint32_t ans = 0;
-            int c_lo = 0, c_hi = EP * 64;
+            int c_lo = 0, c_hi = NP * 64;
             bool one = false;
             for (int bit = 31; bit >= 0; bit--) {
                 const uint32_t t = ans | (1u << bit);
                 int c = 0;
 #pragma unroll
-                for (int j = 0; j < EP; j++) c += __popcll(__ballot(skey(e[j]) < t));
+                for (int j = 0; j < NP; j++) c += __popcll(__ballot(skey(e[j]) < t));
                 if (c < first) {
                     ans = t;
                     c_lo = c;
@@ -1346,7 +1239,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
             if (one) {
                 uint64_t mn = ~0ull;
 #pragma unroll
-                for (int j = 0; j < EP; j++)
+                for (int j = 0; j < NP; j++)
                     if (skey(e[j]) >= ans && skey(e[j]) < mn) mn = skey(e[j]);
                 T = (uint32_t)wave_min_u64(mn);
             }
@@ -1355,7 +1248,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
             const uint64_t lt = lanemask_lt();
             int n1 = 0;
 #pragma unroll
-            for (int j = 0; j < EP; j++) {
+            for (int j = 0; j < NP; j++) {
                 const bool s = e[j] != ~0ull && skey(e[j]) < T;
                 const uint64_t b = __ballot(s);
                 if (s) {
@@ -1365,7 +1258,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
                 n1 += __popcll(b);
             }
 #pragma unroll
-            for (int j = 0; j < EP; j++) {
+            for (int j = 0; j < NP; j++) {
                 const bool s = e[j] != ~0ull && skey(e[j]) == T;
                 const uint64_t b = __ballot(s);
                 const int at = n1 + __popcll(b & lt);
@@ -1396,9 +1289,30 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
             const float tf = !(td < __builtin_huge_valf()) ? __builtin_huge_valf()
                              : metric == 0                 ? fmaf(D.eta, nq + td, td - nq) + 1e-37f
                                                            : fmaf(D.eta, nq + fabsf(td), td) + 1e-37f;
+            // (compacted through LDS, so that one round of row reads serves 64
+            // of them: rescored register by register, the few pairs that pass
+            // cost up to NP dependent round trips)
+            int np = 0;
 #pragma unroll
-            for (int j = 0; j < EP; j++)
-                if (e[j] != ~0ull && ord2f(skey(e[j])) <= tf) insert(score(e[j]));
+            for (int j = 0; j < NP; j++) {
+                const bool s = e[j] != ~0ull && ord2f(skey(e[j])) <= tf;
+                const uint64_t b = __ballot(s);
+                if (s) buf[np + __popcll(b & lt)] = e[j];   // at most 63 + 64 entries
+                np += __popcll(b);
+                if (np >= 64) {
+                    wave_sync();
+                    insert(score(buf[np - 64 + lane]));
+                    np -= 64;
+                    wave_sync();
+                }
+            }
+            wave_sync();
+            if (lane < np) insert(score(buf[lane]));
+            };
+            if (n <= 256)
+                rounds(std::integral_constant<int, 4>{});
+            else
+                rounds(std::integral_constant<int, EP>{});
         }
     }
     // with deferred pairs the partial lists hold keys only for the queries the
@@ -1535,6 +1449,8 @@ struct SearchWs {
     int32_t *probes_c;          // learned routing: centroid probes of the falling-back queries
     int32_t *fbq, *nfb;         // learned routing: the queries that fall back, their count
     int32_t *bad;               // query rows holding NaN or Inf (one counter per call)
+    uint16_t *clv;              // BF16 copy of an FP32 index's rows, with their norms (large searches)
+    float *cxn, *cle, *cln;
     int32_t *qord;              // bucketing order of the queries (grouped by constraint)
     QDesc *qterms;              // disjunctive searches: term descriptors (kMaxTerms per query)
 };
@@ -1546,10 +1462,14 @@ static int64_t tile_cap(int64_t sb, int64_t m, int64_t b) { return (sb * m + 63)
 
 
 static void carve(Arena &ar, SearchWs &w, int32_t nq, int32_t sb, int32_t b, int32_t m, int32_t k,
-                  bool own_ncand, bool own_nsurv, size_t qlow_row_bytes, const Router *router, bool defer,
-                  int32_t nc, bool disj) {
+                  bool own_ncand, bool own_nsurv, size_t qlow_row_bytes, const Router *router, int32_t defer,
+                  int32_t nc, bool disj, int64_t copy_n, int32_t copy_dpad) {
     const int32_t ngrp_max = (sb + kBucketQ - 1) / kBucketQ;
     w.bad = ar.take<int32_t>(1);
+    w.clv = copy_n ? ar.take<uint16_t>((size_t)copy_n * copy_dpad) : nullptr;
+    w.cxn = copy_n ? ar.take<float>((size_t)copy_n) : nullptr;
+    w.cle = copy_n ? ar.take<float>((size_t)copy_n) : nullptr;
+    w.cln = copy_n ? ar.take<float>((size_t)copy_n) : nullptr;
     w.qterms = disj ? ar.take<QDesc>((size_t)sb * kMaxTerms) : nullptr;
     w.qlow = qlow_row_bytes ? ar.take<uint8_t>((size_t)sb * qlow_row_bytes) : nullptr;
     w.qscale = qlow_row_bytes ? ar.take<float>((size_t)sb) : nullptr;
@@ -1566,7 +1486,7 @@ static void carve(Arena &ar, SearchWs &w, int32_t nq, int32_t sb, int32_t b, int
     w.entries = ar.take<int32_t>((size_t)sb * m);
     w.partials = ar.take<uint64_t>((size_t)sb * m * k);
     w.tau = ar.take<uint64_t>((size_t)sb);
-    w.dpos = defer ? ar.take<uint64_t>((size_t)sb * kDeferCap) : nullptr;
+    w.dpos = defer ? ar.take<uint64_t>((size_t)sb * defer) : nullptr;
     w.dcnt = defer ? ar.take<int32_t>((size_t)sb) : nullptr;
     w.oflow = defer ? ar.take<int32_t>((size_t)sb) : nullptr;
     // (main-pass tiles of 128 entries are listed by half: one more per partition)
@@ -1594,30 +1514,64 @@ static void carve(Arena &ar, SearchWs &w, int32_t nq, int32_t sb, int32_t b, int
 // Shape of one search call: which scan, keys per (query, probe), the
 // sub-batch that keeps the workspace within the budget.
 struct SearchPlan {
-    bool lowp, mfma, defer;
+    bool lowp, mfma;
+    int32_t prec, dpad;   // the scanned copy's format (an index without one: BF16 where the search makes its own)
+    int64_t copy_n;       // rows of the search's own copy (0: none)
+    int32_t defer;   // deferred pairs kept per query (0: no deferral)
     int32_t r, sb;
     size_t qlow_row;
     const Router *router;
 };
 
-static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget) {
+// Whether an exact search on an index without a low-precision copy makes a
+// BF16 one in its workspace and prunes with it (mode 0; mode 2 asks for the
+// plain scan).  The copy costs 0.19 ms for 1M x 128 however small the batch;
+// the plain scan costs 3.6 us for each time the batch visits every row once
+// (10k queries x 624 of 1024 partitions, 6094 visits: 21.9 ms), the pruning
+// scan 0.3 us: worth it from about 60 visits, and from the size (visits x
+// elements) at which the plain scan takes longer than the pruning path's
+// further launches.  Rows the copy supports, and a copy that leaves half of
+// the workspace budget to the batch.
+static int32_t copy_dpad(int32_t d) {
+    int32_t p = 32;
+    while (p < d) p <<= 1;
+    return p;
+}
+static size_t copy_bytes(const Index *ix) { return (size_t)ix->n * (2 * (size_t)copy_dpad(ix->d) + 12) + 2048; }
+static bool wants_copy(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget) {
+    if (ix->prec != CAPS_PREC_NONE || sp->mode != 0 || ix->d > 256 || (sp->flags & kSearchNoCopy)) return false;
+    const double visits = (double)nq * sp->nprobe / ix->b;
+    return visits >= 64.0 && visits * (double)ix->n * ix->d >= 1e9 && copy_bytes(ix) <= budget / 2;
+}
+
+static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget,
+                              bool may_copy) {
     const int32_t b = ix->b, m = sp->nprobe, k = sp->k;
     SearchPlan P;
+    P.prec = ix->prec;
+    P.dpad = ix->dpad;
+    P.copy_n = 0;
+    if (may_copy && wants_copy(ix, sp, nq, budget)) {
+        P.prec = CAPS_PREC_BF16;
+        P.dpad = copy_dpad(ix->d);
+        P.copy_n = ix->n;
+        budget -= copy_bytes(ix);
+    }
     // mode 1: approximate keys on the matrix cores, rescored at the merge;
     // mode 0 on an index with a low-precision copy: the matrix-core scan
     // with exact keys (bounds prune, survivors are rescored exactly);
     // otherwise (or mode 2) the plain FP32 scan
     P.lowp = sp->mode == 1;
-    P.mfma = P.lowp || (sp->mode == 0 && ix->prec != CAPS_PREC_NONE);
-    P.defer = P.mfma && !P.lowp;
+    P.mfma = P.lowp || (sp->mode == 0 && P.prec != CAPS_PREC_NONE);
+    P.defer = P.mfma && !P.lowp ? defer_cap(P.prec, k) : 0;
     P.r = P.lowp ? (sp->rerank > 0 ? sp->rerank : std::min(4 * k, kMaxK)) : k;
     P.router = sp->routing == 1 ? ix->router : nullptr;
-    P.qlow_row = P.mfma ? (size_t)ix->dpad * (ix->prec == CAPS_PREC_FP8 ? 1 : 2) : 0;
+    P.qlow_row = P.mfma ? (size_t)P.dpad * (P.prec == CAPS_PREC_FP8 ? 1 : 2) : 0;
     const size_t per_q = sizeof(float) * (size_t)b + sizeof(int32_t) * 5 * (size_t)m +
                          sizeof(uint64_t) * (size_t)m * P.r + sizeof(QDesc) + sizeof(uint64_t) +
                          2 * sizeof(int32_t) * (size_t)b / kBucketQ + P.qlow_row + 5 * sizeof(float) + 64 +
                          sizeof(int32_t) * (size_t)m +
-                         (P.defer ? sizeof(int32_t) * (size_t)(kDeferCap + 2 + m / 64) : 0) +
+                         (P.defer ? sizeof(uint64_t) * (size_t)P.defer + sizeof(int32_t) * (size_t)(2 + m / 64) : 0) +
                          sizeof(int4) * (size_t)m / 64 +
                          ((sp->flags & CAPS_SEARCH_DISJUNCTIVE) ? sizeof(QDesc) * kMaxTerms : 0) +
                          (P.router ? sizeof(uint16_t) * (size_t)(P.router->dpad + P.router->hid) + sizeof(float) +
@@ -1638,12 +1592,12 @@ static size_t measure_ws(const Index *ix, const caps_search_params *sp, const Se
     SearchWs W;
     Arena measure;
     carve(measure, W, nq, sb, ix->b, sp->nprobe, P.r, own_ncand, own_nsurv, P.qlow_row, P.router, P.defer,
-          bucket_classes(ix->h), (sp->flags & CAPS_SEARCH_DISJUNCTIVE) != 0);
+          bucket_classes(ix->h), (sp->flags & CAPS_SEARCH_DISJUNCTIVE) != 0, P.copy_n, P.dpad);
     return measure.off;
 }
 
 size_t search_workspace_bytes(const Index *ix, const caps_search_params *sp, int32_t nq) {
-    const SearchPlan P = plan_search(ix, sp, nq, default_budget(sp));
+    const SearchPlan P = plan_search(ix, sp, nq, default_budget(sp), true);
     return measure_ws(ix, sp, P, nq, P.sb, true, true);
 }
 
@@ -1703,7 +1657,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     // a caller workspace (no allocation) bounds the sub-batch: shrink it
     // until its layout fits
     const size_t budget = ex.ws ? ex.ws_bytes : default_budget(sp);
-    SearchPlan P = plan_search(ix, sp, nq, budget);
+    SearchPlan P = plan_search(ix, sp, nq, budget, !out_probes);
     size_t need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
     if (ex.ws) {
         while (need > ex.ws_bytes && P.sb > 1) {
@@ -1716,6 +1670,21 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             return CAPS_EUNSUPPORTED;
         }
     }
+    SearchWs W;
+    Arena ar;
+    if (ex.ws) {
+        ar.base = reinterpret_cast<char *>(ex.ws);
+    } else {
+        caps_status as = ws_alloc((void **)&ar.base, need, ix->device, st);
+        if (as == CAPS_ENOMEM && P.copy_n) {   // no room for the copy: the plain scan
+            (void)hipGetLastError();
+            P = plan_search(ix, sp, nq, budget, false);
+            need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
+            as = ws_alloc((void **)&ar.base, need, ix->device, st);
+        }
+        if (as != CAPS_OK) return as;
+    }
+    ar.cap = need;
     const bool lowp = P.lowp, mfma = P.mfma;
     const int32_t r = P.r, sb = P.sb;
     const int32_t nc = bucket_classes(h);
@@ -1727,16 +1696,19 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     int pb = 1;
     while (pb < b) pb <<= 1;
 
-    SearchWs W;
-    Arena ar;
-    ar.cap = need;
-    if (ex.ws) {
-        ar.base = reinterpret_cast<char *>(ex.ws);
-    } else {
-        const caps_status as = ws_alloc((void **)&ar.base, ar.cap, ix->device, st);
-        if (as != CAPS_OK) return as;
+    carve(ar, W, nq, sb, b, m, r, !out_ncand, !out_nsurv, qlow_row, router, P.defer, nc, disj, P.copy_n, P.dpad);
+    // the index as the scans see it: with the search's own copy, if it makes one
+    Index view;
+    if (P.copy_n) {
+        static_cast<IndexData &>(view) = *ix;
+        view.prec = P.prec;
+        view.dpad = P.dpad;
+        view.lvecs = W.clv;
+        view.xnorm = W.cxn;
+        view.lerr = W.cle;
+        view.lnrm = W.cln;
+        ix = &view;
     }
-    carve(ar, W, nq, sb, b, m, r, !out_ncand, !out_nsurv, qlow_row, router, P.defer, nc, disj);
 
     // the search proper; every exit below goes through the release at the end
     auto run = [&]() -> caps_status {
@@ -1758,16 +1730,25 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     int32_t *pcount = W.pcount, *pstart = W.pstart, *tstart = W.tstart;
 
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, W.bad, (int64_t)1, 0);
+    if (P.copy_n) {
+        prof_begin(CAPS_STAGE_PREP, st);
+        const caps_status cs = search_copy(ix->vecs, ix->n, d, P.dpad, W.clv, W.cxn, W.cle, W.cln, st);
+        if (cs != CAPS_OK) return cs;
+        prof_end(CAPS_STAGE_PREP, st);
+    }
     if (!probes_only) hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(nq, 256)), dim3(256), 0, st, nsurv, (int64_t)nq, 0);
     if (ex.surv_mask)
         hipLaunchKernelGGL(k_fill_u64, dim3(nblocks((int64_t)nq * mask_words, 256)), dim3(256), 0, st, ex.surv_mask,
                            (int64_t)nq * mask_words, 0ull);
 
     const bool has_labels = ix->sch.label_vocab > 0;
-    const size_t lds = mfma ? lowp_scan_lds(ix, r, lowp ? 0 : 2, disj) : scan_lds_bytes(d, k);
+    // (a search that makes its own copy has the plain scan's limits: whether a
+    // call is accepted does not depend on its batch size)
+    const bool fp32_limits = !mfma || P.copy_n;
+    const size_t lds = fp32_limits ? scan_lds_bytes(d, k) : 0;
     const int qb = mfma ? lowp_qb() : scan_waves(k) * kQPW;
     const ScanFn scan_fn = pick_scan(ix->metric, has_labels, d, k);
-    if (!probes_only && !mfma) {
+    if (!probes_only && fp32_limits) {
         int lds_max = 0;
         CAPS_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ix->device));
         if (lds > (size_t)lds_max) {
@@ -1775,7 +1756,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                       lds_max);
             return CAPS_EUNSUPPORTED;
         }
-        const caps_status ls = set_kernel_lds((const void *)scan_fn, lds, ix->device);
+        const caps_status ls = mfma ? CAPS_OK : set_kernel_lds((const void *)scan_fn, lds, ix->device);
         if (ls != CAPS_OK) return ls;
     }
         for (int32_t q0 = 0; q0 < nq; q0 += sb) {
@@ -1868,7 +1849,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             // did not fit.  (The approximate seed pass is cheap per probe but
             // its bound looser: m/24 seed probes there, enough that on the
             // 1M-point benchmark no query's pairs overflow.)
-            const bool seeded_exact = P.defer;
+            const bool seeded_exact = P.defer != 0;
             const int32_t *qord = nullptr;   // bucketing order of the queries (null: as given)
             if (ix->sch.n_dense > 0) {
                 int32_t kbits = 0;
@@ -1944,7 +1925,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     S.nsurv = out_nsurv && !seed_pass ? nsurv + q0 : nullptr;   // counted only when asked for
                     S.dpos = W.dpos;
                     S.dcnt = W.dcnt;
-                    S.dcap = kDeferCap;
+                    S.dcap = P.defer;
                     S.oflow = W.oflow;
                     S.rescue_grid = sp->rescue_grid;
                     const caps_status ls = lowp_scan(ix, S, st);
@@ -2022,7 +2003,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 D.pos = W.dpos;
                 D.cnt = W.dcnt;
                 D.oflow = W.oflow;
-                D.cap = kDeferCap;
+                D.cap = P.defer;
                 D.d = d;
                 D.vecs = ix->vecs;
                 D.q = q + (int64_t)q0 * d;
@@ -2030,15 +2011,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 D.qaux = W.qaux;
                 D.eta = exact_eta(ix);
             }
-            if (k <= 16)
-                hipLaunchKernelGGL(k_merge<16>, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, mcnt, sel, cand, nb, m,
-                                   k, ix->metric, oi, od, ncand + q0, D);
-            else if (k <= 32)
-                hipLaunchKernelGGL(k_merge<32>, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, mcnt, sel, cand, nb, m,
-                                   k, ix->metric, oi, od, ncand + q0, D);
-            else
-                hipLaunchKernelGGL(k_merge<64>, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, mcnt, sel, cand, nb, m,
-                                   k, ix->metric, oi, od, ncand + q0, D);
+            const auto merge_fn = k <= 16 ? (P.defer > 1024 ? k_merge<16, 32> : k_merge<16, 16>)
+                                  : k <= 32 ? k_merge<32, 32> : k_merge<64, 32>;
+            hipLaunchKernelGGL(merge_fn, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, mcnt, sel, cand, nb, m, k,
+                               ix->metric, oi, od, ncand + q0, D);
             prof_end(CAPS_STAGE_MERGE, st);
             CAPS_HIP(hipGetLastError());
         }

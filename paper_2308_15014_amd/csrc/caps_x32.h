@@ -12,10 +12,10 @@
 //  * chunks are 32 rows, staged by direct loads three chunks ahead into four
 //    buffers, with explicit per-wave wait counts and plain barriers;
 //  * the packed dense test runs only for the products where a score passed,
-//    the label signature test (signatures staged in LDS) only where that
-//    passed too.  The main pass makes the rest of the filter test (label
-//    slots, the terms of a disjunction; global reads) when it drains a wave's
-//    ring of pairs, one pair per lane, so that one round trip to memory
+//    the label signature test and a disjunction's terms' dense fields and
+//    signatures (staged data and registers) only where that passed too.  The
+//    main pass makes the rest of the filter test (label slots; global reads)
+//    when it drains a wave's ring of pairs, one pair per lane, so that one round trip to memory
 //    serves up to 64 pairs; a pair was tested as it was found before, one
 //    round trip for each block of products with any passing score.
 // Element r of lane l is point 8(r/4) + 4(l/32) + r%4 of the chunk and query
@@ -96,6 +96,12 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     typedef uint32_t (*Raw2)[PTS2 ? kXCH : 1];
     __shared__ __align__(16) uint64_t xsig[LAB ? 2 : 1][LAB ? kXCH : 1];   // signatures of the scored chunk
     __shared__ __align__(16) float xsc[F8 ? 2 : 1][F8 ? kXCH : 1];         // FP8 scales of the scored chunk
+    // seed pass: the label slots of narrow rows (8 of them), beside the rows of each buffer
+    constexpr bool SLOTS = SEED && LAB;
+    __shared__ __align__(16) uint16_t xl0[SLOTS ? kXCH * kMaxLabels : 1];
+    __shared__ __align__(16) uint16_t xl1[SLOTS ? kXCH * kMaxLabels : 1];
+    __shared__ __align__(16) uint16_t xl2[SLOTS ? kXCH * kMaxLabels : 1];
+    __shared__ __align__(16) uint16_t xl3[SLOTS ? kXCH * kMaxLabels : 1];
     __shared__ __align__(16) QDesc qds[LAB ? kXQB : 1];                    // the tile's filter descriptors
     __shared__ __align__(16) uint32_t xw[2][kXCH];
     __shared__ __align__(16) float xn[2][kXCH];
@@ -123,6 +129,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     const int g = lane >> 5, c32 = lane & 31;
     const bool has_dense = A.words != nullptr;
     const bool has_lab = LAB && A.sigs != nullptr;
+    const bool narrow = SLOTS && has_lab && A.lslots == kMaxLabels;
     const bool l2 = A.metric == 0;
     const float qnan = __builtin_nanf("");
     const float inf = __builtin_huge_valf();
@@ -136,6 +143,15 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     float my_tf = qnan, qa = 0.0f, qb = 0.0f;
     uint64_t my_tk = ~0ull;   // seed: the shared bound key at the tile's start
     uint64_t my_lsig = 0;     // signature bits of the query's label constraints
+    bool my_or = false;       // the query is a disjunction: its terms' dense fields and signatures
+    uint32_t tm[LAB ? kMaxTerms : 1], tv[LAB ? kMaxTerms : 1];
+    uint64_t tl[LAB ? kMaxTerms : 1];
+#pragma unroll
+    for (int i = 0; i < (LAB ? kMaxTerms : 1); i++) {   // (a term that is not there never matches)
+        tm[i] = 0;
+        tv[i] = 1;
+        tl[i] = 0;
+    }
     float my_qs = 1.0f;       // FP8 scale of the query
     if (own) {
         my_slot = ent[qi];
@@ -146,7 +162,18 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
             my_mask = qd.dmask;
             my_val = qd.dval;
             my_lsig = qd.lsig;
+            my_or = (qd.flags & kQOr) != 0;
             if (g == 0) qds[qi] = qd;   // (read by this wave only)
+            if (my_or) {
+#pragma unroll
+                for (int i = 0; i < kMaxTerms; i++) {
+                    if (i >= qd.nterm) break;
+                    const QDesc &td = A.qterms[(int64_t)my_qq * kMaxTerms + i];
+                    tm[i] = td.dmask;
+                    tv[i] = td.dval;
+                    tl[i] = td.lsig;
+                }
+            }
         } else {
             my_mask = A.qd[my_qq].dmask;
             my_val = A.qd[my_qq].dval;
@@ -252,13 +279,15 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         vrow[u] = row;
         voff[u] = (uint32_t)(row * ROWB + 16 * ((slot % V16) ^ ((row / RPL) & SWZ)));
     }
-    constexpr int OPC = UPW + 1 + (PTS2 ? 1 : 0);   // loads per wave per chunk
+    constexpr int OPC = UPW + 1 + (PTS2 ? 1 : 0) + (SLOTS ? 1 : 0);   // loads per wave per chunk
     const uint32_t *wsrc = has_dense ? A.words : reinterpret_cast<const uint32_t *>(A.xnorm);
     const float *psrc = w == 0   ? A.xnorm
                         : w == 1 ? A.lerr
                         : w == 2 ? A.lnrm
                                  : reinterpret_cast<const float *>(wsrc);
-    auto fetch_rows = [&](bool real, int32_t c0, int cn, uint8_t *dst) {
+    // (seed pass with labels: also the slots of rows 8w..8w+7, 16 bytes each;
+    // wide rows load the start of the copy in their place)
+    auto fetch_rows = [&](bool real, int32_t c0, int cn, uint8_t *dst, uint16_t *sdst) {
         const uint8_t *base = real ? A.lvecs + (int64_t)c0 * ROWB : A.lvecs;
 #pragma unroll
         for (int u = 0; u < UPW; u++) {
@@ -267,6 +296,14 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
             if (real && cn < kXCH) off -= (uint32_t)(max(vrow[u] - (cn - 1), 0) * ROWB);
             __builtin_amdgcn_global_load_lds(base + off, (__attribute__((address_space(3))) void *)(dst + 1024 * i), 16,
                                              0, 0);
+        }
+        if constexpr (SLOTS) {
+            if (lane < 8) {
+                const int64_t row = c0 + min(8 * w + lane, cn - 1);
+                const void *src = real && narrow ? (const void *)(A.slots + row * kMaxLabels) : (const void *)A.lvecs;
+                __builtin_amdgcn_global_load_lds(
+                    src, (__attribute__((address_space(3))) void *)(sdst + 8 * w * kMaxLabels), 16, 0, 0);
+            }
         }
     };
     auto fetch_points = [&](bool real, int32_t c0, int cn, float (*raw)[kXCH], Raw2 raw2) {
@@ -331,18 +368,32 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         }
     };
 
-    // The rest of the filter test for a pair that passed the packed dense test
-    // (exact for a conjunction's dense constraints; for a disjunction the
-    // fields all its terms share) and the signature test: the query's labels
-    // in the point's slots, or each term of a disjunction in full.
+    // The exact test of a pair's labels: the query's in the point's slots (its
+    // dense constraints were tested on the staged words), or each term of a
+    // disjunction in full.
     auto rest_passes = [&](int qj, uint32_t pos) -> bool {
         const QDesc &qd = qds[kXQ * w + qj];
-        const uint64_t sg = has_lab ? A.sigs[pos] : 0ull;
-        const uint16_t *sl = has_lab ? A.slots + (int64_t)pos * A.lslots : nullptr;
+        const uint64_t sg = A.sigs[pos];
+        const uint16_t *sl = A.slots + (int64_t)pos * A.lslots;
         if (qd.flags & kQOr)
-            return query_passes(qd, A.qterms + (int64_t)(ent[kXQ * w + qj] / A.m) * kMaxTerms, has_dense, has_lab,
+            return query_passes(qd, A.qterms + (int64_t)(ent[kXQ * w + qj] / A.m) * kMaxTerms, has_dense, true,
                                 has_dense ? A.words[pos] : 0u, sg, sl, A.lslots);
-        return !has_lab || point_passes(qd, false, true, 0u, sg, sl, A.lslots);
+        return point_passes(qd, false, true, 0u, sg, sl, A.lslots);
+    };
+
+    // The test on staged data only: the query's signature bits; for a
+    // disjunction some term's dense fields and signature bits.  It leaves
+    // rest_passes only the label slots (a disjunction of dense terms nothing).
+    const bool any_or = LAB && __builtin_amdgcn_ballot_w64(my_or) != 0;
+    auto staged_passes = [&](uint32_t wd, uint64_t sig) -> bool {
+        bool ok = (my_lsig & ~sig) == 0;
+        if (any_or) {
+            bool some = false;
+#pragma unroll
+            for (int i = 0; i < (LAB ? kMaxTerms : 1); i++) some |= (wd & tm[i]) == tv[i] && (tl[i] & ~sig) == 0;
+            ok &= some || !my_or;
+        }
+        return ok;
     };
 
     // deferred pairs of this wave: (CSR position, wave query) in a ring of
@@ -363,7 +414,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         const uint32_t pkey = v ? ring_key[slot] : 0u;
         vtail += n;
         if constexpr (LAB) {
-            if (v) v = rest_passes(qj, pos);
+            if (v && has_lab) v = rest_passes(qj, pos);   // (dense terms only: tested)
         }
         if (lane < kXQ) hist[lane] = 0;
         wave_sync();
@@ -394,17 +445,17 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     int fj = cj, rj = cj;
     int32_t fc0 = cc0, fend = cend, rc0 = cc0, rend = cend;
     advance(rj, rc0, rend);
-    auto fetch_next = [&](uint8_t *dst, float (*raw)[kXCH], Raw2 raw2) {
+    auto fetch_next = [&](uint8_t *dst, uint16_t *sdst, float (*raw)[kXCH], Raw2 raw2) {
         const bool fr = fj <= h, rr = rj <= h;
-        fetch_rows(fr, fc0, fr ? min(kXCH, fend - fc0) : 1, dst);
+        fetch_rows(fr, fc0, fr ? min(kXCH, fend - fc0) : 1, dst, sdst);
         fetch_points(rr, rc0, rr ? min(kXCH, rend - rc0) : 1, raw, raw2);
         if (fr) advance(fj, fc0, fend);
         if (rr) advance(rj, rc0, rend);
     };
     fetch_points(true, cc0, min(kXCH, cend - cc0), rw0, rg0);   // the inputs of chunk 0
-    fetch_next(xb0, rw1, rg1);
-    fetch_next(xb1, rw2, rg2);
-    fetch_next(xb2, rw3, rg3);
+    fetch_next(xb0, xl0, rw1, rg1);
+    fetch_next(xb1, xl1, rw2, rg2);
+    fetch_next(xb2, xl2, rw3, rg3);
     // the first three chunks have landed on every wave (waiting for all of
     // them lets the compiler's own wait tracking enter the loop with nothing
     // in flight)
@@ -420,7 +471,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     // Chunk k from buffer `cur` (point arrays `pb`); `nraw` holds the inputs
     // of chunk k + 1, whose point terms wave `ptw` (k % 4) computes; F_{k+3}
     // goes to `nxt` and `fraw`.  Returns whether another chunk follows.
-    auto step = [&](const uint8_t *cur, uint8_t *nxt, const int pb, float (*nraw)[kXCH], Raw2 nraw2,
+    auto step = [&](const uint8_t *cur, uint8_t *nxt, const uint16_t *scur, uint16_t *snxt, const int pb, float (*nraw)[kXCH], Raw2 nraw2,
                     float (*fraw)[kXCH], Raw2 fraw2, const int ptw) -> bool {
         const int j = cj;
         const int32_t c0 = cc0;
@@ -432,7 +483,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         __builtin_amdgcn_s_barrier();
         advance(cj, cc0, cend);
         const bool more = cj <= h;
-        fetch_next(nxt, fraw, fraw2);
+        fetch_next(nxt, snxt, fraw, fraw2);
         if (w == ptw && more) point_terms(nraw, nraw2, min(kXCH, cend - cc0), pb ^ 1);
         if (kXQ * w >= nqt) return more;   // a wave without queries (small batches) only stages
         {
@@ -443,7 +494,14 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
             // wave share constraints and a sub-partition's rows are grouped
             // by their values, so this is common)
             const uint32_t wa = xsum[pb][0], wo = xsum[pb][1];
-            const uint32_t miss = (my_val & ~wo) | (~my_val & my_mask & wa) | (((my_sel >> j) & 1u) ^ 1u);
+            uint32_t miss = (my_val & ~wo) | (~my_val & my_mask & wa) | (((my_sel >> j) & 1u) ^ 1u);
+            if (any_or) {   // a disjunction: some term may pass
+                bool some = !my_or;
+#pragma unroll
+                for (int i = 0; i < (LAB ? kMaxTerms : 1); i++)
+                    some |= ((tv[i] & ~wo) | (~tv[i] & tm[i] & wa)) == 0u;
+                if (!some) miss = 1u;
+            }
             if (!__builtin_amdgcn_ballot_w64(miss == 0u)) return more;
         }
 
@@ -504,7 +562,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
                 for (int e = 0; e < 4; e++) {
                     if (!((hit[e] >> lane) & 1ull) || (wv[e] & my_mask) != my_val) continue;
                     if constexpr (LAB) {
-                        if (!(my_lsig & ~xsig[pb][rb + e])) cand |= 1u << (4 * q4 + e);
+                        if (staged_passes(wv[e], has_lab ? xsig[pb][rb + e] : ~0ull)) cand |= 1u << (4 * q4 + e);
                     } else {
                         const uint64_t key = ((uint64_t)f2ord(canon0(acc[4 * q4 + e])) << 32) | (uint32_t)(c0 + rb + e);
                         if (key < lst[MH - 1]) offer(key);
@@ -520,7 +578,19 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
                     for (int e = 1; e < 16; e++) sc = r == e ? acc[e] : sc;
                     const uint32_t pos = (uint32_t)(c0 + 8 * (r >> 2) + 4 * g + (r & 3));
                     const uint64_t key = ((uint64_t)f2ord(canon0(sc)) << 32) | pos;
-                    if (key < lst[MH - 1] && rest_passes(c32, pos)) offer(key);
+                    if (!(key < lst[MH - 1])) continue;
+                    bool ok;
+                    if (!has_lab) {
+                        ok = true;   // (dense terms only: tested)
+                    } else if (narrow && !my_or) {   // the labels against the staged slots
+                        const uint16_t *sl = scur + (pos - c0) * kMaxLabels;
+                        const QDesc &qd = qds[kXQ * w + c32];
+                        ok = true;
+                        for (int i = 0; i < qd.nlab; i++) ok &= slots_hold(sl, kMaxLabels, qd.lab[i]);
+                    } else {
+                        ok = rest_passes(c32, pos);
+                    }
+                    if (ok) offer(key);
                 }
             }
         } else {
@@ -562,7 +632,8 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
                         if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
 #pragma unroll
                         for (int e = 0; e < 4; e++)
-                            hit[e] &= __builtin_amdgcn_ballot_w64((my_lsig & ~xsig[pb][rb + e]) == 0ull);
+                            hit[e] &= __builtin_amdgcn_ballot_w64(
+                                staged_passes(wv[e], has_lab ? xsig[pb][rb + e] : ~0ull));
                     }
                 }
 #pragma unroll
@@ -583,8 +654,8 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         }
         return more;
     };
-    while (step(xb0, xb3, 0, rw1, rg1, rw0, rg0, 0) && step(xb1, xb0, 1, rw2, rg2, rw1, rg1, 1) &&
-           step(xb2, xb1, 0, rw3, rg3, rw2, rg2, 2) && step(xb3, xb2, 1, rw0, rg0, rw3, rg3, 3)) {
+    while (step(xb0, xb3, xl0, xl3, 0, rw1, rg1, rw0, rg0, 0) && step(xb1, xb0, xl1, xl0, 1, rw2, rg2, rw1, rg1, 1) &&
+           step(xb2, xb1, xl2, xl1, 0, rw3, rg3, rw2, rg2, 2) && step(xb3, xb2, xl3, xl2, 1, rw0, rg0, rw3, rg3, 3)) {
     }
     if constexpr (SEED) {
         // the slot's list: the keys of half 0, then those of half 1 (2 MH <= r
