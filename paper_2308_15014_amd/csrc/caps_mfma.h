@@ -14,7 +14,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // ------------------------------------------------------------------ scan
 struct LowpArgs {
-    const int4 *tiles;          // per tile: partition, first entry, entries (0: no tile)
+    const int4 *tiles;          // per tile: partition, first entry, entries (0: no tile), share of the rows
+                                // (index | shares << 8; 0: all of them; only k_scan_x32 has shares)
     const int32_t *entries;
     const uint32_t *esel;       // level mask per entry, in entry order (null: read sel by slot)
     const uint32_t *sel;
@@ -38,7 +39,7 @@ struct LowpArgs {
     uint64_t *dpos;             // exact: per query deferred pairs, (ordered score of the element test << 32) | CSR position
     int32_t *dcnt;              // exact: their count per query
     int32_t *oflow;             // exact: per query flag, set when its pairs did not fit (rescue pass input)
-    const int32_t *rlist, *rcount;   // rescue pass: tiles with a flagged query and their number
+    const int32_t *rlist, *rcount;   // rescue pass: tiles with a flagged query and their number (null: every tile)
     int32_t m, h, b, r, metric, d, dcap, ntiles;   // ntiles: length of `tiles` (the grid's tile range)
     int32_t rhalves;            // rescue pass over 128-entry tiles: list entries are 2 tile + half
     float eta, gam;             // exact: relative rounding margin, MFMA accumulation bound
@@ -778,10 +779,11 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
         // a workgroup walking several tiles waits for all its waves between
         // them: the cursor and bound arrays (spo, lvw, qmx) are rewritten at
         // the start of a tile and read until its end
-        const int nr = *A.rcount;
+        const int nr = A.rlist ? *A.rcount : A.ntiles * (A.rhalves ? 2 : 1);
         for (int i = blockIdx.x; i < nr; i += gridDim.x) {
-            const int e = A.rlist[i];
+            const int e = A.rlist ? A.rlist[i] : i;
             int4 dsc = A.tiles[A.rhalves ? e >> 1 : e];
+            if (dsc.w & 255) continue;   // a further share of a tile listed before
             if (A.rhalves) {   // the 64 entries of one half of a 128-entry tile
                 dsc.y += kLQB * (e & 1);
                 dsc.z = min(kLQB, dsc.z - kLQB * (e & 1));

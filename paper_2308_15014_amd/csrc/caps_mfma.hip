@@ -402,11 +402,14 @@ static LowpFn pick_prec(int prec, int ns, bool lab, int r) {
     return pick_ns<CAPS_PREC_FP8, KIND>(ns, lab, r);
 }
 
-template <bool LAB>
-static LowpFn pick_x32_prec(int prec, int ns, int mode) {
-    if (prec == CAPS_PREC_BF16) return pick_x32<CAPS_PREC_BF16, LAB>(ns, mode);
-    if (prec == CAPS_PREC_FP16) return pick_x32<CAPS_PREC_FP16, LAB>(ns, mode);
-    return pick_x32<CAPS_PREC_FP8, LAB>(ns, mode);
+template <int PREC>
+static LowpFn pick_x32_filt(int filt, int ns, int mode) {
+    return filt == 0 ? pick_x32<PREC, 0>(ns, mode) : filt == 1 ? pick_x32<PREC, 1>(ns, mode) : pick_x32<PREC, 2>(ns, mode);
+}
+static LowpFn pick_x32_prec(int prec, int filt, int ns, int mode) {
+    if (prec == CAPS_PREC_BF16) return pick_x32_filt<CAPS_PREC_BF16>(filt, ns, mode);
+    if (prec == CAPS_PREC_FP16) return pick_x32_filt<CAPS_PREC_FP16>(filt, ns, mode);
+    return pick_x32_filt<CAPS_PREC_FP8>(filt, ns, mode);
 }
 
 // workgroups of the rescue pass (32 per compute unit): enough to spread a
@@ -474,7 +477,7 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     // (the 32 x 32 scan holds its arrays in static LDS)
     const bool x32 = S.kind == 4 || (S.kind == 1 && x32_kernel(ns, lab, S.nsurv != nullptr));
     const int xmode = S.kind == 4 ? (S.seed_mh == 1 ? 2 : 3) : S.nsurv ? 1 : 0;
-    const LowpFn fn = x32 ? (lab ? pick_x32_prec<true>(ix->prec, ns, xmode) : pick_x32_prec<false>(ix->prec, ns, xmode))
+    const LowpFn fn = x32 ? pick_x32_prec(ix->prec, S.disj ? 2 : lab ? 1 : 0, ns, xmode)
                       : S.kind == 0 ? pick_prec<0>(ix->prec, ns, lab, S.r)
                       : S.kind == 1 ? (S.nsurv ? pick_prec<3>(ix->prec, ns, lab, S.r) : pick_prec<1>(ix->prec, ns, lab, S.r))
                                     : pick_prec<2>(ix->prec, ns, lab, S.r);

@@ -24,6 +24,7 @@
 #include "caps_internal.h"
 #include "caps_mfma.h"
 #include "caps_query.h"
+#include "caps_small.h"
 
 namespace caps {
 
@@ -1160,15 +1161,13 @@ inline int32_t defer_cap(int32_t prec, int32_t k) { return prec == CAPS_PREC_FP8
 // again, at least 16, at most 64 (one per lane).
 __device__ inline int merge_first(int k) { return min(64, max(16, k + (k >> 1))); }
 
-// EP: pairs per lane of a full deferred list (cap / 64).
-template <int KM, int EP>
-__global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ partials,
-                                               const int32_t *__restrict__ pcnt,
-                                               const uint32_t *__restrict__ sel, const int32_t *__restrict__ cand,
-                                               int32_t nq, int32_t m, int32_t k, int32_t metric,
-                                               int32_t *__restrict__ ids, float *__restrict__ dist,
-                                               int32_t *__restrict__ ncand, Deferred D) {
-    __shared__ uint64_t mbuf[4][128], mkb[4][64];   // per wave: pairs to rescore, round 1's keys
+// Plain scan: partial lists padded with ~0; matrix-core lists are counted
+// (pcnt).  One wave per query, a sorted list of KM keys per lane.
+template <int KM>
+__global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ partials, const uint32_t *__restrict__ sel,
+                                               const int32_t *__restrict__ cand, int32_t nq, int32_t m, int32_t k,
+                                               int32_t metric, int32_t *__restrict__ ids, float *__restrict__ dist,
+                                               int32_t *__restrict__ ncand) {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (q >= nq) return;
@@ -1183,18 +1182,95 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
         }
         lst[0] = key < lst[0] ? key : lst[0];
     };
-    if (D.pos && !D.oflow[q]) {
+    int nc = 0;
+    for (int r = lane; r < m; r += 64) {
+        const int64_t slot = (int64_t)q * m + r;
+        if (sel[slot] == 0) continue;
+        nc += cand[slot];
+        const uint64_t *src = partials + slot * k;
+        for (int i = 0; i < k; i++) {
+            const uint64_t key = src[i];
+            if (key >= lst[KM - 1]) break;   // lists are sorted: the rest is worse
+            insert(key);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
+    if (lane == 0) ncand[q] = nc;
+    for (int r = 0; r < k; r++) {
+        const uint64_t best = wave_min_u64(lst[0]);
+        if (lane == 0) {
+            const int64_t o = (int64_t)q * k + r;
+            if (best == ~0ull) {
+                ids[o] = -1;
+                dist[o] = metric == 0 ? __builtin_huge_valf() : -__builtin_huge_valf();
+            } else {
+                ids[o] = (int32_t)(uint32_t)(best & 0xFFFFFFFFu);
+                const float key = ord2f((uint32_t)(best >> 32));
+                dist[o] = metric == 0 ? key : canon0(-key);
+            }
+        }
+        if (best != ~0ull && lst[0] == best) {
+#pragma unroll
+            for (int u = 0; u < KM - 1; u++) lst[u] = lst[u + 1];
+            lst[KM - 1] = ~0ull;
+        }
+    }
+}
+
+// Deferred pairs of the exact matrix-core scan.  One wave per query; the exact
+// keys found collect in an LDS pool whose best k are kept by rank (a sorted
+// list of 16 to 64 keys in each lane's registers, and k wave-wide minima at
+// the end, took 96 us per 10k queries at k = 10 and 162 us for 777 at k = 50).
+// EP: pairs per lane of a full deferred list (cap / 64).
+constexpr int kMergePool = 256;
+template <int EP>
+__global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict__ partials,
+                                                     const int32_t *__restrict__ pcnt,
+                                                     const uint32_t *__restrict__ sel, const int32_t *__restrict__ cand,
+                                                     int32_t nq, int32_t m, int32_t k, int32_t metric,
+                                                     int32_t *__restrict__ ids, float *__restrict__ dist,
+                                                     int32_t *__restrict__ ncand, Deferred D) {
+    __shared__ uint64_t pools[4][kMergePool], mbuf[4][128];   // per wave: keys, pairs to rescore
+    __shared__ int32_t npools[4];
+    const int wq = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = blockIdx.x * 4 + wq;
+    if (q >= nq) return;
+    uint64_t *pool = pools[wq];
+    int32_t *npool = &npools[wq];
+    uint64_t bound = ~0ull;   // k-th key of the pool when last reduced (lane 0 writes it)
+    if (D.oflow[q]) {   // rescanned: the rescue pass's lists
+        const int nc = gather_best<kMergePool>(pool, npool, partials, pcnt, sel, cand, (int64_t)q * m, 0, m, k, k);
+        if (lane == 0) ncand[q] = nc;
+    } else {
         const int n = min(D.cnt[q], D.cap);
         const float *qr = D.q + (int64_t)q * D.d;
         const uint64_t *src = D.pos + (int64_t)q * D.cap;
+        int nc = 0;   // (independent of the rest: its loads overlap)
+        for (int r = lane; r < m; r += 64) {
+            const int64_t slot = (int64_t)q * m + r;
+            nc += sel[slot] ? cand[slot] : 0;
+        }
+        if (lane == 0) *npool = 0;
+        wave_sync();
         auto score = [&](uint64_t ent) {   // the pair's exact key
             const int32_t pos = (int32_t)(uint32_t)ent;
             const float sc = exact_score<8>(D.vecs + (int64_t)pos * D.d, qr, D.d, metric == 0);
             return ((uint64_t)f2ord(sc) << 32) | (uint32_t)D.perm[pos];
         };
+        auto insert = [&](uint64_t key) {   // whole wave; ~0: none
+            const bool has = key != ~0ull;
+            const uint64_t b = __ballot(has);
+            if (*npool + __popcll(b) > kMergePool) buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
+            const int at = *npool;
+            if (has) pool[at + __popcll(b & lanemask_lt())] = key;
+            wave_sync();
+            if (lane == 0) *npool = at + __popcll(b);
+            wave_sync();
+        };
         const int first = merge_first(k);
         if (n <= first) {
-            for (int i = lane; i < n; i += 64) insert(score(src[i]));
+            insert(lane < n ? score(src[lane]) : ~0ull);   // (n <= 64)
         } else {
             // Two rounds.  The scan deferred a pair when its test score passed the
             // row bound of the query's seed key; the same test at any bound tau
@@ -1244,7 +1320,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
                 T = (uint32_t)wave_min_u64(mn);
             }
             // round 1: the pairs below T, then those at T, up to 64, compacted
-            uint64_t *buf = mbuf[threadIdx.x >> 6];
+            uint64_t *buf = mbuf[wq];
             const uint64_t lt = lanemask_lt();
             int n1 = 0;
 #pragma unroll
@@ -1269,20 +1345,10 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
                 n1 = min(64, n1 + __popcll(b));
             }
             wave_sync();
-            uint64_t k1 = ~0ull;
-            if (lane < n1) {
-                k1 = score(buf[lane]);
-                insert(k1);
-            }
-            // K: the k-th smallest of round 1's keys (distinct: the ids differ)
-            uint64_t *kb = mkb[threadIdx.x >> 6];
-            kb[lane] = k1;
-            wave_sync();
-            int rank = 0;
-            if (lane < n1)
-                for (int i = 0; i < n1; i++) rank += kb[i] < k1 ? 1 : 0;
-            const uint64_t kl = __ballot(lane < n1 && rank == k - 1);
-            const uint64_t K = kl ? readlane_u64(k1, __builtin_ctzll(kl)) : ~0ull;
+            insert(lane < n1 ? score(buf[lane]) : ~0ull);
+            // K: the k-th smallest of round 1's keys
+            buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
+            const uint64_t K = *npool == k ? pool[k - 1] : ~0ull;
             // round 2: the row bound at K's score, as the scan computes it
             const float td = bound_score(K);
             const float nq = D.qaux[4 * (int64_t)q + 1];
@@ -1301,56 +1367,36 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
                 np += __popcll(b);
                 if (np >= 64) {
                     wave_sync();
-                    insert(score(buf[np - 64 + lane]));
+                    const uint64_t key = score(buf[np - 64 + lane]);
+                    insert(key < K ? key : ~0ull);
                     np -= 64;
                     wave_sync();
                 }
             }
             wave_sync();
-            if (lane < np) insert(score(buf[lane]));
+            const uint64_t key = lane < np ? score(buf[lane]) : ~0ull;
+            insert(key < K ? key : ~0ull);
             };
             if (n <= 256)
                 rounds(std::integral_constant<int, 4>{});
             else
                 rounds(std::integral_constant<int, EP>{});
         }
-    }
-    // with deferred pairs the partial lists hold keys only for the queries the
-    // rescue pass rescanned (the main pass writes none)
-    const bool lists = !D.pos || D.oflow[q];
-    int nc = 0;
-    for (int r = lane; r < m; r += 64) {
-        const int64_t slot = (int64_t)q * m + r;
-        if (sel[slot] == 0) continue;
-        nc += cand[slot];
-        const uint64_t *src = partials + slot * k;
-        const int c = !lists ? 0 : pcnt ? min(pcnt[slot], k) : k;   // else lists padded with ~0
-        for (int i = 0; i < c; i++) {
-            const uint64_t key = src[i];
-            if (key >= lst[KM - 1]) break;   // lists are sorted: the rest is worse
-            insert(key);
-        }
-    }
+        buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
-    if (lane == 0) ncand[q] = nc;
-    for (int r = 0; r < k; r++) {
-        const uint64_t best = wave_min_u64(lst[0]);
-        if (lane == 0) {
-            const int64_t o = (int64_t)q * k + r;
-            if (best == ~0ull) {
-                ids[o] = -1;
-                dist[o] = metric == 0 ? __builtin_huge_valf() : -__builtin_huge_valf();
-            } else {
-                ids[o] = (int32_t)(uint32_t)(best & 0xFFFFFFFFu);
-                const float key = ord2f((uint32_t)(best >> 32));
-                dist[o] = metric == 0 ? key : canon0(-key);
-            }
-        }
-        if (best != ~0ull && lst[0] == best) {
-#pragma unroll
-            for (int u = 0; u < KM - 1; u++) lst[u] = lst[u + 1];
-            lst[KM - 1] = ~0ull;
+        for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
+        if (lane == 0) ncand[q] = nc;
+    }
+    if (lane < k) {
+        const int64_t o = (int64_t)q * k + lane;
+        const uint64_t best = lane < *npool ? pool[lane] : ~0ull;
+        if (best == ~0ull) {
+            ids[o] = -1;
+            dist[o] = metric == 0 ? __builtin_huge_valf() : -__builtin_huge_valf();
+        } else {
+            ids[o] = (int32_t)(uint32_t)(best & 0xFFFFFFFFu);
+            const float key = ord2f((uint32_t)(best >> 32));
+            dist[o] = metric == 0 ? key : canon0(-key);
         }
     }
 }
@@ -1453,7 +1499,17 @@ struct SearchWs {
     float *cxn, *cle, *cln;
     int32_t *qord;              // bucketing order of the queries (grouped by constraint)
     QDesc *qterms;              // disjunctive searches: term descriptors (kMaxTerms per query)
+    // small batches: entries and tiles of the seed round, tiles of the main
+    // round, entry cursors (the (query, partition) words take `scores`)
+    int32_t *sent, *scur;
+    uint32_t *sesel;
+    int4 *stiles[2];
 };
+
+// Tiles of one round of a small batch at most: 64-entry tiles, each shared by
+// up to kSmallSplit workgroups.
+constexpr int32_t kSmallSplit = 8;
+static int64_t small_tile_cap(int64_t nq, int64_t b) { return b * ((nq + 63) / 64) * kSmallSplit + kXcds; }
 
 // Tiles of one round at most: every (query, probe) entry in tiles of at
 // least 64 entries, plus one partial tile per partition, rounded up to the
@@ -1463,7 +1519,7 @@ static int64_t tile_cap(int64_t sb, int64_t m, int64_t b) { return (sb * m + 63)
 
 static void carve(Arena &ar, SearchWs &w, int32_t nq, int32_t sb, int32_t b, int32_t m, int32_t k,
                   bool own_ncand, bool own_nsurv, size_t qlow_row_bytes, const Router *router, int32_t defer,
-                  int32_t nc, bool disj, int64_t copy_n, int32_t copy_dpad) {
+                  int32_t nc, bool disj, int64_t copy_n, int32_t copy_dpad, bool small) {
     const int32_t ngrp_max = (sb + kBucketQ - 1) / kBucketQ;
     w.bad = ar.take<int32_t>(1);
     w.clv = copy_n ? ar.take<uint16_t>((size_t)copy_n * copy_dpad) : nullptr;
@@ -1502,6 +1558,10 @@ static void carve(Arena &ar, SearchWs &w, int32_t nq, int32_t sb, int32_t b, int
     w.pstart = ar.take<int32_t>(b + 1);
     w.tstart = ar.take<int32_t>(b + 1);
     w.tiles = ar.take<int4>(tile_cap(sb, m, b));
+    w.sent = small ? ar.take<int32_t>((size_t)sb * m) : nullptr;
+    w.sesel = small ? ar.take<uint32_t>((size_t)sb * m) : nullptr;
+    w.scur = small ? ar.take<int32_t>(2) : nullptr;
+    for (int i = 0; i < 2; i++) w.stiles[i] = small ? ar.take<int4>((size_t)small_tile_cap(sb, b)) : nullptr;
     w.rx = router ? ar.take<uint16_t>((size_t)sb * router->dpad) : nullptr;
     w.rh = router ? ar.take<uint16_t>((size_t)sb * router->hid) : nullptr;
     w.rbn = router ? ar.take<float>((size_t)router->nout) : nullptr;
@@ -1517,6 +1577,7 @@ struct SearchPlan {
     bool lowp, mfma;
     int32_t prec, dpad;   // the scanned copy's format (an index without one: BF16 where the search makes its own)
     int64_t copy_n;       // rows of the search's own copy (0: none)
+    bool small, direct;   // the small-batch path, without tiles
     int32_t defer;   // deferred pairs kept per query (0: no deferral)
     int32_t r, sb;
     size_t qlow_row;
@@ -1539,7 +1600,7 @@ static int32_t copy_dpad(int32_t d) {
 }
 static size_t copy_bytes(const Index *ix) { return (size_t)ix->n * (2 * (size_t)copy_dpad(ix->d) + 12) + 2048; }
 static bool wants_copy(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget) {
-    if (ix->prec != CAPS_PREC_NONE || sp->mode != 0 || ix->d > 256 || (sp->flags & kSearchNoCopy)) return false;
+    if (ix->prec != CAPS_PREC_NONE || sp->mode != 0 || ix->d > 256 || (sp->flags & kSearchTightWs)) return false;
     const double visits = (double)nq * sp->nprobe / ix->b;
     return visits >= 64.0 && visits * (double)ix->n * ix->d >= 1e9 && copy_bytes(ix) <= budget / 2;
 }
@@ -1578,6 +1639,16 @@ static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int
                                          sizeof(int32_t) * (size_t)(m + 1)
                                    : 0);
     P.sb = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)std::max(nq, 1), budget / per_q));
+    // A small batch takes the path of caps_small.hip when it is one sub-batch
+    // (the centroid routing and FP32 arithmetic of modes 0 and 2 only).
+    // Its tables (two rounds of tiles, of b x kSmallSplit at least) stay a small
+    // part of the budget, so that a budget that held a query still does.
+    P.small = !P.lowp && !P.router && P.sb >= nq && small_fits(b, ix->d, nq);
+    P.direct = P.small && direct_fits(ix, nq, m);
+    if (P.small && !P.direct) {
+        const size_t tables = 2 * sizeof(int4) * (size_t)small_tile_cap(nq, b) + 8 * (size_t)nq * m;
+        P.small = tables <= budget / 8 && (!(sp->flags & kSearchTightWs) || tables <= (size_t)256 << 10);
+    }
     return P;
 }
 
@@ -1592,7 +1663,7 @@ static size_t measure_ws(const Index *ix, const caps_search_params *sp, const Se
     SearchWs W;
     Arena measure;
     carve(measure, W, nq, sb, ix->b, sp->nprobe, P.r, own_ncand, own_nsurv, P.qlow_row, P.router, P.defer,
-          bucket_classes(ix->h), (sp->flags & CAPS_SEARCH_DISJUNCTIVE) != 0, P.copy_n, P.dpad);
+          bucket_classes(ix->h), (sp->flags & CAPS_SEARCH_DISJUNCTIVE) != 0, P.copy_n, P.dpad, P.small && !P.direct);
     return measure.off;
 }
 
@@ -1660,6 +1731,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     SearchPlan P = plan_search(ix, sp, nq, budget, !out_probes);
     size_t need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
     if (ex.ws) {
+        if (need > ex.ws_bytes && P.small) {   // (without the small-batch tables)
+            P.small = P.direct = false;
+            need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
+        }
         while (need > ex.ws_bytes && P.sb > 1) {
             P.sb = std::max<int32_t>(1, (int32_t)((double)P.sb * (double)ex.ws_bytes / (double)need * 0.95));
             need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
@@ -1696,7 +1771,8 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     int pb = 1;
     while (pb < b) pb <<= 1;
 
-    carve(ar, W, nq, sb, b, m, r, !out_ncand, !out_nsurv, qlow_row, router, P.defer, nc, disj, P.copy_n, P.dpad);
+    carve(ar, W, nq, sb, b, m, r, !out_ncand, !out_nsurv, qlow_row, router, P.defer, nc, disj, P.copy_n, P.dpad,
+          P.small && !P.direct);
     // the index as the scans see it: with the search's own copy, if it makes one
     Index view;
     if (P.copy_n) {
@@ -1729,14 +1805,17 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     int32_t *hist = W.hist, *hscan = W.hscan, *htotal = W.htotal;
     int32_t *pcount = W.pcount, *pstart = W.pstart, *tstart = W.tstart;
 
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, W.bad, (int64_t)1, 0);
+    if (sp->flags & CAPS_SEARCH_VALIDATE)   // (read with validation only)
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, W.bad, (int64_t)1, 0);
     if (P.copy_n) {
         prof_begin(CAPS_STAGE_PREP, st);
         const caps_status cs = search_copy(ix->vecs, ix->n, d, P.dpad, W.clv, W.cxn, W.cle, W.cln, st);
         if (cs != CAPS_OK) return cs;
         prof_end(CAPS_STAGE_PREP, st);
     }
-    if (!probes_only) hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(nq, 256)), dim3(256), 0, st, nsurv, (int64_t)nq, 0);
+    const bool small = P.small && !probes_only && sb >= nq;
+    if (!probes_only && !small)
+        hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(nq, 256)), dim3(256), 0, st, nsurv, (int64_t)nq, 0);
     if (ex.surv_mask)
         hipLaunchKernelGGL(k_fill_u64, dim3(nblocks((int64_t)nq * mask_words, 256)), dim3(256), 0, st, ex.surv_mask,
                            (int64_t)nq * mask_words, 0ull);
@@ -1767,6 +1846,49 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             // the probes query returns them sorted; a search takes the best m as
             // a set with the s_seed best first
             const int32_t topm_s = probes_only ? -1 : s_seed;
+            if (small) {
+                prof_begin(CAPS_STAGE_ROUTE, st);
+                FrontArgs F{};
+                F.q = q;
+                F.d = d;
+                F.con_off = con_off;
+                F.con_attr = con_attr;
+                F.con_val = con_val;
+                F.n_con = n_con;
+                F.sch = ix->sch;
+                F.disj = disj;
+                F.cent = ix->cent;
+                F.cnorm = ix->cnorm;
+                F.b = b;
+                F.metric = ix->metric;
+                F.m = m;
+                F.s = P.direct ? m : s_seed;
+                F.tags = ix->tags;
+                F.offs = ix->offs;
+                F.h = h;
+                F.rule = sp->rule;
+                F.qd = qd;
+                F.qterms = W.qterms;
+                F.probes = probes;
+                F.sel = sel;
+                F.cand = cand;
+                F.ncand = ncand;
+                F.nsurv = nsurv;
+                F.tau = tau;
+                F.dcnt = W.dcnt;
+                F.oflow = W.oflow;
+                F.bad = W.bad;
+                F.qlow = mfma && !P.direct ? W.qlow : nullptr;
+                F.qscale = W.qscale;
+                F.qaux = W.qaux;
+                F.dpad = ix->dpad;
+                F.prec = ix->prec;
+                F.pmask = P.direct ? nullptr : reinterpret_cast<uint32_t *>(scores);
+                F.cursor = P.direct ? W.pstart : W.scur;   // (unused by the direct scan)
+                const caps_status fs = small_front(F, nb, ix->device, st);
+                if (fs != CAPS_OK) return fs;
+                prof_end(CAPS_STAGE_ROUTE, st);
+            } else {
             prof_begin(CAPS_STAGE_PREP, st);
             hipLaunchKernelGGL(k_qprep, dim3(nblocks(nb, 128)), dim3(128), 0, st, con_off + q0, con_attr,
                                con_val, n_con, nb, ix->sch, (int32_t)disj, qd, W.qterms);
@@ -1829,16 +1951,44 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 CAPS_HIP(hipGetLastError());
                 continue;
             }
+            }
             if (ex.surv_mask)
                 hipLaunchKernelGGL(k_surv_mask, dim3(nblocks(pairs, 4)), dim3(256), 0, st, probes, sel, nb, m, qd, W.qterms, ix->offs,
                                    h, ix->words, ix->sigs, ix->slots, ix->lslots, ex.surv_mask + (int64_t)q0 * mask_words,
                                mask_words);
+            if (small && P.direct) {
+                DirectArgs A{};
+                A.probes = probes;
+                A.sel = sel;
+                A.qd = qd;
+                A.qterms = W.qterms;
+                A.offs = ix->offs;
+                A.perm = ix->perm;
+                A.vecs = ix->vecs;
+                A.q = q;
+                A.words = ix->words;
+                A.sigs = ix->sigs;
+                A.slots = ix->slots;
+                A.lslots = ix->lslots;
+                A.d = d;
+                A.m = m;
+                A.h = h;
+                A.k = k;
+                A.metric = ix->metric;
+                A.partials = partials;
+                A.nsurv = out_nsurv;
+                const caps_status ds = small_direct(A, nb, out_ids, out_dist, st);
+                if (ds != CAPS_OK) return ds;
+                continue;
+            }
+            if (!small) {
             hipLaunchKernelGGL(k_fill_u64, dim3(nblocks(nb, 256)), dim3(256), 0, st, tau, (int64_t)nb, ~0ull);
             if (P.defer) {
                 hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(nb, 256)), dim3(256), 0, st, W.dcnt, (int64_t)nb, 0);
                 hipLaunchKernelGGL(k_fill_i32, dim3(nblocks(nb, 256)), dim3(256), 0, st, W.oflow, (int64_t)nb, 0);
             }
             prof_end(CAPS_STAGE_SELECT, st);
+            }
             // Two rounds: the first probes of every query (best first) give each
             // query a tight seed bound on its final r-th key; the remaining probes
             // are scanned against it.  Exact keys on the matrix cores: the first
@@ -1851,7 +2001,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             // 1M-point benchmark no query's pairs overflow.)
             const bool seeded_exact = P.defer != 0;
             const int32_t *qord = nullptr;   // bucketing order of the queries (null: as given)
-            if (ix->sch.n_dense > 0) {
+            if (ix->sch.n_dense > 0 && !small) {
                 int32_t kbits = 0;
                 for (int a = 0; a < ix->sch.n_dense; a++) kbits += ix->sch.field_bits[a] + 1;
                 const int32_t shift = std::max(0, kbits - kQordBits), nk = 1 << (kbits - shift);
@@ -1861,17 +2011,58 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 prof_end(CAPS_STAGE_SELECT, st);
                 qord = W.qord;
             }
+            // tile width of a round: the exact main pass and the seed lists may
+            // run 128-entry tiles
+            const int seed_mh = seeded_exact ? lowp_seed_x32(ix, disj, r, k, s_seed) : 0;
+            int qbs[2], splits[2] = {1, 1};
+            for (int round = 0; round < 2; round++) {
+                const bool seed_pass = seeded_exact && round == 0;
+                qbs[round] = !mfma || lowp || (seed_pass && !seed_mh) ? qb
+                                                                      : lowp_qb_main(ix, disj, !seed_pass && out_nsurv);
+            }
+            if (small) {
+                // Few tiles leave most of the chip idle: up to kSmallSplit
+                // workgroups share a tile's rows (in 32-row chunks, at least two
+                // each on average) until there are about four per compute unit.
+                SmallRound R[2] = {};
+                for (int round = 0; round < 2; round++) {
+                    const bool seed_pass = seeded_exact && round == 0;
+                    const int32_t nslot = round == 0 ? s_seed : seeded_exact ? m : m - s_seed;
+                    if (nslot <= 0) continue;
+                    const bool x32 = seed_pass ? seed_mh > 0 : mfma && qbs[1] != qb;
+                    const int64_t tl = std::min<int64_t>((int64_t)b * ((nb + qbs[round] - 1) / qbs[round]), (int64_t)nb * nslot);
+                    int64_t split = std::min<int64_t>({1024 / std::max<int64_t>(1, tl), ix->n / b / 64, kSmallSplit});
+                    if (seed_pass) split = std::min<int64_t>(split, r / (2 * std::max(1, seed_mh)));
+                    splits[round] = x32 ? (int)std::max<int64_t>(1, split) : 1;
+                    R[round].entries = round == 0 ? W.sent : entries;
+                    R[round].esel = !seeded_exact ? nullptr : round == 0 ? W.sesel : W.esel;
+                    R[round].tiles = W.stiles[round];
+                    R[round].which = round == 0 ? (s_seed < m ? 1 : 0) : seeded_exact ? 0 : 2;
+                    R[round].qb = qbs[round];
+                    R[round].split = splits[round];
+                }
+                prof_begin(CAPS_STAGE_SELECT, st);
+                const caps_status ts = small_tiles(reinterpret_cast<const uint32_t *>(scores), nb, b, m, R[0], R[1],
+                                                   W.scur, ix->device, st);
+                if (ts != CAPS_OK) return ts;
+                prof_end(CAPS_STAGE_SELECT, st);
+            }
             for (int round = 0; round < 2; round++) {
                 const int32_t r0 = round == 0 || seeded_exact ? 0 : s_seed;
                 const int32_t r1 = round == 0 ? s_seed : m;
                 if (r0 >= r1) continue;
-                // tile width of this round: the exact main pass and the seed lists may
-                // run 128-entry tiles
                 const bool seed_pass = seeded_exact && round == 0;
-                const int seed_mh = seed_pass ? lowp_seed_x32(ix, disj, r, k, s_seed) : 0;
-                const int qbr = !mfma || lowp             ? qb
-                                : seed_pass && !seed_mh   ? qb
-                                                          : lowp_qb_main(ix, disj, !seed_pass && out_nsurv);
+                const int qbr = qbs[round];
+                const int32_t *ent = entries;
+                const uint32_t *esel = W.esel;
+                const int4 *tiles = W.tiles;
+                int64_t grid = 0;
+                if (small) {
+                    grid = (int64_t)b * ((nb + qbr - 1) / qbr) * splits[round];
+                    ent = round == 0 ? W.sent : entries;
+                    esel = round == 0 ? W.sesel : W.esel;
+                    tiles = W.stiles[round];
+                } else {
                 prof_begin(CAPS_STAGE_SELECT, st);
                 const unsigned ggrid = (unsigned)((ngrp + kXcds - 1) / kXcds * kXcds);   // XCD-mapped groups
                 hipLaunchKernelGGL(k_bucket_hist, dim3(ggrid), dim3(kBucketT), sizeof(int32_t) * (size_t)b, st, probes, sel,
@@ -1883,15 +2074,14 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, st, hscan, htotal, b, ngrp, qbr, pstart, pcount,
                                    tstart);
                 const int64_t max_tiles = ((int64_t)nb * (r1 - r0) + qbr - 1) / qbr + b;
-                const int64_t grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
+                grid = (max_tiles + kXcds - 1) / kXcds * kXcds;
                 hipLaunchKernelGGL(k_tile_desc, dim3(nblocks(grid, 256)), dim3(256), 0, st, tstart, pstart, pcount, b,
                                    qbr, (int32_t)grid, W.tiles);
                 // the fill packs each entry's class when entries stay below 2^27
                 const int32_t nc_pack = nc > 1 && (int64_t)nb * m < ((int64_t)1 << kClassShift) ? nc : 1;
                 hipLaunchKernelGGL(k_bucket_fill, dim3(ggrid), dim3(kBucketT), sizeof(int32_t) * (size_t)b, st, probes, sel,
                                    qord, nb, m, r0, r1, b, ngrp, hscan, nc_pack, entries, nc > 1 ? nullptr : W.esel);
-                const int32_t *ent = entries;
-                const uint32_t *esel = W.esel;   // (the class sort writes the level masks itself)
+                // (the class sort writes the level masks itself)
                 if (nc > 1) {
                     hipLaunchKernelGGL(k_class_sort, dim3(b), dim3(kClassW * 64), 0, st, entries, sel, pstart, pcount, nc,
                                        (int32_t)(nc_pack > 1), W.entries2, W.esel);
@@ -1899,16 +2089,17 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 }
                 CAPS_HIP(hipGetLastError());
                 prof_end(CAPS_STAGE_SELECT, st);
+                }
                 if (mfma) {
                     LowpScan S{};
                     S.nb = nb;
                     S.m = m;
                     S.r = r;
-                    S.kind = seed_mh ? 4 : lowp || seed_pass ? 0 : 1;
+                    S.kind = seed_pass && seed_mh ? 4 : lowp || seed_pass ? 0 : 1;
                     S.seed_mh = seed_mh;
                     S.stage = seed_pass ? CAPS_STAGE_SEED : CAPS_STAGE_SCAN;
                     S.max_tiles = grid;
-                    S.tiles = W.tiles;
+                    S.tiles = tiles;
                     S.entries = ent;
                     S.esel = esel;
                     S.sel = sel;
@@ -1931,13 +2122,15 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     const caps_status ls = lowp_scan(ix, S, st);
                     if (ls != CAPS_OK) return ls;
                     if (S.kind == 1) {   // rescue pass over the tiles that hold a flagged query
-                        hipLaunchKernelGGL(k_rescue_init, dim3(1), dim3(1024), 0, st, W.oflow, nb, W.rcount);
-                        hipLaunchKernelGGL(k_rescue_tiles, dim3(nblocks(grid, 256)), dim3(256), 0, st, W.tiles,
-                                           (int32_t)grid, ent, m, W.oflow, qb, (int32_t)(qbr != qb), W.rlist,
-                                           W.rcount);
+                        if (!small) {   // (a small batch's few tiles are all looked at)
+                            hipLaunchKernelGGL(k_rescue_init, dim3(1), dim3(1024), 0, st, W.oflow, nb, W.rcount);
+                            hipLaunchKernelGGL(k_rescue_tiles, dim3(nblocks(grid, 256)), dim3(256), 0, st, W.tiles,
+                                               (int32_t)grid, ent, m, W.oflow, qb, (int32_t)(qbr != qb), W.rlist,
+                                               W.rcount);
+                        }
                         S.kind = 2;
                         S.rhalves = qbr != qb;
-                        S.rlist = W.rlist;
+                        S.rlist = small ? nullptr : W.rlist;
                         S.rcount = W.rcount;
                         S.nsurv = nullptr;
                         S.stage = CAPS_STAGE_RESCUE;
@@ -1946,7 +2139,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     }
                 } else {
                     ScanArgs A;
-                    A.tiles = W.tiles;
+                    A.tiles = tiles;
                     A.ntiles = (int32_t)grid;
                     A.entries = ent;
                     A.sel = sel;
@@ -1969,7 +2162,8 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     A.b = b;
                     A.k = k;
                     prof_begin(CAPS_STAGE_SCAN, st);
-                    hipLaunchKernelGGL(scan_fn, dim3((unsigned)grid), dim3(scan_waves(k) * 64), lds, st, A);
+                    hipLaunchKernelGGL(scan_fn, dim3((unsigned)((grid + kXcds - 1) / kXcds * kXcds)),
+                                       dim3(scan_waves(k) * 64), lds, st, A);
                     prof_end(CAPS_STAGE_SCAN, st);
                     CAPS_HIP(hipGetLastError());
                 }
@@ -1997,7 +2191,6 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             prof_begin(CAPS_STAGE_MERGE, st);
             int32_t *oi = out_ids + (int64_t)q0 * k;
             float *od = out_dist + (int64_t)q0 * k;
-            const int32_t *mcnt = mfma ? W.pcnt : nullptr;   // matrix-core lists are counted, plain ones padded
             Deferred D{};
             if (P.defer) {
                 D.pos = W.dpos;
@@ -2011,10 +2204,14 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 D.qaux = W.qaux;
                 D.eta = exact_eta(ix);
             }
-            const auto merge_fn = k <= 16 ? (P.defer > 1024 ? k_merge<16, 32> : k_merge<16, 16>)
-                                  : k <= 32 ? k_merge<32, 32> : k_merge<64, 32>;
-            hipLaunchKernelGGL(merge_fn, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, mcnt, sel, cand, nb, m, k,
-                               ix->metric, oi, od, ncand + q0, D);
+            if (P.defer) {
+                hipLaunchKernelGGL(P.defer > 1024 ? k_merge_defer<32> : k_merge_defer<16>, dim3(nblocks(nb, 4)), dim3(256),
+                                   0, st, partials, W.pcnt, sel, cand, nb, m, k, ix->metric, oi, od, ncand + q0, D);
+            } else {
+                const auto merge_fn = k <= 16 ? k_merge<16> : k <= 32 ? k_merge<32> : k_merge<64>;
+                hipLaunchKernelGGL(merge_fn, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, sel, cand, nb, m, k,
+                                   ix->metric, oi, od, ncand + q0);
+            }
             prof_end(CAPS_STAGE_MERGE, st);
             CAPS_HIP(hipGetLastError());
         }

@@ -404,7 +404,7 @@ extern "C" caps_status caps_server_create(const caps_index *idx, const caps_serv
     S->sp.rerank = p->rerank;
     S->sp.routing = p->routing;
     S->sp.flags = p->flags & CAPS_SEARCH_DISJUNCTIVE;   // (the budget is the server's own: not a sub-batch cap)
-    if (p->workspace_bytes > 0) S->sp.flags |= kSearchNoCopy;   // (batches in flight share it: no copy each)
+    if (p->workspace_bytes > 0) S->sp.flags |= kSearchTightWs;   // (batches in flight share it)
     S->d = ix.d;
     S->k = p->k;
     // batch cap: largest size whose search workspace fits the budget

@@ -62,8 +62,10 @@ __device__ inline f32x16 mma32(uint4 a, uint4 b, f32x16 c) {
 }
 
 // Register budget per SIMD: four waves; three with the label state.
-template <int PREC, int NS, int MODE, int MH, bool LAB>
-__global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 3 : 4))) void k_scan_x32(LowpArgs A) {
+template <int PREC, int NS, int MODE, int MH, int FILT>
+__global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ? 3 : 4))) void k_scan_x32(LowpArgs A) {
+    constexpr bool LAB = FILT != 0;     // label tests (an index with labels)
+    constexpr bool DISJ = FILT == 2;    // and disjunctions, on any index
     static_assert(!(LAB && MODE == 1), "survivors of label tests are counted by k_scan_mfma");
     constexpr bool COUNT = MODE == 1;   // survivor counts of the exact filter
     constexpr bool SEED = MODE == 2;    // approximate keys: per query and probe the best 2 MH
@@ -124,6 +126,9 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     const int nqt = dsc.z;
     const int32_t *ent = A.entries + dsc.y;
     const int h = A.h;
+    // the tile's share of the rows: chunks share, share + nshare, ... (small
+    // batches; a whole tile has w = 0)
+    const int share = dsc.w & 255, nshare = max(1, dsc.w >> 8);
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // (wave-uniform: kept in a scalar register)
     const int g = lane >> 5, c32 = lane & 31;
@@ -144,10 +149,10 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     uint64_t my_tk = ~0ull;   // seed: the shared bound key at the tile's start
     uint64_t my_lsig = 0;     // signature bits of the query's label constraints
     bool my_or = false;       // the query is a disjunction: its terms' dense fields and signatures
-    uint32_t tm[LAB ? kMaxTerms : 1], tv[LAB ? kMaxTerms : 1];
-    uint64_t tl[LAB ? kMaxTerms : 1];
+    uint32_t tm[DISJ ? kMaxTerms : 1], tv[DISJ ? kMaxTerms : 1];
+    uint64_t tl[DISJ ? kMaxTerms : 1];
 #pragma unroll
-    for (int i = 0; i < (LAB ? kMaxTerms : 1); i++) {   // (a term that is not there never matches)
+    for (int i = 0; i < (DISJ ? kMaxTerms : 1); i++) {   // (a term that is not there never matches)
         tm[i] = 0;
         tv[i] = 1;
         tl[i] = 0;
@@ -162,9 +167,9 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
             my_mask = qd.dmask;
             my_val = qd.dval;
             my_lsig = qd.lsig;
-            my_or = (qd.flags & kQOr) != 0;
+            my_or = DISJ && (qd.flags & kQOr) != 0;
             if (g == 0) qds[qi] = qd;   // (read by this wave only)
-            if (my_or) {
+            if (DISJ && my_or) {
 #pragma unroll
                 for (int i = 0; i < kMaxTerms; i++) {
                     if (i >= qd.nterm) break;
@@ -252,9 +257,13 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         c0 = __builtin_amdgcn_readlane(spv, j);
         end = __builtin_amdgcn_readlane(spv, j + 1);
     };
-    auto advance = [&](int &j, int32_t &c0, int32_t &end) {
+    auto advance1 = [&](int &j, int32_t &c0, int32_t &end) {
         c0 += kXCH;
         if (c0 >= end) next_level(j, c0, end);
+    };
+    auto advance = [&](int &j, int32_t &c0, int32_t &end) {
+        advance1(j, c0, end);
+        for (int i = 1; i < nshare; i++) advance1(j, c0, end);
     };
 
     // Staging.  Every wave issues the same loads per chunk (UPW row loads
@@ -375,7 +384,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         const QDesc &qd = qds[kXQ * w + qj];
         const uint64_t sg = A.sigs[pos];
         const uint16_t *sl = A.slots + (int64_t)pos * A.lslots;
-        if (qd.flags & kQOr)
+        if (DISJ && (qd.flags & kQOr))
             return query_passes(qd, A.qterms + (int64_t)(ent[kXQ * w + qj] / A.m) * kMaxTerms, has_dense, true,
                                 has_dense ? A.words[pos] : 0u, sg, sl, A.lslots);
         return point_passes(qd, false, true, 0u, sg, sl, A.lslots);
@@ -384,13 +393,13 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     // The test on staged data only: the query's signature bits; for a
     // disjunction some term's dense fields and signature bits.  It leaves
     // rest_passes only the label slots (a disjunction of dense terms nothing).
-    const bool any_or = LAB && __builtin_amdgcn_ballot_w64(my_or) != 0;
+    const bool any_or = DISJ && __builtin_amdgcn_ballot_w64(my_or) != 0;
     auto staged_passes = [&](uint32_t wd, uint64_t sig) -> bool {
         bool ok = (my_lsig & ~sig) == 0;
         if (any_or) {
             bool some = false;
 #pragma unroll
-            for (int i = 0; i < (LAB ? kMaxTerms : 1); i++) some |= (wd & tm[i]) == tv[i] && (tl[i] & ~sig) == 0;
+            for (int i = 0; i < (DISJ ? kMaxTerms : 1); i++) some |= (wd & tm[i]) == tv[i] && (tl[i] & ~sig) == 0;
             ok &= some || !my_or;
         }
         return ok;
@@ -437,8 +446,13 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     int cj = -1;
     int32_t cc0 = 0, cend = 0;
     next_level(cj, cc0, cend);
+    for (int i = 0; i < share; i++) advance1(cj, cc0, cend);
     if (cj > h) {   // nothing to scan
-        if (SEED && g == 0 && own) A.pcnt[my_slot] = 0;
+        if (SEED && g == 0 && own) {
+            if (share == 0) A.pcnt[my_slot] = nshare > 1 ? 2 * MH * nshare : 0;
+            if (nshare > 1)
+                for (int i = 0; i < 2 * MH; i++) A.partials[(int64_t)my_slot * A.r + share * 2 * MH + i] = ~0ull;
+        }
         return;
     }
     // fetch cursor (chunk of the rows of the next fetch) and the chunk after it
@@ -498,7 +512,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
             if (any_or) {   // a disjunction: some term may pass
                 bool some = !my_or;
 #pragma unroll
-                for (int i = 0; i < (LAB ? kMaxTerms : 1); i++)
+                for (int i = 0; i < (DISJ ? kMaxTerms : 1); i++)
                     some |= ((tv[i] & ~wo) | (~tv[i] & tm[i] & wa)) == 0u;
                 if (!some) miss = 1u;
             }
@@ -562,7 +576,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
                 for (int e = 0; e < 4; e++) {
                     if (!((hit[e] >> lane) & 1ull) || (wv[e] & my_mask) != my_val) continue;
                     if constexpr (LAB) {
-                        if (staged_passes(wv[e], has_lab ? xsig[pb][rb + e] : ~0ull)) cand |= 1u << (4 * q4 + e);
+                        if (staged_passes(wv[e], !DISJ || has_lab ? xsig[pb][rb + e] : ~0ull)) cand |= 1u << (4 * q4 + e);
                     } else {
                         const uint64_t key = ((uint64_t)f2ord(canon0(acc[4 * q4 + e])) << 32) | (uint32_t)(c0 + rb + e);
                         if (key < lst[MH - 1]) offer(key);
@@ -633,7 +647,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
 #pragma unroll
                         for (int e = 0; e < 4; e++)
                             hit[e] &= __builtin_amdgcn_ballot_w64(
-                                staged_passes(wv[e], has_lab ? xsig[pb][rb + e] : ~0ull));
+                                staged_passes(wv[e], !DISJ || has_lab ? xsig[pb][rb + e] : ~0ull));
                     }
                 }
 #pragma unroll
@@ -667,7 +681,12 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
         const int c_hi = __shfl(cnt, c32 + 32, 64);
         const uint64_t w_hi = ((uint64_t)(uint32_t)__shfl((int)(lst[MH - 1] >> 32), c32 + 32, 64) << 32) |
                               (uint32_t)__shfl((int)(uint32_t)lst[MH - 1], c32 + 32, 64);
-        if (own) {
+        if (own && nshare > 1) {   // each share fills its part of the list (2 MH nshare <= r), padding included
+            uint64_t *out = A.partials + (int64_t)my_slot * A.r + share * 2 * MH + g * MH;
+#pragma unroll
+            for (int i = 0; i < MH; i++) out[i] = lst[i];
+            if (g == 0 && share == 0) A.pcnt[my_slot] = 2 * MH * nshare;
+        } else if (own) {
             uint64_t *out = A.partials + (int64_t)my_slot * A.r + (g ? c_lo : 0);
 #pragma unroll
             for (int i = 0; i < MH; i++)
@@ -690,14 +709,16 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(LAB ? 
     }
 }
 
-// The kernel for rows of ns 32-element steps (ns <= 4; caps_x32_inst.hip):
-// mode 0 exact main pass, 1 counting survivors (not with label tests), 2 seed
-// lists of one key, 3 of four keys per half of a partition's rows.
-template <int PREC, bool LAB>
+// The kernel for rows of ns 32-element steps (ns <= 4; caps_x32_inst.hip) and a
+// filter kind (0 dense values, 1 labels too, 2 disjunctions too): mode 0 exact
+// main pass, 1 counting survivors (filter kind 0 only), 2 seed lists of one
+// key, 3 of four keys per half of a partition's rows.
+template <int PREC, int FILT>
 LowpFn pick_x32(int ns, int mode);
-#define CAPS_X32_DECL(P)                                  \
-    template <> LowpFn pick_x32<P, false>(int, int);      \
-    template <> LowpFn pick_x32<P, true>(int, int);
+#define CAPS_X32_DECL(P)                              \
+    template <> LowpFn pick_x32<P, 0>(int, int);      \
+    template <> LowpFn pick_x32<P, 1>(int, int);      \
+    template <> LowpFn pick_x32<P, 2>(int, int);
 CAPS_X32_DECL(CAPS_PREC_BF16)
 CAPS_X32_DECL(CAPS_PREC_FP16)
 CAPS_X32_DECL(CAPS_PREC_FP8)
