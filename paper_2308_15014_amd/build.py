@@ -12,13 +12,13 @@ LIB = os.path.join(HERE, "libcaps.so")
 SOURCES = ["caps_api.hip", "caps_build.hip", "caps_search.hip", "caps_small.hip", "caps_mfma.hip", "caps_router.hip", "caps_server.hip", "caps_io.hip", "caps_util.hip", "caps_static.hip"]
 # The matrix-core scan instantiations, compiled in parallel (CAPS_PREC_BF16 = 1,
 # FP8 = 2, FP16 = 3): caps_scan_inst.hip once per precision and kind (0
-# approximate keys, also per row length; 1 exact main pass; 2 rescue pass; 3
-# exact main pass with survivor counts), caps_x32_inst.hip once per precision
+# approximate keys and 5 approximate rescue pass, also per row length; 1 exact
+# main pass; 2 rescue pass; 3 exact main pass with survivor counts), caps_x32_inst.hip once per precision
 # and filter kind (0 dense values, 1 labels, 2 disjunctions).  The longest compilations first.
 _PRECS = (("bf16", 1), ("fp8", 2), ("fp16", 3))
-INSTANCES = [("caps_scan_inst.hip", f"caps_scan_{name}_approx{ns}",
-              [f"-DCAPS_INST_PREC={prec}", "-DCAPS_INST_KIND=0", f"-DCAPS_INST_NS={ns}"])
-             for name, prec in _PRECS for ns in (8, 4, 2, 1)]
+INSTANCES = [("caps_scan_inst.hip", f"caps_scan_{name}_{kind}{ns}",
+              [f"-DCAPS_INST_PREC={prec}", f"-DCAPS_INST_KIND={kd}", f"-DCAPS_INST_NS={ns}"])
+             for kind, kd in (("approx", 0), ("arescue", 5)) for name, prec in _PRECS for ns in (8, 4, 2, 1)]
 INSTANCES += [("caps_scan_inst.hip", f"caps_scan_{name}_{kind}", [f"-DCAPS_INST_PREC={prec}", f"-DCAPS_INST_KIND={kd}"])
               for kind, kd in (("rescue", 2), ("exact", 1), ("exactcnt", 3)) for name, prec in _PRECS]
 INSTANCES += [("caps_x32_inst.hip", f"caps_x32_{name}_{filt}", [f"-DCAPS_INST_PREC={prec}", f"-DCAPS_INST_FILT={filt}"])

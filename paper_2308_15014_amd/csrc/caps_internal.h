@@ -193,7 +193,8 @@ caps_status insert_points(Index *ix, const float *x, int64_t n_new, const uint32
 struct LowpScan {
     int32_t nb, m, r;             // r: keys kept per (query, probe)
     int kind;                     // 0 approximate keys, 1 exact main pass, 2 exact rescue pass, 4 seed lists
-                                  // (approximate keys of the seed probes on 32 x 32 blocks)
+                                  // (approximate keys of the seed probes on 32 x 32 blocks), 5 approximate
+                                  // rescue pass, 6 approximate main pass (32 x 32 blocks)
     int seed_mh;                  // kind 4: keys per lane (half of a probe's rows), 1 or 4
     int stage;                    // profiling stage of the launch (CAPS_STAGE_SCAN or _SEED)
     int64_t max_tiles;
@@ -224,7 +225,10 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st);
 inline float exact_eta(const Index *ix) { return (float)(6.0 * ix->dpad + 64.0) * 0x1p-24f; }
 caps_status lowp_merge(const Index *ix, const float *q, int32_t nb, const uint32_t *sel, int32_t m, int32_t k,
                        int32_t r, const uint64_t *partials, const int32_t *pcnt, const int32_t *cand, int32_t *ncand,
-                       int32_t *out_ids, float *out_dist, hipStream_t st);
+                       int32_t *out_ids, float *out_dist, hipStream_t st, const uint64_t *dpos = nullptr,
+                       const int32_t *dcnt = nullptr, const int32_t *oflow = nullptr, int32_t dcap = 0);
+// whether the approximate search runs its main pass on 32 x 32 blocks
+bool lowp_approx_x32(int32_t dpad, bool lab, int32_t r, int32_t s_seed);
 
 // ---- shared device utilities (caps_util.hip)
 // `sums` is caller workspace of exclusive_scan_tiles(n) ints

@@ -56,7 +56,8 @@ constexpr int kVRing = 128;      // exact: per-wave ring of pairs awaiting resco
 struct LowpLds {
     size_t xw, xn, xsc, xsig, buf, bcnt, tau, qslot, qd, ring, dhist, qnq, scnt, total;
     // kind: 0 approximate keys, 1 exact main pass (no buffers), 2 exact rescue
-    // pass, 3 exact main pass counting the survivors of the filter.
+    // pass, 3 exact main pass counting the survivors of the filter, 5 approximate
+    // rescue pass.
     // The chunk tiles themselves are static arrays of the kernel (two of
     // kLCH rows); the per-point arrays here are double buffered alike.
     __host__ __device__ constexpr LowpLds(int cb, int kind, bool labels)
@@ -77,9 +78,9 @@ struct LowpLds {
         xn = take(sizeof(float) * 2 * kLCH);
         xsc = take(sizeof(float) * 2 * kLCH);
         xsig = take(labels ? sizeof(uint64_t) * 2 * kLCH : 0);
-        ring = take(kind != 0 ? sizeof(uint32_t) * (kind == 1 || kind == 3 ? 3 : 2) * kLNW * kVRing : 0);
+        ring = take(kind != 0 && kind != 5 ? sizeof(uint32_t) * (kind == 1 || kind == 3 ? 3 : 2) * kLNW * kVRing : 0);
         dhist = take(kind == 1 || kind == 3 ? sizeof(int32_t) * kLNW * kLQPW : 0);
-        qnq = take(kind != 0 ? sizeof(float) * kLQB : 0);
+        qnq = take(kind != 0 && kind != 5 ? sizeof(float) * kLQB : 0);
         scnt = take(sizeof(int32_t) * kLQB);
         buf = take(kind == 1 || kind == 3 ? 0 : sizeof(uint64_t) * (size_t)kLQB * cb);
         total = take(16);
@@ -233,11 +234,12 @@ __device__ inline float exact_score(const float *__restrict__ xr, const float *_
 // tiles, looped) and with label tests or longer rows (their state does not
 // fit).
 template <int PREC, bool HAS_LABELS, int CB, int NS, int KIND>
-__global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 || HAS_LABELS || KIND == 2 ? 2 : KIND == 1 || KIND == 3 ? 4 : 3))) void k_scan_mfma(
+__global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 || HAS_LABELS || KIND == 2 || KIND == 5 ? 2 : KIND == 1 || KIND == 3 ? 4 : 3))) void k_scan_mfma(
     LowpArgs A) {
-    constexpr bool EXACT = KIND != 0;    // exact keys (bounds + exact rescoring)
+    constexpr bool EXACT = KIND != 0 && KIND != 5;    // exact keys (bounds + exact rescoring)
     constexpr bool DEFER = KIND == 1 || KIND == 3;   // main pass: passing pairs go to the deferred lists
-    constexpr bool RESCUE = KIND == 2;   // rescue pass: flagged queries only, rescored here
+    constexpr bool WALK = KIND == 2 || KIND == 5;     // rescue passes: flagged queries only
+    constexpr bool RESCUE = KIND == 2;   // exact rescue pass: rescored here
     typedef MfmaOp<PREC> Op;
     typedef typename Op::T VT;
     constexpr int ES = Op::ES;
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
         const int32_t slot = ent[qi];
         const int32_t qq = slot / A.m;
         qslot[qi] = slot;
-        if (!RESCUE || A.oflow[qq]) {   // the rescue pass takes flagged queries only
+        if (!WALK || A.oflow[qq]) {   // the rescue pass takes flagged queries only
             my_qq = qq;
             my_sel = A.sel[slot];
             if (HAS_LABELS) qds[qi] = A.qd[my_qq];
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
         if (lane == 0) lvw[w] = wor;
         wall = __builtin_amdgcn_readfirstlane(wall);
     }
-    if (RESCUE) {   // leave early when no query of the tile is flagged (uniform)
+    if (WALK) {   // leave early when no query of the tile is flagged (uniform)
         __syncthreads();
         uint32_t any = 0;
 #pragma unroll
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
         }
     }
     };
-    if (RESCUE) {
+    if (WALK) {
         // a workgroup walking several tiles waits for all its waves between
         // them: the cursor and bound arrays (spo, lvw, qmx) are rewritten at
         // the start of a tile and read until its end
@@ -811,8 +813,9 @@ __host__ __device__ constexpr bool x32_kernel(int ns, bool lab, bool count) {
 
 template <int PREC, bool LAB, int NS, int KIND>
 LowpFn pick_cb(int r) {
-    if constexpr ((KIND == 1 || KIND == 3) && x32_kernel(NS, LAB, KIND == 3)) {
-        return nullptr;   // (the 32 x 32 scan's)
+    if constexpr (((KIND == 1 || KIND == 3) && x32_kernel(NS, LAB, KIND == 3)) ||
+                  (KIND == 5 && !x32_kernel(NS, LAB, false))) {
+        return nullptr;   // (the 32 x 32 scan's; no approximate rescue without its main pass)
     } else if constexpr (KIND == 1 || KIND == 3) {
         return k_scan_mfma<PREC, LAB, 32, NS, KIND>;   // (keeps no keys)
     } else {
@@ -831,7 +834,8 @@ LowpFn pick_lab(bool lab, int r);
     template <> LowpFn pick_lab<P, N, 0>(bool, int);  \
     template <> LowpFn pick_lab<P, N, 1>(bool, int);  \
     template <> LowpFn pick_lab<P, N, 2>(bool, int);  \
-    template <> LowpFn pick_lab<P, N, 3>(bool, int);
+    template <> LowpFn pick_lab<P, N, 3>(bool, int);  \
+    template <> LowpFn pick_lab<P, N, 5>(bool, int);
 #define CAPS_PICK_NS(P) \
     CAPS_PICK_KIND(P, 1) CAPS_PICK_KIND(P, 2) CAPS_PICK_KIND(P, 4) CAPS_PICK_KIND(P, 8)
 CAPS_PICK_NS(CAPS_PREC_BF16)

@@ -24,6 +24,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "caps_mfma.h"
 #include "caps_query.h"
@@ -339,8 +340,12 @@ caps_status build_lowp_centroids(Index *ix, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ merge + rerank
-// One wave per query: collect the approximate candidates of all probes
-// (keeping the best r), rescore them with the exact FP32 arithmetic, keep k.
+// One wave per query: the best r approximate keys over all probes, rescored
+// with the exact FP32 arithmetic, keep k.  They come from the query's deferred
+// pairs (dpos: at most dcap pairs at or below the seed bound, whose r smallest
+// keys are found by bisection over their scores, then over the positions of
+// the tied ones) or, without those lists or where a query's did not fit
+// (oflow), from the per-probe lists.
 constexpr int kMCap = 256;
 
 template <int METRIC>
@@ -351,7 +356,10 @@ __global__ __launch_bounds__(256) void k_merge_rerank(const uint64_t *__restrict
                                                       int32_t r, int32_t k, const float *__restrict__ q,
                                                       int32_t d, const float *__restrict__ vecs,
                                                       const int32_t *__restrict__ perm, int32_t *__restrict__ ids,
-                                                      float *__restrict__ dist, int32_t *__restrict__ ncand) {
+                                                      float *__restrict__ dist, int32_t *__restrict__ ncand,
+                                                      const uint64_t *__restrict__ dpos,
+                                                      const int32_t *__restrict__ dcnt,
+                                                      const int32_t *__restrict__ oflow, int32_t dcap) {
     __shared__ uint64_t pool_all[4][kMCap];
     __shared__ int32_t npool_all[4];
     const int wq = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -359,9 +367,79 @@ __global__ __launch_bounds__(256) void k_merge_rerank(const uint64_t *__restrict
     if (qq >= nq) return;
     uint64_t *pool = pool_all[wq];
     int32_t *npool = &npool_all[wq];
-    const int nc = gather_best<kMCap>(pool, npool, partials, pcnt, sel, cand, (int64_t)qq * m, 0, m, r, r);
-    if (lane == 0) ncand[qq] = nc;
-    const int nr = *npool;   // <= r <= 64, sorted by approximate key
+    int nr;   // <= r <= 64 candidates in the pool
+    if (!dpos || oflow[qq]) {
+        const int nc = gather_best<kMCap>(pool, npool, partials, pcnt, sel, cand, (int64_t)qq * m, 0, m, r, r);
+        if (lane == 0) ncand[qq] = nc;
+        nr = *npool;
+    } else {
+        const int n = min(dcnt[qq], dcap);
+        const uint64_t *src = dpos + (int64_t)qq * dcap;
+        auto select = [&](auto np_c) {
+            constexpr int NP = decltype(np_c)::value;   // n <= 64 NP
+            uint64_t e[NP];
+#pragma unroll
+            for (int j = 0; j < NP; j++) e[j] = j * 64 + lane < n ? src[j * 64 + lane] : ~0ull;
+            // the r-th smallest key: its score, then its position
+            uint64_t T = ~0ull - 1;
+            if (n > r) {
+                uint32_t ans = 0;
+                int below = 0;   // keys of scores below ans
+                for (int bit = 31; bit >= 0; bit--) {
+                    const uint32_t t = ans | (1u << bit);
+                    int c = 0;
+#pragma unroll
+                    for (int j = 0; j < NP; j++) c += __popcll(__ballot((uint32_t)(e[j] >> 32) < t));
+                    if (c < r) {
+                        ans = t;
+                        below = c;
+                    }
+                    if (c == r) {   // exactly the keys below t
+                        ans = t - 1;
+                        below = -1;
+                        break;
+                    }
+                }
+                uint32_t pa = ~0u;
+                if (below >= 0) {   // r - below of the keys with score ans
+                    int eq = 0;
+#pragma unroll
+                    for (int j = 0; j < NP; j++) eq += __popcll(__ballot((uint32_t)(e[j] >> 32) == ans));
+                    if (eq > r - below) {
+                        pa = 0;
+                        for (int bit = 31; bit >= 0; bit--) {
+                            const uint32_t t = pa | (1u << bit);
+                            int c = 0;
+#pragma unroll
+                            for (int j = 0; j < NP; j++)
+                                c += __popcll(__ballot((uint32_t)(e[j] >> 32) == ans && (uint32_t)e[j] < t));
+                            if (c < r - below) pa = t;
+                        }
+                    }
+                }
+                T = ((uint64_t)ans << 32) | pa;
+            }
+            int at = 0;
+#pragma unroll
+            for (int j = 0; j < NP; j++) {
+                const bool s = e[j] <= T;
+                const uint64_t b = __ballot(s);
+                if (s) pool[at + __popcll(b & lanemask_lt())] = e[j];
+                at += __popcll(b);
+            }
+            return at;
+        };
+        nr = n <= 512 ? select(std::integral_constant<int, 8>{}) : select(std::integral_constant<int, 32>{});
+        wave_sync();
+        int nc = 0;
+        for (int i = lane; i < m; i += 64) {
+            const int64_t slot = (int64_t)qq * m + i;
+            nc += sel[slot] ? cand[slot] : 0;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
+        if (lane == 0) ncand[qq] = nc;
+    }
     // exact FP32 rescoring, one candidate per lane
     uint64_t key2 = ~0ull;
     if (lane < nr) {
@@ -475,11 +553,12 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     const bool lab = ix->sch.label_vocab > 0 || S.disj;
     const int ns = ix->dpad / 32;
     // (the 32 x 32 scan holds its arrays in static LDS)
-    const bool x32 = S.kind == 4 || (S.kind == 1 && x32_kernel(ns, lab, S.nsurv != nullptr));
-    const int xmode = S.kind == 4 ? (S.seed_mh == 1 ? 2 : 3) : S.nsurv ? 1 : 0;
+    const bool x32 = S.kind == 4 || S.kind == 6 || (S.kind == 1 && x32_kernel(ns, lab, S.nsurv != nullptr));
+    const int xmode = S.kind == 4 ? (S.seed_mh == 1 ? 2 : 3) : S.kind == 6 ? 4 : S.nsurv ? 1 : 0;
     const LowpFn fn = x32 ? pick_x32_prec(ix->prec, S.disj ? 2 : lab ? 1 : 0, ns, xmode)
                       : S.kind == 0 ? pick_prec<0>(ix->prec, ns, lab, S.r)
                       : S.kind == 1 ? (S.nsurv ? pick_prec<3>(ix->prec, ns, lab, S.r) : pick_prec<1>(ix->prec, ns, lab, S.r))
+                      : S.kind == 5 ? pick_prec<5>(ix->prec, ns, lab, S.r)
                                     : pick_prec<2>(ix->prec, ns, lab, S.r);
     const size_t lds = x32 ? 0 : lowp_scan_lds(ix, S.r, S.kind, S.disj);
     {
@@ -490,7 +569,7 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     // the rescue pass walks its (device-side) tile list with a bounded grid
     const int64_t full = (S.max_tiles + kXcds - 1) / kXcds * kXcds;
     const int64_t rcap = S.rescue_grid > 0 ? S.rescue_grid : kRescueWgs;
-    const int64_t grid = S.kind == 2 ? std::min<int64_t>(full, rcap) : full;
+    const int64_t grid = S.kind == 2 || S.kind == 5 ? std::min<int64_t>(full, rcap) : full;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kLNT), lds, st, A);
     prof_end(S.stage, st);
     CAPS_HIP(hipGetLastError());
@@ -499,14 +578,15 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
 
 caps_status lowp_merge(const Index *ix, const float *q, int32_t nb, const uint32_t *sel, int32_t m, int32_t k,
                        int32_t r, const uint64_t *partials, const int32_t *pcnt, const int32_t *cand, int32_t *ncand,
-                       int32_t *out_ids, float *out_dist, hipStream_t st) {
+                       int32_t *out_ids, float *out_dist, hipStream_t st, const uint64_t *dpos, const int32_t *dcnt,
+                       const int32_t *oflow, int32_t dcap) {
     prof_begin(CAPS_STAGE_MERGE, st);
     if (ix->metric == 0)
         hipLaunchKernelGGL(k_merge_rerank<0>, dim3((nb + 3) / 4), dim3(256), 0, st, partials, pcnt, sel, cand, nb, m,
-                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand);
+                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand, dpos, dcnt, oflow, dcap);
     else
         hipLaunchKernelGGL(k_merge_rerank<1>, dim3((nb + 3) / 4), dim3(256), 0, st, partials, pcnt, sel, cand, nb, m,
-                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand);
+                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand, dpos, dcnt, oflow, dcap);
     prof_end(CAPS_STAGE_MERGE, st);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;
@@ -529,6 +609,14 @@ int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed) {
     if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false)) return 0;
     if (r >= 2 && s_seed >= k) return 1;
     return r >= 8 && 8 * s_seed >= k ? 4 : 0;
+}
+
+// The approximate search defers its pairs (32 x 32 blocks) where that scan has
+// a kernel and the seed lists (eight keys a probe, or two for r < 8) can hold r
+// keys.  10k queries x 1M x 128 BF16, r = 40: 1.9 ms main pass against 5.5 ms
+// with the per-query key buffers of k_scan_mfma's approximate kind.
+bool lowp_approx_x32(int32_t dpad, bool lab, int32_t r, int32_t s_seed) {
+    return x32_kernel(dpad / 32, lab, false) && r >= 2 && (r >= 8 ? 8 : 2) * (int64_t)s_seed >= r;
 }
 
 }  // namespace caps

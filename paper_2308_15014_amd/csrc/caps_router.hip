@@ -682,14 +682,19 @@ __global__ __launch_bounds__(64) void k_router_conf(const float *__restrict__ S,
 
 __global__ void k_zero_i32(int32_t *p) { *p = 0; }
 
-__global__ void k_router_fb_list(int32_t nb, int32_t m, int32_t k, float fb_prob, const float *__restrict__ conf,
+// One wave per query (a thread per query, adding its m counts one by one, took
+// 85 us for 10k queries x 608 probes).
+__global__ __launch_bounds__(256) void k_router_fb_list(int32_t nb, int32_t m, int32_t k, float fb_prob, const float *__restrict__ conf,
                                  const int32_t *__restrict__ cand, int32_t *__restrict__ fbq,
                                  int32_t *__restrict__ nfb) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= nb) return;
     int64_t c = 0;
-    for (int j = 0; j < m; j++) c += cand[i * m + j];
-    if (conf[i] < fb_prob || c < k) fbq[atomicAdd(nfb, 1)] = (int32_t)i;
+    for (int j = lane; j < m; j += 64) c += cand[i * m + j];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
+    if (lane == 0 && (conf[i] < fb_prob || c < k)) fbq[atomicAdd(nfb, 1)] = (int32_t)i;
 }
 
 __global__ void k_router_fb_apply(int32_t nb, int32_t m, const int32_t *__restrict__ fbq,
@@ -730,7 +735,7 @@ caps_status router_scores(const Index *ix, const float *q, int32_t nb, const int
 caps_status router_fallback_list(const Index *ix, int32_t nb, int32_t m, int32_t k, const float *conf,
                                  const int32_t *cand, int32_t *fbq, int32_t *nfb, hipStream_t st) {
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, st, nfb);
-    hipLaunchKernelGGL(k_router_fb_list, dim3((unsigned)nblk(nb, 256)), dim3(256), 0, st, nb, m, k,
+    hipLaunchKernelGGL(k_router_fb_list, dim3((unsigned)nblk(nb, 4)), dim3(256), 0, st, nb, m, k,
                        ix->router->fb_prob, conf, cand, fbq, nfb);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;

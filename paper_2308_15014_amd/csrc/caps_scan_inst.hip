@@ -1,12 +1,12 @@
 // Instantiates the matrix-core scan kernels of one precision and kind
 // (0 approximate keys, 1 exact main pass, 2 exact rescue pass, 3 exact main
-// pass with survivor counts): compiled once per (CAPS_INST_PREC,
-// CAPS_INST_KIND), the approximate kind once per row length (CAPS_INST_NS)
-// too, so that they build in parallel.
+// pass with survivor counts, 5 approximate rescue pass): compiled once per
+// (CAPS_INST_PREC, CAPS_INST_KIND), the approximate kinds once per row length
+// (CAPS_INST_NS) too, so that they build in parallel.
 #include "caps_mfma.h"
 
 #if !defined(CAPS_INST_PREC) || !defined(CAPS_INST_KIND)
-#error "compile with -DCAPS_INST_PREC=<CAPS_PREC_*> -DCAPS_INST_KIND=<0|1|2|3> [-DCAPS_INST_NS=<1|2|4|8>]"
+#error "compile with -DCAPS_INST_PREC=<CAPS_PREC_*> -DCAPS_INST_KIND=<0|1|2|3|5> [-DCAPS_INST_NS=<1|2|4|8>]"
 #endif
 
 namespace caps {

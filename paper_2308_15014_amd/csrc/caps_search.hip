@@ -377,10 +377,17 @@ static void launch_topm(const float *scores, int32_t nb, int32_t b, int32_t pb, 
 __global__ void k_select(const int32_t *__restrict__ probes, int32_t nq, int32_t m,
                          const QDesc *__restrict__ qd, const QDesc *__restrict__ qterms, Schema sch,
                          const int32_t *__restrict__ tags, int32_t h, const int32_t *__restrict__ offs, int32_t rule,
-                         uint32_t *__restrict__ sel, int32_t *__restrict__ cand_out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                         uint32_t *__restrict__ sel, int32_t *__restrict__ cand_out,
+                         const int32_t *__restrict__ rows = nullptr, const int32_t *__restrict__ nrows = nullptr) {
+    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= (int64_t)nq * m) return;
-    const int32_t q = (int32_t)(e / m);
+    int32_t q = (int32_t)(e / m);
+    if (rows) {   // only the queries rows[0 .. *nrows)
+        if (q >= *nrows) return;
+        e -= (int64_t)q * m;
+        q = rows[q];
+        e += (int64_t)q * m;
+    }
     const int32_t p = probes[e];
     const uint32_t mask = choose_query_levels(sch, qd[q], qterms + (int64_t)q * kMaxTerms, tags + (int64_t)p * h, h,
                                               rule);
@@ -606,13 +613,14 @@ __global__ __launch_bounds__(kClassW * 64) void k_class_sort(const int32_t *__re
 
 // Seed bound: the keep-th best key over a query's first s probes (any keep
 // valid candidates bound the final keep-th key from above).  One wave per
-// query; ~0 when fewer than keep candidates were found.
+// query; ~0 when fewer than keep candidates were found.  past 1: one past that
+// key (the next pass covers the seed probes again, so it must admit the key).
 constexpr int kSeedCap = 256;
 
 __global__ __launch_bounds__(256) void k_seed_tau(const uint64_t *__restrict__ partials,
                                                   const int32_t *__restrict__ pcnt,
                                                   const uint32_t *__restrict__ sel, int32_t nq, int32_t m,
-                                                  int32_t s, int32_t slot_len, int32_t keep,
+                                                  int32_t s, int32_t slot_len, int32_t keep, uint64_t past,
                                                   uint64_t *__restrict__ tau) {
     __shared__ uint64_t pool_all[4][kSeedCap];
     __shared__ int32_t npool_all[4];
@@ -622,7 +630,7 @@ __global__ __launch_bounds__(256) void k_seed_tau(const uint64_t *__restrict__ p
     uint64_t *pool = pool_all[wq];
     int32_t *npool = &npool_all[wq];
     (void)gather_best<kSeedCap>(pool, npool, partials, pcnt, sel, nullptr, (int64_t)qq * m, 0, s, slot_len, keep);
-    if (lane == 0 && *npool == keep && pool[keep - 1] < tau[qq]) tau[qq] = pool[keep - 1];
+    if (lane == 0 && *npool == keep && pool[keep - 1] < tau[qq]) tau[qq] = pool[keep - 1] + past;
 }
 
 // Seed bound for exact keys from an approximate scan of a query's first s
@@ -1579,6 +1587,7 @@ struct SearchPlan {
     int64_t copy_n;       // rows of the search's own copy (0: none)
     bool small, direct;   // the small-batch path, without tiles
     int32_t defer;   // deferred pairs kept per query (0: no deferral)
+    int32_t s_seed;  // probes of the seed round
     int32_t r, sb;
     size_t qlow_row;
     const Router *router;
@@ -1605,6 +1614,9 @@ static bool wants_copy(const Index *ix, const caps_search_params *sp, int32_t nq
     return visits >= 64.0 && visits * (double)ix->n * ix->d >= 1e9 && copy_bytes(ix) <= budget / 2;
 }
 
+// The seed round's probes: the best 1/part of them, at least 8; all below 32.
+static int32_t seed_probes(int32_t m, int32_t part) { return m >= 32 ? std::max(8, m / part) : m; }
+
 static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget,
                               bool may_copy) {
     const int32_t b = ix->b, m = sp->nprobe, k = sp->k;
@@ -1624,8 +1636,12 @@ static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int
     // otherwise (or mode 2) the plain FP32 scan
     P.lowp = sp->mode == 1;
     P.mfma = P.lowp || (sp->mode == 0 && P.prec != CAPS_PREC_NONE);
-    P.defer = P.mfma && !P.lowp ? defer_cap(P.prec, k) : 0;
     P.r = P.lowp ? (sp->rerank > 0 ? sp->rerank : std::min(4 * k, kMaxK)) : k;
+    const bool filt = ix->sch.label_vocab > 0 || (sp->flags & CAPS_SEARCH_DISJUNCTIVE);
+    P.defer = !P.mfma  ? 0
+              : !P.lowp ? defer_cap(P.prec, k)
+                        : m >= 32 && lowp_approx_x32(P.dpad, filt, P.r, seed_probes(m, 16)) ? 2048 : 0;
+    P.s_seed = seed_probes(m, P.defer && !P.lowp ? 24 : 16);
     P.router = sp->routing == 1 ? ix->router : nullptr;
     P.qlow_row = P.mfma ? (size_t)P.dpad * (P.prec == CAPS_PREC_FP8 ? 1 : 2) : 0;
     const size_t per_q = sizeof(float) * (size_t)b + sizeof(int32_t) * 5 * (size_t)m +
@@ -1640,11 +1656,11 @@ static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int
                                    : 0);
     P.sb = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)std::max(nq, 1), budget / per_q));
     // A small batch takes the path of caps_small.hip when it is one sub-batch
-    // (the centroid routing and FP32 arithmetic of modes 0 and 2 only).
+    // with centroid routing.
     // Its tables (two rounds of tiles, of b x kSmallSplit at least) stay a small
     // part of the budget, so that a budget that held a query still does.
-    P.small = !P.lowp && !P.router && P.sb >= nq && small_fits(b, ix->d, nq);
-    P.direct = P.small && direct_fits(ix, nq, m);
+    P.small = !P.router && P.sb >= nq && small_fits(b, ix->d, nq);
+    P.direct = P.small && !P.lowp && direct_fits(ix, nq, m);
     if (P.small && !P.direct) {
         const size_t tables = 2 * sizeof(int4) * (size_t)small_tile_cap(nq, b) + 8 * (size_t)nq * m;
         P.small = tables <= budget / 8 && (!(sp->flags & kSearchTightWs) || tables <= (size_t)256 << 10);
@@ -1842,12 +1858,17 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             const int32_t nb = std::min(sb, nq - q0);
             const int64_t pairs = (int64_t)nb * m;
             const int32_t ngrp = (nb + kBucketQ - 1) / kBucketQ;
-            const int32_t s_seed = m >= 32 ? std::max(8, m / (P.defer ? 24 : 16)) : m;
+            const int32_t s_seed = P.s_seed;
             // the probes query returns them sorted; a search takes the best m as
             // a set with the s_seed best first
             const int32_t topm_s = probes_only ? -1 : s_seed;
             if (small) {
                 prof_begin(CAPS_STAGE_ROUTE, st);
+                if (lowp) {   // precision mode: centroid scores from the rounded queries
+                    caps_status rs = lowp_qquant(ix, q, nb, W.qlow, W.qscale, W.qaux, st);
+                    if (rs == CAPS_OK) rs = lowp_route(ix, W.qlow, W.qscale, nb, scores, st);
+                    if (rs != CAPS_OK) return rs;
+                }
                 FrontArgs F{};
                 F.q = q;
                 F.d = d;
@@ -1859,6 +1880,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 F.disj = disj;
                 F.cent = ix->cent;
                 F.cnorm = ix->cnorm;
+                F.scores = lowp ? scores : nullptr;
                 F.b = b;
                 F.metric = ix->metric;
                 F.m = m;
@@ -1878,7 +1900,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 F.dcnt = W.dcnt;
                 F.oflow = W.oflow;
                 F.bad = W.bad;
-                F.qlow = mfma && !P.direct ? W.qlow : nullptr;
+                F.qlow = mfma && !lowp && !P.direct ? W.qlow : nullptr;
                 F.qscale = W.qscale;
                 F.qaux = W.qaux;
                 F.dpad = ix->dpad;
@@ -1940,7 +1962,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             }
             prof_begin(CAPS_STAGE_SELECT, st);
             hipLaunchKernelGGL(k_select, dim3(nblocks(pairs, 256)), dim3(256), 0, st, probes, nb, m, qd, W.qterms, ix->sch,
-                               ix->tags, h, ix->offs, sp->rule, sel, cand);
+                               ix->tags, h, ix->offs, sp->rule, sel, cand, rows, nrows);
             CAPS_HIP(hipGetLastError());
             if (probes_only) {
                 prof_end(CAPS_STAGE_SELECT, st);
@@ -1999,7 +2021,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             // did not fit.  (The approximate seed pass is cheap per probe but
             // its bound looser: m/24 seed probes there, enough that on the
             // 1M-point benchmark no query's pairs overflow.)
-            const bool seeded_exact = P.defer != 0;
+            // (the approximate search likewise, with a bound on its r-th approximate
+            // key; its survivors are counted by the scan with key buffers)
+            const bool deferred = P.defer && !(lowp && out_nsurv);
+            const bool seeded_exact = deferred && !lowp;
             const int32_t *qord = nullptr;   // bucketing order of the queries (null: as given)
             if (ix->sch.n_dense > 0 && !small) {
                 int32_t kbits = 0;
@@ -2013,11 +2038,11 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             }
             // tile width of a round: the exact main pass and the seed lists may
             // run 128-entry tiles
-            const int seed_mh = seeded_exact ? lowp_seed_x32(ix, disj, r, k, s_seed) : 0;
+            const int seed_mh = seeded_exact ? lowp_seed_x32(ix, disj, r, k, s_seed) : deferred ? (r >= 8 ? 4 : 1) : 0;
             int qbs[2], splits[2] = {1, 1};
             for (int round = 0; round < 2; round++) {
-                const bool seed_pass = seeded_exact && round == 0;
-                qbs[round] = !mfma || lowp || (seed_pass && !seed_mh) ? qb
+                const bool seed_pass = deferred && round == 0;
+                qbs[round] = !mfma || (lowp && !deferred) || (seed_pass && !seed_mh) ? qb
                                                                       : lowp_qb_main(ix, disj, !seed_pass && out_nsurv);
             }
             if (small) {
@@ -2026,8 +2051,8 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 // each on average) until there are about four per compute unit.
                 SmallRound R[2] = {};
                 for (int round = 0; round < 2; round++) {
-                    const bool seed_pass = seeded_exact && round == 0;
-                    const int32_t nslot = round == 0 ? s_seed : seeded_exact ? m : m - s_seed;
+                    const bool seed_pass = deferred && round == 0;
+                    const int32_t nslot = round == 0 ? s_seed : deferred ? m : m - s_seed;
                     if (nslot <= 0) continue;
                     const bool x32 = seed_pass ? seed_mh > 0 : mfma && qbs[1] != qb;
                     const int64_t tl = std::min<int64_t>((int64_t)b * ((nb + qbs[round] - 1) / qbs[round]), (int64_t)nb * nslot);
@@ -2035,9 +2060,9 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     if (seed_pass) split = std::min<int64_t>(split, r / (2 * std::max(1, seed_mh)));
                     splits[round] = x32 ? (int)std::max<int64_t>(1, split) : 1;
                     R[round].entries = round == 0 ? W.sent : entries;
-                    R[round].esel = !seeded_exact ? nullptr : round == 0 ? W.sesel : W.esel;
+                    R[round].esel = !deferred ? nullptr : round == 0 ? W.sesel : W.esel;
                     R[round].tiles = W.stiles[round];
-                    R[round].which = round == 0 ? (s_seed < m ? 1 : 0) : seeded_exact ? 0 : 2;
+                    R[round].which = round == 0 ? (s_seed < m ? 1 : 0) : deferred ? 0 : 2;
                     R[round].qb = qbs[round];
                     R[round].split = splits[round];
                 }
@@ -2048,10 +2073,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 prof_end(CAPS_STAGE_SELECT, st);
             }
             for (int round = 0; round < 2; round++) {
-                const int32_t r0 = round == 0 || seeded_exact ? 0 : s_seed;
+                const int32_t r0 = round == 0 || deferred ? 0 : s_seed;
                 const int32_t r1 = round == 0 ? s_seed : m;
                 if (r0 >= r1) continue;
-                const bool seed_pass = seeded_exact && round == 0;
+                const bool seed_pass = deferred && round == 0;
                 const int qbr = qbs[round];
                 const int32_t *ent = entries;
                 const uint32_t *esel = W.esel;
@@ -2095,7 +2120,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     S.nb = nb;
                     S.m = m;
                     S.r = r;
-                    S.kind = seed_pass && seed_mh ? 4 : lowp || seed_pass ? 0 : 1;
+                    S.kind = seed_pass && seed_mh    ? 4
+                             : lowp && !seed_pass && deferred ? 6
+                             : lowp || seed_pass     ? 0
+                                                     : 1;
                     S.seed_mh = seed_mh;
                     S.stage = seed_pass ? CAPS_STAGE_SEED : CAPS_STAGE_SCAN;
                     S.max_tiles = grid;
@@ -2121,14 +2149,14 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     S.rescue_grid = sp->rescue_grid;
                     const caps_status ls = lowp_scan(ix, S, st);
                     if (ls != CAPS_OK) return ls;
-                    if (S.kind == 1) {   // rescue pass over the tiles that hold a flagged query
+                    if (S.kind == 1 || S.kind == 6) {   // rescue pass over the tiles that hold a flagged query
                         if (!small) {   // (a small batch's few tiles are all looked at)
                             hipLaunchKernelGGL(k_rescue_init, dim3(1), dim3(1024), 0, st, W.oflow, nb, W.rcount);
                             hipLaunchKernelGGL(k_rescue_tiles, dim3(nblocks(grid, 256)), dim3(256), 0, st, W.tiles,
                                                (int32_t)grid, ent, m, W.oflow, qb, (int32_t)(qbr != qb), W.rlist,
                                                W.rcount);
                         }
-                        S.kind = 2;
+                        S.kind = S.kind == 1 ? 2 : 5;
                         S.rhalves = qbr != qb;
                         S.rlist = small ? nullptr : W.rlist;
                         S.rcount = W.rcount;
@@ -2174,17 +2202,18 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                                        ix->metric, tau);
                     prof_end(CAPS_STAGE_SEED, st);
                     CAPS_HIP(hipGetLastError());
-                } else if (round == 0 && s_seed < m) {
+                } else if (round == 0 && (s_seed < m || deferred)) {
                     prof_begin(CAPS_STAGE_SELECT, st);
                     hipLaunchKernelGGL(k_seed_tau, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials,
-                                       lowp ? W.pcnt : nullptr, sel, nb, m, s_seed, r, r, tau);
+                                       lowp ? W.pcnt : nullptr, sel, nb, m, s_seed, r, r, (uint64_t)(deferred ? 1 : 0), tau);
                     prof_end(CAPS_STAGE_SELECT, st);
                     CAPS_HIP(hipGetLastError());
                 }
             }
             if (lowp) {
                 const caps_status ls = lowp_merge(ix, q + (int64_t)q0 * d, nb, sel, m, k, r, partials, W.pcnt, cand,
-                                                  ncand + q0, out_ids + (int64_t)q0 * k, out_dist + (int64_t)q0 * k, st);
+                                                  ncand + q0, out_ids + (int64_t)q0 * k, out_dist + (int64_t)q0 * k, st,
+                                                  deferred ? W.dpos : nullptr, W.dcnt, W.oflow, P.defer);
                 if (ls != CAPS_OK) return ls;
                 continue;
             }

@@ -16,6 +16,7 @@ struct FrontArgs {
     Schema sch;
     int32_t disj;
     const float *cent, *cnorm;
+    const float *scores;          // centroid scores nq x b (null: computed from cent in FP32)
     int32_t b, metric, m, s;      // s: seed probes in the first slots (s >= m: every probe)
     const int32_t *tags, *offs;
     int32_t h, rule;

@@ -183,7 +183,15 @@ __global__ __launch_bounds__(kFrontNT) void k_front(FrontArgs A) {
         float *tl = tile + w * 64 * kRouteS;
         const int nst = dp / kRouteD;
         uint32_t klo = ~0u, khi = 0u;
-        for (int c0 = w * 64; c0 < b; c0 += kFrontNT) {
+        if (A.scores) {   // (pmask may share their memory: this row is read before it is written)
+            for (int c = t; c < b; c += kFrontNT) {
+                const uint32_t k = f2ord(A.scores[q * b + c]);
+                keys[c] = k;
+                klo = min(klo, k);
+                khi = max(khi, k);
+            }
+        }
+        for (int c0 = w * 64; c0 < b && !A.scores; c0 += kFrontNT) {
             const int lr = lane >> 2, lc = 4 * (lane & 3);
             float4 pf[4][4];
             auto load = [&](float4 (&v)[4], int s) {

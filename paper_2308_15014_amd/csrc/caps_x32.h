@@ -23,7 +23,9 @@
 // the survivors of the filter, MODE 2 the seed pass of the exact search:
 // approximate keys (plain point term) of the first probes, of which each
 // lane keeps its MH best that pass the filter in registers, written as the
-// (query, probe)'s partial list for the exact seed bound.
+// (query, probe)'s partial list for the seed bound; MODE 3 is the main pass of
+// the approximate search: the plain point term, pairs at or below the query's
+// bound on its r-th approximate key deferred with their approximate scores.
 //
 // An FP8 row's 32-element block is read as one 16-byte operand per lane like
 // a two-byte row's 16-element step and multiplied as two K = 16 products (low
@@ -69,6 +71,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     static_assert(!(LAB && MODE == 1), "survivors of label tests are counted by k_scan_mfma");
     constexpr bool COUNT = MODE == 1;   // survivor counts of the exact filter
     constexpr bool SEED = MODE == 2;    // approximate keys: per query and probe the best 2 MH
+    constexpr bool APPROX = MODE >= 2;  // approximate scores (no margin)
     constexpr bool F8 = PREC == CAPS_PREC_FP8;
     constexpr int ROWB = NS * (F8 ? 32 : 64);      // bytes per row of the copy
     constexpr int KS = ROWB / 32;                  // 16-byte operands per lane and row
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         const uint64_t tk = __hip_atomic_load(A.tau + my_qq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const float td = bound_score(tk);
         const float nq = ax.y;
-        my_tf = SEED          ? td
+        my_tf = APPROX        ? td
                 : !(td < inf) ? inf
                 : l2          ? fmaf(A.eta, nq + td, td - nq) + 1e-37f
                               : fmaf(A.eta, nq + fabsf(td), td) + 1e-37f;
@@ -347,7 +350,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         const float slack = fmaf(raw[1][c32], qa, raw[2][c32] * qb) * (1.0f + 0x1p-20f);
         float pt = l2 ? fmaf(-A.eta, nx, fmaf(-2.0f, slack, nx)) : fmaf(-A.eta, nx, -slack);
         if (!(fabsf(pt) < inf)) pt = -inf;
-        if (SEED) pt = l2 ? nx : 0.0f;   // approximate keys: the plain point term
+        if (APPROX) pt = l2 ? nx : 0.0f;   // approximate keys: the plain point term
         if constexpr (LAB) {   // (without labels every query's signature, 0, is a subset)
             reinterpret_cast<uint32_t *>(xsig[pb])[lane] = raw2[lane >> 5][c32];
         }
@@ -695,7 +698,8 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
                 A.pcnt[my_slot] = c_lo + c_hi;
                 if (c_lo + c_hi == A.r) {
                     const uint64_t worst = lst[MH - 1] > w_hi ? lst[MH - 1] : w_hi;
-                    atomicMin((unsigned long long *)(A.tau + my_qq), (unsigned long long)worst);
+                    // (one past it: the main pass covers this probe again)
+                    atomicMin((unsigned long long *)(A.tau + my_qq), (unsigned long long)worst + 1ull);
                 }
             }
         }
@@ -712,7 +716,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
 // The kernel for rows of ns 32-element steps (ns <= 4; caps_x32_inst.hip) and a
 // filter kind (0 dense values, 1 labels too, 2 disjunctions too): mode 0 exact
 // main pass, 1 counting survivors (filter kind 0 only), 2 seed lists of one
-// key, 3 of four keys per half of a partition's rows.
+// key, 3 of four keys per half of a partition's rows, 4 approximate main pass.
 template <int PREC, int FILT>
 LowpFn pick_x32(int ns, int mode);
 #define CAPS_X32_DECL(P)                              \

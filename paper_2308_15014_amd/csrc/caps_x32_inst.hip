@@ -1,5 +1,6 @@
-// Instantiates the 32 x 32 scan kernels of one precision and filter kind: compiled once per (CAPS_INST_PREC, CAPS_INST_FILT) pair so that
-// they build in parallel.
+// Instantiates the 32 x 32 scan kernels of one precision and filter kind:
+// compiled once per (CAPS_INST_PREC, CAPS_INST_FILT) pair so that they build in
+// parallel.
 #include "caps_x32.h"
 
 #if !defined(CAPS_INST_PREC) || !defined(CAPS_INST_FILT)
@@ -16,6 +17,7 @@ static LowpFn pick_mode(int mode) {
     }
     if (mode == 2) return k_scan_x32<CAPS_INST_PREC, NS, 2, 1, F>;
     if (mode == 3) return k_scan_x32<CAPS_INST_PREC, NS, 2, 4, F>;
+    if (mode == 4) return k_scan_x32<CAPS_INST_PREC, NS, 3, 1, F>;
     return k_scan_x32<CAPS_INST_PREC, NS, 0, 1, F>;
 }
 

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import synth
+from oracle import ref64
 
 pytestmark = pytest.mark.gpu
 
@@ -50,4 +51,48 @@ def test_x32_equals_oracle(caps, orc, case):
         assert np.array_equal(got[1].cpu().numpy().view(np.uint32), r.dist.view(np.uint32))
         if counters:
             assert np.array_equal(got[2].cpu().numpy(), r.n_cand) and np.array_equal(got[3].cpu().numpy(), r.n_surv)
+    ix.close()
+
+
+APPROX = [
+    # seed, prec, vocabs, label_vocab, d, rerank, n_q
+    (620, "bf16", (3,), 0, 32, 12, 300),
+    (621, "fp16", (), 5, 64, 40, 300),       # label tests
+    (622, "fp8", (2,), 0, 128, 5, 300),      # two keys a list
+    (623, "bf16", (2,), 4, 100, 64, 90),     # small batch
+]
+
+
+@pytest.mark.parametrize("case", APPROX)
+def test_approximate_deferral(caps, orc, case):
+    """Mode 1 on binary vectors, whose approximate scores are known (exact in the
+    two-byte formats) and tie in thousands: the candidates are the `rerank` smallest (score, CSR position),
+    from the deferred lists or, for queries whose pairs overflow those, from
+    the rescue pass."""
+    seed, prec, voc, lv, d, rr, nq = case
+    w = synth.make_tiny(seed, n=24_000, d=d, n_q=nq, vocabs=voc, label_vocab=lv, b=40, h=2, cmin=0, cmax=2, integer=True)
+    w.x = (w.x > 3).astype(np.float32)
+    w.q = (w.q > 3).astype(np.float32)
+    w.x[0] = w.q[0] = 1.0
+    ix = caps.Index.from_workload(w, kmeans_iters=1, precision=prec)
+    perm = ix.export()["perm"]
+    k = 5
+    ids, dist = (t.cpu().numpy() for t in ix.search(w.q, w.con_off, w.con_attr, w.con_val, k, 40, mode=1, rerank=rr))
+    xc = w.x[perm]
+    nx = (xc * xc).sum(1)
+    for i in range(nq):
+        ok = ref64.valid_mask(w.dense, w.label_off, w.labels, ref64.pairs_of(w.con_off, w.con_attr, w.con_val, i), w.n_dense,
+                              w.dense_vocab, w.label_vocab)[perm]
+        pos = np.flatnonzero(ok)
+        dot = (xc[pos] @ w.q[i]).astype(np.float32)
+        if prec == "fp8":   # codes of 448, both FP32 scales applied in turn (exact products otherwise)
+            s = np.float32(1.0) / np.float32(448.0)
+            dot = (dot * np.float32(448.0 * 448.0) * s) * s
+        score = (nx[pos].astype(np.float64) - 2.0 * dot).astype(np.float32)   # (one fused rounding)
+        cand = pos[np.lexsort((pos, score))[:rr]]
+        dd = ((xc[cand] - w.q[i]) ** 2).sum(1)
+        o = np.lexsort((perm[cand], dd))[:k]
+        n = len(o)
+        assert np.array_equal(ids[i, :n], perm[cand][o]) and np.all(ids[i, n:] == -1), i
+        assert np.array_equal(dist[i, :n], dd[o].astype(np.float32)), i
     ix.close()
