@@ -41,7 +41,8 @@ void release_index(Index &ix) {
 
 // Points to add to an index with schema `sch`: finite vectors, dense
 // values inside their vocabularies, label sets of at most max_labels
-// distinct labels inside the label vocabulary (HOST arrays).
+// distinct labels inside the label vocabulary (HOST arrays).  x null: checked
+// on the device.
 static caps_status check_points(const char *who, const Schema &sch, const float *x, int64_t n, int32_t d,
                                 const uint32_t *dense_vals, const int64_t *label_off, const uint32_t *labels,
                                 int32_t max_labels = kMaxPointLabels) {
@@ -62,10 +63,11 @@ static caps_status check_points(const char *who, const Schema &sch, const float 
             }
         }
     }
-    for (int64_t i = 0; i < n * n_dense; i++)
-        if (dense_vals[i] >= (uint32_t)sch.dense_vocab[i % n_dense])
-            return fail(CAPS_EINVAL, "%s: dense value outside vocabulary at %lld", who, (long long)i);
-    for (int64_t i = 0; i < n * (int64_t)d; i++)
+    for (int64_t i = 0; i < n; i++)
+        for (int a = 0; a < n_dense; a++)
+            if (dense_vals[i * n_dense + a] >= (uint32_t)sch.dense_vocab[a])
+                return fail(CAPS_EINVAL, "%s: dense value outside vocabulary at %lld", who, (long long)(i * n_dense + a));
+    for (int64_t i = 0; x && i < n * (int64_t)d; i++)
         if (!isfinite(x[i])) return fail(CAPS_EINVAL, "%s: non-finite x at %lld", who, (long long)i);
     return CAPS_OK;
 }
@@ -128,7 +130,8 @@ extern "C" caps_status caps_build(const float *x, int64_t n, int32_t d, const ui
     if (sch.n_tok > kMaxTokensLds)
         return fail(CAPS_EUNSUPPORTED, "caps_build: %d attribute values exceed %d", sch.n_tok, kMaxTokensLds);
     {
-        const caps_status cs = check_points("caps_build", sch, x, n, d, dense_vals, label_off, labels);
+        // (the vectors are checked on the device: one core took 18 ms for 0.5M x 128)
+        const caps_status cs = check_points("caps_build", sch, nullptr, n, d, dense_vals, label_off, labels);
         if (cs != CAPS_OK) return cs;
     }
     if (p->init_ids) {

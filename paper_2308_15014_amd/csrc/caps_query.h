@@ -187,7 +187,7 @@ constexpr double kNormSlack = 1.0 + 0x1p-40;
 // infinite error norms: its pairs always pass the bound and are rescored.
 constexpr float kNormMax = 1e37f;
 
-// One wave, query row r (the i-th): rounded copy (the codes of quantize_row, element by
+// One wave, query row r (the i-th): rounded copy (the codes of k_quantize, element by
 // element), FP8 scale and qaux = {|q| (up), |q|^2 (down), |q - q~| (up),
 // |q~| (up)}; the FP64 sums are reduced across the wave (their order does
 // not matter: kNormSlack covers any order).

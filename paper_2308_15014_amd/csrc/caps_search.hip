@@ -24,6 +24,7 @@
 #include "caps_internal.h"
 #include "caps_mfma.h"
 #include "caps_query.h"
+#include "caps_scores.h"
 #include "caps_small.h"
 
 namespace caps {
@@ -79,69 +80,6 @@ __global__ __launch_bounds__(128) void k_qprep(const int32_t *__restrict__ con_o
 }
 
 // ------------------------------------------------------------------ routing
-constexpr int kDC = 32;
-constexpr int kTile = 64;
-
-// Q x B scores, 64 x 64 tile per workgroup, sequential fma over dims.
-// With a row list, score row r belongs to query rows[r] and only the first
-// *nrows rows (a count on the device, at most nq) are computed.
-__global__ __launch_bounds__(256) void k_route_scores(const float *__restrict__ q, int32_t nq, int32_t d,
-                                                      const float *__restrict__ cent,
-                                                      const float *__restrict__ cn, int32_t b,
-                                                      int32_t metric, float *__restrict__ scores,
-                                                      const int32_t *__restrict__ rows = nullptr,
-                                                      const int32_t *__restrict__ nrows = nullptr) {
-    __shared__ float xs[kDC][kTile + 4];
-    __shared__ float cs[kDC][kTile + 4];
-    const int t = threadIdx.x;
-    const int ty = t >> 4, tx = t & 15;
-    const int64_t r0 = (int64_t)blockIdx.x * kTile;
-    const int c0 = blockIdx.y * kTile;
-    if (nrows) nq = min(nq, *nrows);
-    if (r0 >= nq) return;
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) acc[i][k] = 0.0f;
-    for (int j0 = 0; j0 < d; j0 += kDC) {
-        const int dc = min(kDC, d - j0);
-        for (int e = t; e < kTile * kDC; e += 256) {
-            const int ri = e / kDC, jj = e % kDC;
-            float v = 0.0f, w = 0.0f;
-            if (jj < dc) {
-                if (r0 + ri < nq) v = q[(rows ? (int64_t)rows[r0 + ri] : r0 + ri) * d + j0 + jj];
-                if (c0 + ri < b) w = cent[(int64_t)(c0 + ri) * d + j0 + jj];
-            }
-            xs[jj][ri] = v;
-            cs[jj][ri] = w;
-        }
-        __syncthreads();
-        for (int jj = 0; jj < dc; jj++) {
-            const float4 a = *reinterpret_cast<const float4 *>(&xs[jj][ty * 4]);
-            const float4 c = *reinterpret_cast<const float4 *>(&cs[jj][tx * 4]);
-            const float av[4] = {a.x, a.y, a.z, a.w};
-            const float cv[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int k = 0; k < 4; k++) acc[i][k] = fmaf(av[i], cv[k], acc[i][k]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int64_t r = r0 + ty * 4 + i;
-        if (r >= nq) continue;
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int c = c0 + tx * 4 + k;
-            if (c >= b) continue;
-            scores[r * b + c] = canon0(metric == 0 ? cn[c] - 2.0f * acc[i][k] : -acc[i][k]);
-        }
-    }
-}
-
 // Best m of B per query: bitonic sort of (score, id) keys in LDS.
 constexpr int kTopmNT = 256;
 
@@ -1949,8 +1887,8 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 const caps_status rs = lowp_route(ix, W.qlow, W.qscale, nb, scores, st, rows, nrows);
                 if (rs != CAPS_OK) return rs;
             } else {
-                hipLaunchKernelGGL(k_route_scores, dim3(nblocks(nb, kTile), nblocks(b, kTile)), dim3(256), 0, st,
-                                   q + (int64_t)q0 * d, nb, d, ix->cent, ix->cnorm, b, ix->metric, scores, rows, nrows);
+                launch_scores<false>(q + (int64_t)q0 * d, nb, d, ix->cent, ix->cnorm, b, ix->metric, nullptr, scores, st,
+                                     rows, nrows);
             }
             prof_end(CAPS_STAGE_ROUTE, st);
             prof_begin(CAPS_STAGE_TOPM, st);

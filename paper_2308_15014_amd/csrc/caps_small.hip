@@ -99,7 +99,7 @@ __device__ inline void front_kth(const uint32_t *keys, int b, int need, uint32_t
 // on), one per lane; their rows come 16 dimensions at a time, coalesced, four
 // steps ahead in registers, through a wave-private transposing tile in LDS (no
 // workgroup barrier), and each lane sums its centroid's products in ascending
-// order as k_route_scores does.  The best partitions are found by front_kth
+// order as k_scores_mfma does.  The best partitions are found by front_kth
 // instead of a sort.  Latency bound: one query against 1024 x 128 centroids
 // 14 us, against 22 us for scores, 20 us for the selection and six more
 // launches on the batch-sized path.
