@@ -86,14 +86,18 @@ __global__ __launch_bounds__(64) void k_router_input(const float *__restrict__ q
 // of that order, so a die's working set of rows and columns stays in its L2.
 // Epilogue: + bias[n], ReLU, zero where mask(m, n) <= 0 (a BF16 array with
 // leading dimension ldm), negation (scores, smaller is better); written as
-// FP32 and/or BF16 with leading dimension ldc.
+// FP32 and/or BF16 with leading dimension ldc, and as BF16 transposed (leading
+// dimension ldt, the columns from M up to it zero).
 //
-// Two kernels: k_gemm_nt for operands whose rows are K-contiguous (every
-// forward product and inference), with branch-free loads issued two K steps
-// ahead into registers and two LDS buffers (one barrier per step); and
-// k_gemm_bf16 for any strides (the transposed operands of the weight
-// gradients), which can also split K over blockIdx.y into FP32 partial
-// products summed afterwards in a fixed order.
+// Two kernels: k_gemm_nt for operands whose rows are K-contiguous, with
+// branch-free loads issued two K steps ahead into registers and two LDS
+// buffers (one barrier per step); and k_gemm_bf16 for any strides.  Both can
+// split K over blockIdx.y into FP32 partial products summed afterwards in a
+// fixed order.  The weight gradients multiply transposed matrices: those are
+// written transposed by the products that make them, or by k_transpose (5 us
+// for 4096 x 1024), and go through k_gemm_nt; with k_gemm_bf16, which turns
+// each piece in LDS with two-byte stores, the three products of a backward
+// pass took 186 us of a 360 us step of 4096 x 1024 x 1024.
 enum { kGemmRelu = 1, kGemmMask = 2, kGemmNeg = 4 };
 // operand layouts of the strided kernel: K-contiguous 16-byte runs,
 // row-contiguous 16-byte runs, else element gathers
@@ -111,131 +115,163 @@ __device__ inline void gemm_tile_origin(int32_t M, int32_t N, int64_t &m0, int64
     n0 = (rr / gh) * kGT;
 }
 
-// The products of one wave's 64 x 64 block: 4 x 4 16 x 16 blocks; D row
+// The products of one wave's 64 x 16 NJ block: 4 x NJ 16 x 16 blocks; D row
 // (lane/16)*4 + r, column lane%16 of each.
-__device__ inline void gemm_epilogue(const f32x4 (&acc)[4][4], int64_t m0, int64_t n0, int32_t M, int32_t N,
+template <int NJ>
+__device__ inline void gemm_epilogue(const f32x4 (&acc)[4][NJ], int64_t m0, int64_t n0, int32_t M, int32_t N,
                                      const float *__restrict__ bias, int32_t flags, const uint16_t *__restrict__ mask,
-                                     int64_t ldm, float *__restrict__ C32, uint16_t *__restrict__ C16, int64_t ldc) {
+                                     int64_t ldm, float *__restrict__ C32, uint16_t *__restrict__ C16, int64_t ldc,
+                                     uint16_t *__restrict__ C16t = nullptr, int64_t ldt = 0) {
     const int lane = threadIdx.x & 63;
+    // bias and mask first, from clamped places, so that the loads overlap
+    float bv[NJ];
+    uint16_t mk[4][NJ][4];
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+        const int64_t nc = min(n0 + j * 16 + (lane & 15), (int64_t)N - 1);
+        bv[j] = bias ? bias[nc] : 0.0f;
+        if (flags & kGemmMask)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    mk[i][j][r] = mask[min(m0 + i * 16 + (lane >> 4) * 4 + r, (int64_t)M - 1) * ldm + nc];
+    }
 #pragma unroll
     for (int i = 0; i < 4; i++)
 #pragma unroll
-        for (int j = 0; j < 4; j++)
+        for (int j = 0; j < NJ; j++) {
+            uint16_t h[4] = {0, 0, 0, 0};   // (transposed: rows past M are zeros)
+            const int64_t mm0 = m0 + i * 16 + (lane >> 4) * 4, nn = n0 + j * 16 + (lane & 15);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int64_t mm = m0 + i * 16 + (lane >> 4) * 4 + r;
-                const int64_t nn = n0 + j * 16 + (lane & 15);
+                const int64_t mm = mm0 + r;
                 if (mm >= M || nn >= N) continue;
                 float v = acc[i][j][r];
-                if (bias) v = v + bias[nn];
+                if (bias) v = v + bv[j];
                 if (flags & kGemmRelu) v = fmaxf(v, 0.0f);
-                if ((flags & kGemmMask) && !(__builtin_bit_cast(float, (uint32_t)mask[mm * ldm + nn] << 16) > 0.0f))
+                if ((flags & kGemmMask) && !(__builtin_bit_cast(float, (uint32_t)mk[i][j][r] << 16) > 0.0f))
                     v = 0.0f;
                 if (flags & kGemmNeg) v = canon0(-v);
                 if (C32) C32[mm * ldc + nn] = v;
-                if (C16) C16[mm * ldc + nn] = bf16_rne(v);
+                h[r] = bf16_rne(v);
+                if (C16) C16[mm * ldc + nn] = h[r];
             }
+            if (C16t && nn < N && mm0 < ldt)   // (ldt a multiple of 8: four rows fit)
+                *reinterpret_cast<uint2 *>(C16t + nn * ldt + mm0) =
+                    make_uint2(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16);
+        }
 }
 
+template <int NJ>
 __device__ inline void gemm_mfma_step(const uint16_t (*As)[kGKP], const uint16_t (*Bs)[kGKP], int wm, int wn,
-                                      f32x4 (&acc)[4][4]) {
+                                      f32x4 (&acc)[4][NJ]) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int ks = 0; ks < kGK; ks += 32) {
-        bf16x8 a[4], b[4];
+        bf16x8 a[4], b[NJ];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
+        for (int i = 0; i < 4; i++)
             a[i] = __builtin_bit_cast(
                 bf16x8, *reinterpret_cast<const uint4 *>(&As[wm + i * 16 + (lane & 15)][ks + (lane >> 4) * 8]));
-            b[i] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const uint4 *>(&Bs[wn + i * 16 + (lane & 15)][ks + (lane >> 4) * 8]));
-        }
+#pragma unroll
+        for (int j = 0; j < NJ; j++)
+            b[j] = __builtin_bit_cast(
+                bf16x8, *reinterpret_cast<const uint4 *>(&Bs[wn + j * 16 + (lane & 15)][ks + (lane >> 4) * 8]));
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
-            for (int j = 0; j < 4; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < NJ; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
 }
 
 // K-contiguous operands: A row m at A + m*lda, B row n at B + n*ldb, K a
 // multiple of 8, rows 16-byte aligned, every element offset below 2^31.
-// Thread t loads rows t/8 + 32u (u < 4) of each operand, columns
+// Thread t loads rows t/8 + 64u (u < 2) of each operand, columns
 // (t%8)*8 .. +7 of the step; rows past M or N and the K tail are loaded
 // clamped to an element in range and zeroed by a select.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_nt(
+// Eight waves of 64 x 32: a training product has about one tile per compute
+// unit (4096 x 1024: 256), so its waves per SIMD are those of one workgroup.
+constexpr int kNtT = 512, kNtU = kGT * 8 / kNtT;
+__global__ __launch_bounds__(kNtT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_gemm_nt(
     const uint16_t *__restrict__ A, int32_t lda, const uint16_t *__restrict__ B, int32_t ldb, int32_t M, int32_t N,
-    int32_t K, const float *__restrict__ bias, int32_t flags, const uint16_t *__restrict__ mask, int64_t ldm,
-    float *__restrict__ C32, uint16_t *__restrict__ C16, int64_t ldc) {
+    int32_t K, int32_t kchunk, const float *__restrict__ bias, int32_t flags, const uint16_t *__restrict__ mask,
+    int64_t ldm, float *__restrict__ C32, uint16_t *__restrict__ C16, int64_t ldc, uint16_t *__restrict__ C16t,
+    int64_t ldt) {
+    // split K: workgroup (x, y) takes columns y kchunk.. (kchunk of them at most)
+    // and writes its plain partial product to C32 + y M ldc
+    A += (int64_t)blockIdx.y * kchunk;
+    B += (int64_t)blockIdx.y * kchunk;
+    K = min(kchunk, K - (int32_t)blockIdx.y * kchunk);
+    if (gridDim.y > 1) C32 += (int64_t)blockIdx.y * M * ldc;
     __shared__ __align__(16) uint16_t As[2][kGT][kGKP];
     __shared__ __align__(16) uint16_t Bs[2][kGT][kGKP];
     const int t = threadIdx.x, w = t >> 6;
     int64_t m0, n0;
     gemm_tile_origin(M, N, m0, n0);
-    const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
+    const int wm = (w >> 2) * 64, wn = (w & 3) * 32;
     const int kk0 = (t & 7) * 8;
-    int32_t oa[4], ob[4];
+    int32_t oa[kNtU], ob[kNtU];
     uint32_t ok = 0;
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-        const int r = (t >> 3) + 32 * u;
+    for (int u = 0; u < kNtU; u++) {
+        const int r = (t >> 3) + (kNtT / 8) * u;
         const int64_t ra = m0 + r, rb = n0 + r;
         ok |= (ra < M ? 1u : 0u) << u;
         ok |= (rb < N ? 1u : 0u) << (4 + u);
         oa[u] = (int32_t)((ra < M ? ra : M - 1) * (int64_t)lda) + kk0;
         ob[u] = (int32_t)((rb < N ? rb : N - 1) * (int64_t)ldb) + kk0;
     }
-    auto fetch = [&](uint4 (&ga)[4], uint4 (&gb)[4], int32_t k0) {
+    // (Loads only: the values are first used, and zeroed where they lie outside
+    // the operands, when they are staged, and every load is issued on every path.
+    // A select beside each load made the wave wait for it there, and no load
+    // overlapped a product: 29 us for 4096 x 1024 x 1024.)
+    auto fetch = [&](uint4 (&ga)[kNtU], uint4 (&gb)[kNtU], int32_t k0) {
+        const int32_t kc = k0 + kk0 < K ? k0 : K - 8 - kk0;
+#pragma unroll
+        for (int u = 0; u < kNtU; u++) {
+            ga[u] = *reinterpret_cast<const uint4 *>(A + oa[u] + kc);
+            gb[u] = *reinterpret_cast<const uint4 *>(B + ob[u] + kc);
+        }
+    };
+    auto stage = [&](int buf, const uint4 (&ga)[kNtU], const uint4 (&gb)[kNtU], int32_t k0) {
         const bool okk = k0 + kk0 < K;
-        const int32_t kc = okk ? k0 : K - 8 - kk0;
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const uint4 va = *reinterpret_cast<const uint4 *>(A + oa[u] + kc);
-            const uint4 vb = *reinterpret_cast<const uint4 *>(B + ob[u] + kc);
+        for (int u = 0; u < kNtU; u++) {
+            const int r = (t >> 3) + (kNtT / 8) * u;
             const bool ka = okk && ((ok >> u) & 1u), kb = okk && ((ok >> (4 + u)) & 1u);
-            ga[u] = make_uint4(ka ? va.x : 0u, ka ? va.y : 0u, ka ? va.z : 0u, ka ? va.w : 0u);
-            gb[u] = make_uint4(kb ? vb.x : 0u, kb ? vb.y : 0u, kb ? vb.z : 0u, kb ? vb.w : 0u);
+            *reinterpret_cast<uint4 *>(&As[buf][r][kk0]) =
+                make_uint4(ka ? ga[u].x : 0u, ka ? ga[u].y : 0u, ka ? ga[u].z : 0u, ka ? ga[u].w : 0u);
+            *reinterpret_cast<uint4 *>(&Bs[buf][r][kk0]) =
+                make_uint4(kb ? gb[u].x : 0u, kb ? gb[u].y : 0u, kb ? gb[u].z : 0u, kb ? gb[u].w : 0u);
         }
     };
-    auto stage = [&](int buf, const uint4 (&ga)[4], const uint4 (&gb)[4]) {
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int r = (t >> 3) + 32 * u;
-            *reinterpret_cast<uint4 *>(&As[buf][r][kk0]) = ga[u];
-            *reinterpret_cast<uint4 *>(&Bs[buf][r][kk0]) = gb[u];
-        }
-    };
-    f32x4 acc[4][4];
+    f32x4 acc[4][2];
 #pragma unroll
     for (int i = 0; i < 4; i++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < 2; j++) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // a0/b0 and a1/b1 alternate: while step s is multiplied from LDS buffer
-    // s%2, step s+1 is staged into the other buffer and step s+2 (or s+3)
-    // is in flight into the registers just staged
+    // s%2, step s+1 is staged into the other buffer and step s+3 is in flight
+    // into the registers just staged (steps past the last load its data again)
     const int32_t ns = (K + kGK - 1) / kGK;
-    uint4 a0[4], b0[4], a1[4], b1[4];
+    uint4 a0[kNtU], b0[kNtU], a1[kNtU], b1[kNtU];
     fetch(a0, b0, 0);
-    if (ns > 1) fetch(a1, b1, kGK);
-    stage(0, a0, b0);
-    if (ns > 2) fetch(a0, b0, 2 * kGK);
-    __syncthreads();
+    fetch(a1, b1, kGK);
+    stage(0, a0, b0, 0);
+    fetch(a0, b0, 2 * kGK);
+    lds_barrier();
     for (int32_t s = 0; s < ns; s += 2) {
         gemm_mfma_step(As[0], Bs[0], wm, wn, acc);
-        if (s + 1 < ns) {
-            stage(1, a1, b1);
-            if (s + 3 < ns) fetch(a1, b1, (s + 3) * kGK);
-        }
-        __syncthreads();
-        if (s + 1 < ns) {
-            gemm_mfma_step(As[1], Bs[1], wm, wn, acc);
-            if (s + 2 < ns) {
-                stage(0, a0, b0);
-                if (s + 4 < ns) fetch(a0, b0, (s + 4) * kGK);
-            }
-            __syncthreads();
-        }
+        stage(1, a1, b1, (s + 1) * kGK);
+        fetch(a1, b1, (s + 3) * kGK);
+        lds_barrier();
+        if (s + 1 < ns) gemm_mfma_step(As[1], Bs[1], wm, wn, acc);
+        stage(0, a0, b0, (s + 2) * kGK);
+        fetch(a0, b0, (s + 4) * kGK);
+        lds_barrier();
     }
-    gemm_epilogue(acc, m0 + wm, n0 + wn, M, N, bias, flags, mask, ldm, C32, C16, ldc);
+    gemm_epilogue(acc, m0 + wm, n0 + wn, M, N, bias, flags, mask, ldm, C32, C16, ldc, C16t, ldt);
 }
 
 // Loads one operand tile (rows r0.., k0..) into registers as 16-byte groups
@@ -344,13 +380,56 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint16_t *__restrict__ 
         gemm_epilogue(acc, m0 + wm, n0 + wn, M, N, bias, flags, mask, ldm, C32, C16, ldc);
 }
 
-// out[i] = sum over s = 0..S-1 (in order) of P[s*n + i]
+// out[i] = sum over s = 0..S-1 (in order) of P[s*n + i]; eight parts are loaded
+// before they are added.
 __global__ void k_sum_parts(const float *__restrict__ P, int32_t S, int64_t n, float *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     float v = 0.0f;
-    for (int32_t s = 0; s < S; s++) v += P[s * n + i];
+    int32_t s = 0;
+    for (; s + 8 <= S; s += 8) {
+        float p[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) p[u] = P[(s + u) * n + i];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v += p[u];
+    }
+    for (; s < S; s++) v += P[s * n + i];
     out[i] = v;
+}
+
+// dst[c][r] = src[r][c] for r < R, c < C (BF16; leading dimensions C and ldt >=
+// R); columns R.. up to ldt are zeros.  64 x 64 tiles through LDS.
+__global__ __launch_bounds__(256) void k_transpose(const uint16_t *__restrict__ src, int32_t R, int32_t C,
+                                                   uint16_t *__restrict__ dst, int32_t ldt) {
+    __shared__ __align__(4) uint16_t tile[64][66];
+    const int t = threadIdx.x;
+    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    if ((C & 1) == 0) {   // two columns per load
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int e = t + 256 * u, r = e >> 5, c = 2 * (e & 31);
+            const bool in = r0 + r < R && c0 + c < C;
+            *reinterpret_cast<uint32_t *>(&tile[r][c]) =
+                in ? *reinterpret_cast<const uint32_t *>(src + (int64_t)(r0 + r) * C + c0 + c) : 0u;
+        }
+    } else {
+        for (int e = t; e < 64 * 64; e += 256) {
+            const int r = e >> 6, c = e & 63;
+            tile[r][c] = r0 + r < R && c0 + c < C ? src[(int64_t)(r0 + r) * C + c0 + c] : (uint16_t)0;
+        }
+    }
+    __syncthreads();
+    for (int e = t; e < 64 * 32; e += 256) {   // two rows of the source per store (ldt is even)
+        const int c = e >> 5, r = 2 * (e & 31);
+        if (c0 + c < C && r0 + r < ldt)
+            *reinterpret_cast<uint32_t *>(dst + (int64_t)(c0 + c) * ldt + r0 + r) = tile[r][c] | (uint32_t)tile[r + 1][c] << 16;
+    }
+}
+
+static void transpose(const uint16_t *src, int32_t R, int32_t C, uint16_t *dst, int32_t ldt, hipStream_t st) {
+    hipLaunchKernelGGL(k_transpose, dim3((unsigned)((ldt + 63) / 64), (unsigned)((C + 63) / 64)), dim3(256), 0, st, src, R,
+                       C, dst, ldt);
 }
 
 // Size in floats of the training scratch that holds split-K partial
@@ -361,7 +440,7 @@ constexpr int64_t kGemmParts = 8ll << 20;
 static caps_status gemm(const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbn, int64_t sbk,
                         int32_t M, int32_t N, int32_t K, const float *bias, int32_t flags, const uint16_t *mask,
                         int64_t ldm, float *C32, uint16_t *C16, int64_t ldc, hipStream_t st,
-                        float *parts = nullptr) {
+                        float *parts = nullptr, uint16_t *C16t = nullptr, int64_t ldt = 0) {
     if (M <= 0 || N <= 0) return CAPS_OK;
     const auto aligned = [](const uint16_t *P) { return ((uintptr_t)P & 15) == 0; };
     // K-contiguous rows whose 8-element groups are 16-byte aligned
@@ -378,8 +457,8 @@ static caps_status gemm(const uint16_t *A, int64_t sam, int64_t sak, const uint1
         return CAPS_EINVAL;
     }
     if (vec_ok(A, sam, sak) && vec_ok(B, sbn, sbk) && (int64_t)M * sam < INT32_MAX && (int64_t)N * sbn < INT32_MAX) {
-        hipLaunchKernelGGL(k_gemm_nt, dim3((unsigned)tiles), dim3(256), 0, st, A, (int32_t)sam, B, (int32_t)sbn, M,
-                           N, K, bias, flags, mask, ldm, C32, C16, ldc);
+        hipLaunchKernelGGL(k_gemm_nt, dim3((unsigned)tiles), dim3(kNtT), 0, st, A, (int32_t)sam, B, (int32_t)sbn, M,
+                           N, K, K, bias, flags, mask, ldm, C32, C16, ldc, C16t, ldt);
         CAPS_HIP(hipGetLastError());
         return CAPS_OK;
     }
@@ -405,6 +484,33 @@ static caps_status gemm(const uint16_t *A, int64_t sam, int64_t sak, const uint1
         hipLaunchKernelGGL(k_gemm_bf16, dim3((unsigned)tiles), dim3(256), 0, st, A, sam, sak, B, sbn, sbk, M, N, K,
                            K, bias, flags, mask, ldm, C32, C16, ldc);
     }
+    CAPS_HIP(hipGetLastError());
+    if (C16t) transpose(C16, M, N, C16t, (int32_t)ldt, st);   // (k_gemm_nt writes it itself)
+    CAPS_HIP(hipGetLastError());
+    return CAPS_OK;
+}
+
+// C (M x N, FP32) = A B^T over the K batch rows of transposed matrices, A (M x
+// K) and B (N x K) with leading dimension ldk (K rounded up to a multiple of 8,
+// the further columns zero).  K is split as in gemm() when the tiles alone
+// cannot fill the chip.
+static caps_status gemm_grad(const uint16_t *A, const uint16_t *B, int32_t ldk, int32_t M, int32_t N, int32_t K, float *C32,
+                             hipStream_t st, float *parts) {
+    const int64_t tiles = (int64_t)((M + kGT - 1) / kGT) * ((N + kGT - 1) / kGT), n = (int64_t)M * N;
+    if (tiles > INT32_MAX || (int64_t)M * ldk >= INT32_MAX || (int64_t)N * ldk >= INT32_MAX) {
+        // offsets beyond k_gemm_nt's
+        return gemm(A, ldk, 1, B, ldk, 1, M, N, ldk, nullptr, 0, nullptr, 0, C32, nullptr, N, st, parts);
+    }
+    const int64_t want = (512 + tiles - 1) / tiles;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(K / (4 * kGK), kGemmParts / n));
+    int32_t splits = (int32_t)std::min<int64_t>(want, most);
+    const int32_t kchunk = (int32_t)(((K + splits - 1) / splits + kGK - 1) / kGK * kGK);
+    splits = (K + kchunk - 1) / kchunk;
+    hipLaunchKernelGGL(k_gemm_nt, dim3((unsigned)tiles, (unsigned)splits), dim3(kNtT), 0, st, A, ldk, B, ldk, M, N, ldk,
+                       splits > 1 ? kchunk : ldk, nullptr, 0, nullptr, 0, splits > 1 ? parts : C32, nullptr, (int64_t)N,
+                       nullptr, 0);
+    if (splits > 1)
+        hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, parts, splits, n, C32);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;
 }
@@ -510,56 +616,92 @@ __global__ void k_negate(const float *__restrict__ x, int32_t n, float *__restri
 // One workgroup per row: softmax of the logits, loss -(1/|S|) sum_{s in S}
 // log p_s over the row's distinct labels S (entries < 0 are padding), and
 // the logit gradient (p - y) / M with y uniform on S (both 0 when S is
-// empty), as FP32 and BF16.
+// empty), as FP32 and BF16.  The row stays in registers (kCeRow logits per
+// thread, longer rows are read again); labels are loaded by a wave at once.
+// Sums add thread t + o to t, o = 128, 64, .. 1: across the waves through LDS,
+// then by lane shuffles.
+constexpr int kCeRow = 8;
+__device__ inline float ce_lane_reduce(float v, bool mx) {   // lane 0 of wave 0: t + o to t, o = 32 .. 1
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const float u = __shfl_down(v, o, 64);
+        v = mx ? fmaxf(v, u) : v + u;
+    }
+    return v;
+}
 __global__ __launch_bounds__(256) void k_softmax_ce(const float *__restrict__ Z, int32_t M, int32_t nout,
                                                     const int32_t *__restrict__ labels, int32_t L,
                                                     float *__restrict__ loss_rows, float *__restrict__ dZ32,
                                                     uint16_t *__restrict__ dZ16) {
-    __shared__ float red[256];
+    __shared__ float red[256], total[2];
     __shared__ int32_t lab[64];
     __shared__ int32_t nlab;
     const int64_t i = blockIdx.x;
     const float *z = Z + i * nout;
     const int t = threadIdx.x;
-    if (t == 0) {
+    float zr[kCeRow];
+#pragma unroll
+    for (int u = 0; u < kCeRow; u++) zr[u] = t + 256 * u < nout ? z[t + 256 * u] : 0.0f;
+    if (t < 64) {   // distinct labels in their order, at most 64
         int n = 0;
-        for (int e = 0; e < L && n < 64; e++) {
-            const int32_t v = labels[i * L + e];
-            if (v < 0 || v >= nout) continue;
-            bool dup = false;
-            for (int f = 0; f < n; f++) dup |= lab[f] == v;
-            if (!dup) lab[n++] = v;
+        for (int e0 = 0; e0 < L && n < 64; e0 += 64) {
+            const int32_t lv = e0 + t < L ? labels[i * L + e0 + t] : -1;
+            for (int e = 0; e < min(64, L - e0) && n < 64; e++) {
+                const int32_t v = __builtin_amdgcn_readlane(lv, e);
+                if (v < 0 || v >= nout) continue;
+                const bool dup = __ballot(t < n && lab[t] == v) != 0;
+                if (!dup) {
+                    if (t == 0) lab[n] = v;
+                    n++;
+                }
+                wave_sync();
+            }
         }
-        nlab = n;
+        if (t == 0) nlab = n;
     }
+    // o = 128, 64 through LDS, the rest in wave 0
+    auto reduce = [&](float v, bool mx, int slot) {
+        red[t] = v;
+        __syncthreads();
+        if (t < 64) {
+            const float a = mx ? fmaxf(red[t], red[t + 128]) : red[t] + red[t + 128];
+            const float b = mx ? fmaxf(red[t + 64], red[t + 192]) : red[t + 64] + red[t + 192];
+            const float r = ce_lane_reduce(mx ? fmaxf(a, b) : a + b, mx);
+            if (t == 0) total[slot] = r;
+        }
+        __syncthreads();
+        return total[slot];
+    };
     float mx = -__builtin_huge_valf();
-    for (int j = t; j < nout; j += 256) mx = fmaxf(mx, z[j]);
-    red[t] = mx;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) red[t] = fmaxf(red[t], red[t + o]);
-        __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCeRow; u++)
+        if (t + 256 * u < nout) mx = fmaxf(mx, zr[u]);
+    for (int j = t + 256 * kCeRow; j < nout; j += 256) mx = fmaxf(mx, z[j]);
+    mx = reduce(mx, true, 0);
+    float s = 0.0f, er[kCeRow];
+#pragma unroll
+    for (int u = 0; u < kCeRow; u++) {
+        er[u] = 0.0f;
+        if (t + 256 * u < nout) {
+            er[u] = expf(zr[u] - mx);
+            s += er[u];
+        }
     }
-    mx = red[0];
-    __syncthreads();
-    float s = 0.0f;
-    for (int j = t; j < nout; j += 256) s += expf(z[j] - mx);
-    red[t] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) red[t] += red[t + o];
-        __syncthreads();
-    }
-    const float sum = red[0];
+    for (int j = t + 256 * kCeRow; j < nout; j += 256) s += expf(z[j] - mx);
+    const float sum = reduce(s, false, 1);
     const int n = nlab;
     const float inv = n ? 1.0f / (float)n : 0.0f;
-    for (int j = t; j < nout; j += 256) {
+    auto grad = [&](int j, float ex) {
         float y = 0.0f;
         for (int f = 0; f < n; f++) y += lab[f] == j ? inv : 0.0f;
-        const float g = n ? (expf(z[j] - mx) / sum - y) / (float)M : 0.0f;
+        const float g = n ? (ex / sum - y) / (float)M : 0.0f;
         dZ32[i * nout + j] = g;
         dZ16[i * nout + j] = bf16_rne(g);
-    }
+    };
+#pragma unroll
+    for (int u = 0; u < kCeRow; u++)
+        if (t + 256 * u < nout) grad(t + 256 * u, er[u]);
+    for (int j = t + 256 * kCeRow; j < nout; j += 256) grad(j, expf(z[j] - mx));
     if (t == 0) {
         float l = 0.0f;
         if (n) {
@@ -614,9 +756,12 @@ __global__ __launch_bounds__(256) void k_accum_mean(const float *__restrict__ v,
 }
 
 // ------------------------------------------------------------------ Adam (K13)
+// One step of every parameter, with the BF16 copies of the two weight matrices
+// (parameters [0, n1) and [o2, o2 + n2)).
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
                        float *__restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float bc1,
-                       float bc2) {
+                       float bc2, int64_t n1, uint16_t *__restrict__ w1h, int64_t o2, int64_t n2,
+                       uint16_t *__restrict__ w2h) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float gi = g[i];
@@ -624,7 +769,10 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
     const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+    const float w = p[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+    p[i] = w;
+    if (i < n1) w1h[i] = bf16_rne(w);
+    else if (i >= o2 && i < o2 + n2) w2h[i - o2] = bf16_rne(w);
 }
 
 __global__ void k_to_bf16(const float *__restrict__ x, int64_t n, uint16_t *__restrict__ y) {
@@ -763,12 +911,31 @@ static uint64_t sm64_next(uint64_t &s) {
     return mix64(s);
 }
 
+// Drawn weights: W ~ U(-1/sqrt(fan_in), 1/sqrt(fan_in)) from splitmix64(seed),
+// W1 row by row (padding columns drawn and zeroed), then W2; zero biases.
+// Draw i of the generator is a function of seed and i alone.
+__global__ void k_router_draw(float *__restrict__ p, uint64_t seed, int32_t din, int32_t dpad, int64_t n1, int64_t o2,
+                              int64_t n, double a1, double a2) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const bool w1 = i < n1, w2 = i >= o2 && i < o2 + (n - o2);
+    float w = 0.0f;
+    if (w1 || w2) {
+        const uint64_t draw = (uint64_t)(w1 ? i : n1 + (i - o2));
+        const double u = (double)(mix64(seed + (draw + 1) * 0x9E3779B97F4A7C15ull) >> 11) * 0x1p-53;
+        if (!w1 || (int32_t)(i % dpad) < din) w = (float)((2.0 * u - 1.0) * (w1 ? a1 : a2));
+    }
+    p[i] = w;
+}
+
 // Allocates a router for the index with zeroed moments; w1/b1/w2/b2 from
-// host arrays, or (when null) W ~ U(-1/sqrt(fan_in), 1/sqrt(fan_in)) drawn
-// from splitmix64(seed) and zero biases.
+// host arrays, or (when null) drawn.  A router of the same shape is filled
+// again in place.
 static caps_status router_alloc(Index *ix, int32_t hid, float in_scale, float in_shift, float fb_prob, uint64_t seed,
                                 const float *w1, const float *b1, const float *w2, const float *b2) {
-    Router *R = new Router;
+    Router *old = ix->router;
+    const bool reuse = !w1 && old && old->hid == hid && old->nout == ix->b && old->din == ix->d + kEmbed;
+    Router *R = reuse ? old : new Router;
     R->din = ix->d + kEmbed;
     R->dpad = (R->din + 31) / 32 * 32;
     R->hid = hid;
@@ -776,57 +943,58 @@ static caps_status router_alloc(Index *ix, int32_t hid, float in_scale, float in
     R->in_scale = in_scale;
     R->in_shift = in_shift;
     R->fb_prob = fb_prob;
+    R->step = 0;
     R->o_b1 = (int64_t)hid * R->dpad;
     R->o_w2 = R->o_b1 + hid;
     R->o_b2 = R->o_w2 + (int64_t)R->nout * hid;
     R->nparam = R->o_b2 + R->nout;
-    std::vector<float> h((size_t)R->nparam, 0.0f);
-    if (w1) {
-        memcpy(h.data(), w1, sizeof(float) * (size_t)R->o_b1);
-        memcpy(h.data() + R->o_b1, b1, sizeof(float) * (size_t)hid);
-        memcpy(h.data() + R->o_w2, w2, sizeof(float) * (size_t)R->nout * hid);
-        memcpy(h.data() + R->o_b2, b2, sizeof(float) * (size_t)R->nout);
-    } else {
-        uint64_t s = seed;
-        const double a1 = 1.0 / sqrt((double)R->din), a2 = 1.0 / sqrt((double)hid);
-        for (int64_t r = 0; r < hid; r++)
-            for (int64_t c = 0; c < R->dpad; c++) {
-                const double u = (double)(sm64_next(s) >> 11) * 0x1p-53;
-                h[(size_t)(r * R->dpad + c)] = c < R->din ? (float)((2.0 * u - 1.0) * a1) : 0.0f;
-            }
-        for (int64_t e = 0; e < (int64_t)R->nout * hid; e++) {
-            const double u = (double)(sm64_next(s) >> 11) * 0x1p-53;
-            h[(size_t)(R->o_w2 + e)] = (float)((2.0 * u - 1.0) * a2);
-        }
-    }
     const size_t pb = sizeof(float) * (size_t)R->nparam;
     auto fail_free = [&](hipError_t e) {
-        router_free(R);
+        if (!reuse) router_free(R);
         set_error("router allocation failed: %s", hipGetErrorString(e));
         return e == hipErrorOutOfMemory ? CAPS_ENOMEM : CAPS_EDEVICE;
     };
     hipError_t e;
-    if ((e = hipMalloc((void **)&R->param, pb)) != hipSuccess) return fail_free(e);
-    if ((e = hipMalloc((void **)&R->mom, pb)) != hipSuccess) return fail_free(e);
-    if ((e = hipMalloc((void **)&R->vel, pb)) != hipSuccess) return fail_free(e);
-    if ((e = hipMalloc((void **)&R->w1h, sizeof(uint16_t) * (size_t)R->o_b1)) != hipSuccess) return fail_free(e);
-    if ((e = hipMalloc((void **)&R->w2h, sizeof(uint16_t) * (size_t)R->nout * hid)) != hipSuccess)
+    if (!reuse) {
+        if ((e = hipMalloc((void **)&R->param, pb)) != hipSuccess) return fail_free(e);
+        if ((e = hipMalloc((void **)&R->mom, pb)) != hipSuccess) return fail_free(e);
+        if ((e = hipMalloc((void **)&R->vel, pb)) != hipSuccess) return fail_free(e);
+        if ((e = hipMalloc((void **)&R->w1h, sizeof(uint16_t) * (size_t)R->o_b1)) != hipSuccess) return fail_free(e);
+        if ((e = hipMalloc((void **)&R->w2h, sizeof(uint16_t) * (size_t)R->nout * hid)) != hipSuccess)
+            return fail_free(e);
+    } else if ((e = hipDeviceSynchronize()) != hipSuccess) {   // (calls in flight may still read the weights)
         return fail_free(e);
-    if ((e = hipMemcpy(R->param, h.data(), pb, hipMemcpyHostToDevice)) != hipSuccess) return fail_free(e);
-    if ((e = hipMemset(R->mom, 0, pb)) != hipSuccess) return fail_free(e);
-    if ((e = hipMemset(R->vel, 0, pb)) != hipSuccess) return fail_free(e);
+    }
+    if (w1) {
+        std::vector<float> h((size_t)R->nparam, 0.0f);
+        memcpy(h.data(), w1, sizeof(float) * (size_t)R->o_b1);
+        memcpy(h.data() + R->o_b1, b1, sizeof(float) * (size_t)hid);
+        memcpy(h.data() + R->o_w2, w2, sizeof(float) * (size_t)R->nout * hid);
+        memcpy(h.data() + R->o_b2, b2, sizeof(float) * (size_t)R->nout);
+        if ((e = hipMemcpy(R->param, h.data(), pb, hipMemcpyHostToDevice)) != hipSuccess) return fail_free(e);
+    } else {
+        hipLaunchKernelGGL(k_router_draw, dim3((unsigned)nblk(R->o_b2, 256)), dim3(256), 0, 0, R->param, seed, R->din,
+                           R->dpad, R->o_b1, R->o_w2, R->o_b2, 1.0 / sqrt((double)R->din), 1.0 / sqrt((double)hid));
+        if ((e = hipMemsetAsync(R->param + R->o_b2, 0, sizeof(float) * (size_t)R->nout, 0)) != hipSuccess)
+            return fail_free(e);
+    }
+    if ((e = hipMemsetAsync(R->mom, 0, pb, 0)) != hipSuccess) return fail_free(e);
+    if ((e = hipMemsetAsync(R->vel, 0, pb, 0)) != hipSuccess) return fail_free(e);
     hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)nblk(R->o_b1, 256)), dim3(256), 0, 0, R->param, R->o_b1, R->w1h);
     hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)nblk((int64_t)R->nout * hid, 256)), dim3(256), 0, 0,
                        R->param + R->o_w2, (int64_t)R->nout * hid, R->w2h);
     if ((e = hipDeviceSynchronize()) != hipSuccess) return fail_free(e);
-    router_free(ix->router);
-    ix->router = R;
+    if (!reuse) {
+        router_free(ix->router);
+        ix->router = R;
+    }
     return CAPS_OK;
 }
 
 // Workspace of one training / gradient batch of up to bs rows.
 struct BatchWs {
     uint16_t *Xb, *Hb, *dZ16, *dH16;
+    uint16_t *XT, *HT, *dZT, *dHT, *W2T;   // transposed, the batch rounded up to a multiple of 8 columns
     int32_t *Lb;
     float *Z, *dZ32, *dH32, *grad, *loss_rows, *parts;
 };
@@ -844,6 +1012,12 @@ static size_t batch_ws(const Router &R, int32_t bs, int32_t L, uint8_t *base, Ba
     t.Hb = (uint16_t *)take(sizeof(uint16_t) * (size_t)bs * R.hid);
     t.dZ16 = (uint16_t *)take(sizeof(uint16_t) * (size_t)bs * R.nout);
     t.dH16 = (uint16_t *)take(sizeof(uint16_t) * (size_t)bs * R.hid);
+    const size_t ldk = ((size_t)bs + 7) / 8 * 8;
+    t.XT = (uint16_t *)take(sizeof(uint16_t) * ldk * R.dpad);
+    t.HT = (uint16_t *)take(sizeof(uint16_t) * ldk * R.hid);
+    t.dZT = (uint16_t *)take(sizeof(uint16_t) * ldk * R.nout);
+    t.dHT = (uint16_t *)take(sizeof(uint16_t) * ldk * R.hid);
+    t.W2T = (uint16_t *)take(sizeof(uint16_t) * (size_t)R.nout * R.hid);
     t.Lb = (int32_t *)take(sizeof(int32_t) * (size_t)bs * std::max(L, 1));
     t.Z = (float *)take(sizeof(float) * (size_t)bs * R.nout);
     t.dZ32 = (float *)take(sizeof(float) * (size_t)bs * R.nout);
@@ -858,9 +1032,10 @@ static size_t batch_ws(const Router &R, int32_t bs, int32_t L, uint8_t *base, Ba
 // Forward, loss and gradients of one batch already gathered into w.Xb / w.Lb.
 static caps_status batch_grads(const Router &R, const BatchWs &w, int32_t nb, int32_t L, hipStream_t st) {
     caps_status s;
+    const int32_t ldk = (nb + 7) / 8 * 8;
     // h = relu(W1 x + b1), z = W2 h + b2
     s = gemm(w.Xb, R.dpad, 1, R.w1h, R.dpad, 1, nb, R.hid, R.dpad, R.param + R.o_b1, kGemmRelu, nullptr, 0,
-             nullptr, w.Hb, R.hid, st);
+             nullptr, w.Hb, R.hid, st, nullptr, w.HT, ldk);
     if (s != CAPS_OK) return s;
     s = gemm(w.Hb, R.hid, 1, R.w2h, R.hid, 1, nb, R.nout, R.hid, R.param + R.o_b2, 0, nullptr, 0, w.Z, nullptr,
              R.nout, st);
@@ -870,18 +1045,23 @@ static caps_status batch_grads(const Router &R, const BatchWs &w, int32_t nb, in
     CAPS_HIP(hipGetLastError());
     float *gw1 = w.grad, *gb1 = w.grad + R.o_b1, *gw2 = w.grad + R.o_w2, *gb2 = w.grad + R.o_b2;
     // dW2 = dZ^T h;  db2 = column sums of dZ
-    s = gemm(w.dZ16, 1, R.nout, w.Hb, 1, R.hid, R.nout, R.hid, nb, nullptr, 0, nullptr, 0, gw2, nullptr, R.hid, st,
-             w.parts);
+    transpose(w.dZ16, nb, R.nout, w.dZT, ldk, st);
+    s = gemm_grad(w.dZT, w.HT, ldk, R.nout, R.hid, nb, gw2, st, w.parts);
     if (s != CAPS_OK) return s;
     colsum(w.dZ32, nb, R.nout, w.parts, gb2, st);
     // dH = (dZ W2) masked by h > 0;  db1 = column sums of dH
-    s = gemm(w.dZ16, R.nout, 1, R.w2h, 1, R.hid, nb, R.hid, R.nout, nullptr, kGemmMask, w.Hb, R.hid, w.dH32, w.dH16,
-             R.hid, st);
+    // (W2 transposed where its rows of nout allow 16-byte loads)
+    const bool w2t = R.nout % 8 == 0;
+    if (w2t) transpose(R.w2h, R.nout, R.hid, w.W2T, R.nout, st);
+    s = w2t ? gemm(w.dZ16, R.nout, 1, w.W2T, R.nout, 1, nb, R.hid, R.nout, nullptr, kGemmMask, w.Hb, R.hid, w.dH32, w.dH16,
+                   R.hid, st, nullptr, w.dHT, ldk)
+            : gemm(w.dZ16, R.nout, 1, R.w2h, 1, R.hid, nb, R.hid, R.nout, nullptr, kGemmMask, w.Hb, R.hid, w.dH32, w.dH16,
+                   R.hid, st, nullptr, w.dHT, ldk);
     if (s != CAPS_OK) return s;
     colsum(w.dH32, nb, R.hid, w.parts, gb1, st);
     // dW1 = dH^T x
-    s = gemm(w.dH16, 1, R.hid, w.Xb, 1, R.dpad, R.hid, R.dpad, nb, nullptr, 0, nullptr, 0, gw1, nullptr, R.dpad, st,
-             w.parts);
+    transpose(w.Xb, nb, R.dpad, w.XT, ldk, st);
+    s = gemm_grad(w.dHT, w.XT, ldk, R.hid, R.dpad, nb, gw1, st, w.parts);
     if (s != CAPS_OK) return s;
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;
@@ -1114,7 +1294,8 @@ extern "C" caps_status caps_router_train(caps_index *idx, const caps_router_para
     const size_t off_batch = al(off_perm + sizeof(int32_t) * (size_t)n);
     const size_t total = off_batch + batch_ws(R, bs, n_labels, nullptr, nullptr);
     uint8_t *base = nullptr;
-    CAPS_HIP(hipMallocAsync((void **)&base, total, st));
+    s = ws_alloc((void **)&base, total, ix.device, st);   // (the library's pool: the free keeps it)
+    if (s != CAPS_OK) return s;
     uint16_t *X = reinterpret_cast<uint16_t *>(base);
     int32_t *perm = reinterpret_cast<int32_t *>(base + off_perm);
     BatchWs w;
@@ -1152,11 +1333,8 @@ extern "C" caps_status caps_router_train(caps_index *idx, const caps_router_para
             const double bc1 = 1.0 - pow((double)p->beta1, (double)R.step);
             const double bc2 = 1.0 - pow((double)p->beta2, (double)R.step);
             hipLaunchKernelGGL(k_adam, dim3((unsigned)nblk(R.nparam, 256)), dim3(256), 0, st, R.param, w.grad, R.mom,
-                               R.vel, R.nparam, p->lr, p->beta1, p->beta2, p->eps, (float)bc1, (float)bc2);
-            hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)nblk(R.o_b1, 256)), dim3(256), 0, st, R.param, R.o_b1,
-                               R.w1h);
-            hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)nblk((int64_t)R.nout * R.hid, 256)), dim3(256), 0, st,
-                               R.param + R.o_w2, (int64_t)R.nout * R.hid, R.w2h);
+                               R.vel, R.nparam, p->lr, p->beta1, p->beta2, p->eps, (float)bc1, (float)bc2, R.o_b1, R.w1h,
+                               R.o_w2, (int64_t)R.nout * R.hid, R.w2h);
             e = hipGetLastError();
             if (e != hipSuccess) {
                 set_error("caps_router_train: %s", hipGetErrorString(e));

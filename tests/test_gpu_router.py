@@ -229,3 +229,24 @@ def test_short_training_run_tracks_oracle(caps, tiny):
     got = ix.router_get()
     for k in params:
         assert _rel(got[k] - wt[k], params[k] - wt[k]) < 0.02, k
+
+
+@pytest.mark.parametrize("b,hid,rows", [(13, 48, 77), (200, 144, 1), (1000, 80, 700), (136, 272, 1100)])
+def test_gradient_shapes(caps, b, hid, rows):
+    """The transposed products at their edges: output widths that are not
+    multiples of 8 or of a tile, batches that are not multiples of 8, a single
+    row, batches whose rows are split (more than 512)."""
+    w = synth.make_tiny(960 + b, n=2000, d=20, n_q=rows, vocabs=(3, 4), b=b, h=1, cmin=0, cmax=2)
+    ix = caps.Index.from_workload(w, kmeans_iters=1)
+    rng = np.random.default_rng(b)
+    wt = _weights(rng, hid, R.pad_width(w.d), b)
+    ix.router_set(**wt, hidden=hid, in_scale=0.9, in_shift=0.1)
+    labels = rng.integers(-1, b, size=(rows, 5)).astype(np.int32)
+    labels[:, 3] = labels[:, 0]   # (a repeated label counts once)
+    loss, g = ix.router_grads(w.q, w.con_off, w.con_attr, w.con_val, labels)
+    x = R.input_rows(w.q, w.con_off, w.con_attr, w.con_val, w.dense_vocab, w.label_vocab, 0.9, 0.1)
+    want_loss, want = R.loss_and_grads(x, labels, **wt)
+    assert abs(loss - want_loss) <= 1e-4 * abs(want_loss)
+    for k in ("w1", "b1", "w2", "b2"):
+        assert _rel(g[k], want[k]) < 1e-4, k
+    ix.close()
