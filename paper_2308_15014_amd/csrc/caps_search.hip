@@ -782,8 +782,11 @@ __device__ __attribute__((always_inline)) inline void fetch_chunk(
 }
 
 // Partition-major filtered scan.  One workgroup = one tile (a partition and
-// up to QB of the queries probing it); wave w owns queries 16w..16w+15 and
-// does their filtering, survivor compaction, distances and candidate
+// up to QB of the queries probing it); wave w owns an even share of them, at
+// most 16 (in runs of 16 from the first wave on, a tile of 23 queries kept six
+// of eight waves idle: 342 us for the second round of 146 queries over 304
+// partitions of 664 rows, d = 128, against 190 dealt evenly), and does
+// their filtering, survivor compaction, distances and candidate
 // selection with no workgroup barrier beyond the two per chunk.  Chunks of
 // 64 points of the chosen sub-partitions go through LDS (the next chunk is
 // prefetched into registers); survivors go to a per-wave ring of (query,
@@ -830,13 +833,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 2)))
 
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     const bool has_dense = A.words != nullptr;
-    const int qbase = w * kQPW;
+    // the tile's queries dealt evenly to the waves, in runs of at most kQPW
+    const int qpw = (nqt + NW - 1) / NW, qbase = w * qpw, qend = min(nqt, qbase + qpw);
     if (t <= h + 1) spo[t] = A.offs[(int64_t)p * (h + 1) + t];
-    // per-query state; lane i < 16 of wave w keeps query qbase+i in registers
+    // per-query state; lane i < qpw of wave w keeps query qbase+i in registers
     uint32_t my_sel = 0, my_dmask = 0, my_dval = 0;
     int my_surv = 0;
     int32_t my_qq = -1;
-    if (lane < kQPW && qbase + lane < nqt) {
+    if (qbase + lane < qend) {
         const int qi = qbase + lane;
         const int32_t slot = ent[qi];
         my_qq = slot / A.m;
@@ -1027,7 +1031,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 2)))
             wave_sync();
             head += n;
         };
-        for (int i = 0; i < kQPW; i++) {
+        for (int i = 0; i < qpw; i++) {
             const uint32_t sl = __builtin_amdgcn_readlane(my_sel, i);
             if (!(sl & (1u << j))) continue;
             bool pass;
@@ -1059,9 +1063,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 2)))
     }
     // ---- finalize my queries: best k sorted, partial list, shared bound,
     // survivor count
-    for (int i = 0; i < kQPW; i++) {
-        const int qi = qbase + i;
-        if (qi >= nqt) break;
+    for (int qi = qbase; qi < qend; qi++) {
         buf_reduce<C>(buf, bcnt, tau, qi, k);
         const int c = bcnt[qi];
         uint64_t *out = A.partials + (int64_t)qslot[qi] * k;
