@@ -28,6 +28,7 @@ struct LowpArgs {
     const uint64_t *sigs;
     const uint16_t *slots;
     int32_t lslots;             // label slots per point
+    int32_t wbits;              // bits of the packed dense word in use
     const uint8_t *qlow;        // query rows of dpad elements
     const float *qscale, *qaux;
     const float *vecs, *q;      // FP32 CSR rows and queries (exact rescoring)

@@ -542,6 +542,8 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     A.sigs = ix->sigs;
     A.slots = ix->slots;
     A.lslots = ix->lslots;
+    A.wbits = 0;
+    for (int a = 0; a < ix->sch.n_dense; a++) A.wbits += ix->sch.field_bits[a];
     A.qlow = reinterpret_cast<const uint8_t *>(S.qlow);
     A.qscale = S.qscale;
     A.qaux = S.qaux;
@@ -595,7 +597,7 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     const int64_t full = (S.max_tiles + kXcds - 1) / kXcds * kXcds;
     const int64_t rcap = S.rescue_grid > 0 ? S.rescue_grid : kRescueWgs;
     const int64_t grid = S.kind == 2 || S.kind == 5 ? std::min<int64_t>(full, rcap) : full;
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kLNT), lds, st, A);
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(x32 ? kXW * 64 : kLNT), lds, st, A);
     prof_end(S.stage, st);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;

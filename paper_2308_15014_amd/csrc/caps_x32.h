@@ -9,15 +9,27 @@
 //    the 32 queries 32w..32w+31, whose operands stay in registers;
 //  * each product is a 32 x 32 block (points x queries, K = 16 per step), so
 //    a staged row read from LDS serves 32 queries instead of 16;
-//  * chunks are 32 rows, staged by direct loads three chunks ahead into four
-//    buffers, with explicit per-wave wait counts and plain barriers;
-//  * the packed dense test runs only for the products where a score passed,
-//    the label signature test and a disjunction's terms' dense fields and
-//    signatures (staged data and registers) only where that passed too.  The
-//    main pass makes the rest of the filter test (label slots; global reads)
-//    when it drains a wave's ring of pairs, one pair per lane, so that one round trip to memory
-//    serves up to 64 pairs; a pair was tested as it was found before, one
-//    round trip for each block of products with any passing score.
+//  * rows come in chunks of 32, two chunks a step, staged by direct loads one
+//    step ahead into two buffers; one barrier a step.  Which rows a chunk holds
+//    is laid out for 64 chunks at once, one per lane, and read out by lane
+//    index (a cursor advanced per chunk cost 100 scalar instructions a chunk);
+//  * a chunk is skipped where the AND and OR of its rows' packed words show
+//    that no query of the wave passes, without labels also where no row passes
+//    any query's packed test;
+//  * the filter test of an element runs on staged words: the packed dense
+//    fields and, in the bits they leave free, the label signature folded, in
+//    one masked compare; then the signature.  The main pass makes the rest
+//    (label slots, terms of disjunctions; global reads) when it drains a wave's
+//    ring of pairs, one pair per lane, so that one round trip to memory serves
+//    up to 64 pairs.
+// What bounds it: the chain of waits of a step, with four waves per SIMD (matrix
+// cores busy 18 % of the time, vector units 36 %).  Before the steps of two
+// chunks, the masks of passing elements (instead of branches per element) and
+// the folded signatures: main pass of 10k queries x 1M x 128 BF16 1.73 ms, now
+// 1.63; 4k queries, labels, 96-d FP8 3.16, now 2.46; 8k queries, dense values
+// and labels, 2M FP16 5.59, now 4.98; their seed passes 0.25, 0.70 and 1.37 ms,
+// now 0.23, 0.46 and 1.04.  Two blocks of queries per wave (half the steps, but
+// 3 and 2 waves per SIMD) ran 1.83, 4.40 and 7.86 ms.
 // Element r of lane l is point 8(r/4) + 4(l/32) + r%4 of the chunk and query
 // l%32 of the wave.  MODE 0 is the exact main pass, MODE 1 the same counting
 // the survivors of the filter, MODE 2 the seed pass of the exact search:
@@ -38,7 +50,8 @@
 
 namespace caps {
 
-constexpr int kXW = 4;                 // waves per tile
+constexpr int kXG = 2;                 // chunks per step
+constexpr int kXW = 2 * kXG;           // waves per tile
 constexpr int kXQ = 32;                // queries per wave
 constexpr int kXQB = kXW * kXQ;        // entries per tile
 constexpr int kXCH = 32;               // rows per chunk
@@ -63,9 +76,29 @@ __device__ inline f32x16 mma32(uint4 a, uint4 b, f32x16 c) {
     }
 }
 
-// Register budget per SIMD: four waves; three with the label state.
+// A label signature folded into the bits of the packed word that no dense field
+// uses (nfree of them from bit `at` on): the query's folded bits are a subset
+// of those of every point that holds its labels, so the one masked compare of
+// the packed words refuses most pairs that fail the labels.  nfree 0: no bits.
+__device__ inline uint32_t fold_sig(uint64_t sig, int at, int nfree) {
+    if (nfree == 0) return 0u;
+    uint64_t f = 0;
+    for (int s = 0; s < 64; s += nfree) f |= sig >> s;
+    return (uint32_t)(f & ((1ull << nfree) - 1ull)) << at;
+}
+
+// Waves per SIMD the registers are budgeted for.  A step is a chain of waits
+// (LDS operands, products, tests), so a fourth wave beats the registers it
+// costs: FP8 labels 2.46 against 3.04 ms in the main pass and 0.56 against
+// 0.65 ms in the seed pass although 22 registers spill there, FP16 labels 5.03
+// against 5.47 ms.  Disjunctions (their terms in registers) and seed lists of
+// four keys with labels stay at three.
+constexpr int x32_waves(int mode, int mh, int filt) {
+    return filt == 2 || (filt == 1 && mode == 2 && mh > 1) ? 3 : 4;
+}
+
 template <int PREC, int NS, int MODE, int MH, int FILT>
-__global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ? 3 : 4))) void k_scan_x32(LowpArgs A) {
+__global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_waves(MODE, MH, FILT)))) void k_scan_x32(LowpArgs A) {
     constexpr bool LAB = FILT != 0;     // label tests (an index with labels)
     constexpr bool DISJ = FILT == 2;    // and disjunctions, on any index
     static_assert(!(LAB && MODE == 1), "survivors of label tests are counted by k_scan_mfma");
@@ -75,44 +108,37 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     constexpr bool F8 = PREC == CAPS_PREC_FP8;
     constexpr int ROWB = NS * (F8 ? 32 : 64);      // bytes per row of the copy
     constexpr int KS = ROWB / 32;                  // 16-byte operands per lane and row
-    constexpr bool PTS2 = LAB || F8;               // a second per-point load: signatures, FP8 scales
     constexpr int V16 = ROWB / 16;                 // 16-byte pieces per row
     constexpr int NDMA = kXCH * ROWB / 1024;       // 1 KB direct loads per chunk
-    constexpr int UPW = (NDMA + kXW - 1) / kXW;
+    constexpr int UPW = (kXG * NDMA + kXW - 1) / kXW;
     constexpr int RPL = ROWB >= 256 ? 1 : 256 / ROWB;
     constexpr int SWZ = ROWB >= 256 ? 15 : V16 - 1;
-    constexpr int PRE = 4;                         // per-point inputs per chunk (one direct load per wave)
-    static_assert(PRE == kXW, "each wave stages one per-point input");
-    // the four chunk buffers: distinct arrays, so that the compiler can tell
-    // the reads of one from the direct loads into the others
-    __shared__ __align__(16) uint8_t xb0[kXCH * ROWB];
-    __shared__ __align__(16) uint8_t xb1[kXCH * ROWB];
-    __shared__ __align__(16) uint8_t xb2[kXCH * ROWB];
-    __shared__ __align__(16) uint8_t xb3[kXCH * ROWB];
-    __shared__ __align__(16) float rw0[PRE][kXCH];   // the per-point inputs of each buffer's chunk
-    __shared__ __align__(16) float rw1[PRE][kXCH];
-    __shared__ __align__(16) float rw2[PRE][kXCH];
-    __shared__ __align__(16) float rw3[PRE][kXCH];
-    // the second per-point load: label signatures (two words each), FP8 scales
-    __shared__ __align__(16) uint32_t rg0[PTS2 ? 3 : 1][PTS2 ? kXCH : 1];
-    __shared__ __align__(16) uint32_t rg1[PTS2 ? 3 : 1][PTS2 ? kXCH : 1];
-    __shared__ __align__(16) uint32_t rg2[PTS2 ? 3 : 1][PTS2 ? kXCH : 1];
-    __shared__ __align__(16) uint32_t rg3[PTS2 ? 3 : 1][PTS2 ? kXCH : 1];
-    typedef uint32_t (*Raw2)[PTS2 ? kXCH : 1];
-    __shared__ __align__(16) uint64_t xsig[LAB ? 2 : 1][LAB ? kXCH : 1];   // signatures of the scored chunk
-    __shared__ __align__(16) float xsc[F8 ? 2 : 1][F8 ? kXCH : 1];         // FP8 scales of the scored chunk
+    constexpr int PRE = APPROX ? 2 : 4;            // per-point inputs per row (approximate scores: no error norms)
+    constexpr int GR = kXG * kXCH;                 // rows per step
+    // the two row buffers: distinct arrays, so that the compiler can tell
+    // the reads of one from the direct loads into the other
+    __shared__ __align__(16) uint8_t xb0[GR * ROWB];
+    __shared__ __align__(16) uint8_t xb1[GR * ROWB];
+    __shared__ __align__(16) float rw0[PRE][GR];   // the per-point inputs of each buffer's rows
+    __shared__ __align__(16) float rw1[PRE][GR];
+    // label signatures (two words each), FP8 scales
+    __shared__ __align__(16) uint32_t rg0[LAB ? 2 * GR : 1];
+    __shared__ __align__(16) uint32_t rg1[LAB ? 2 * GR : 1];
+    __shared__ __align__(16) float rs0[F8 ? GR : 1];
+    __shared__ __align__(16) float rs1[F8 ? GR : 1];
+    __shared__ __align__(16) uint64_t xsig[LAB ? 2 : 1][LAB ? GR : 1];   // signatures of the scored rows
+    __shared__ __align__(16) float xsc[F8 ? 2 : 1][F8 ? GR : 1];         // FP8 scales of the scored rows
     // seed pass: the label slots of narrow rows (8 of them), beside the rows of each buffer
     constexpr bool SLOTS = SEED && LAB;
-    __shared__ __align__(16) uint16_t xl0[SLOTS ? kXCH * kMaxLabels : 1];
-    __shared__ __align__(16) uint16_t xl1[SLOTS ? kXCH * kMaxLabels : 1];
-    __shared__ __align__(16) uint16_t xl2[SLOTS ? kXCH * kMaxLabels : 1];
-    __shared__ __align__(16) uint16_t xl3[SLOTS ? kXCH * kMaxLabels : 1];
-    __shared__ __align__(16) QDesc qds[LAB ? kXQB : 1];                    // the tile's filter descriptors
-    __shared__ __align__(16) uint32_t xw[2][kXCH];
-    __shared__ __align__(16) float xn[2][kXCH];
-    __shared__ uint32_t xsum[2][2];   // AND and OR of each point slot's packed words (the chunk's rows)
-    __shared__ uint32_t ring[kXW][SEED ? 2 : 3][kXRing];
-    __shared__ int32_t dhist[kXW][kXQ];   // (before the pipeline starts: also the tile's maxima, below)
+    __shared__ __align__(16) uint16_t xl0[SLOTS ? GR * kMaxLabels : 1];
+    __shared__ __align__(16) uint16_t xl1[SLOTS ? GR * kMaxLabels : 1];
+    __shared__ __align__(16) uint4 qlab[SLOTS ? kXQB : 1];   // the tile's query labels (8 of 16 bits)
+    __shared__ __align__(16) uint32_t xw[2][GR];
+    __shared__ __align__(16) float xn[2][GR];
+    __shared__ uint32_t xsum[2][kXG][2];   // AND and OR of each point slot's packed words (the chunk's rows)
+    __shared__ uint32_t ring[SEED ? 1 : kXW][2][SEED ? 1 : kXRing];
+    __shared__ uint8_t rrow[SEED ? 1 : kXW][SEED ? 1 : kXRing];
+    __shared__ int32_t dhist[SEED ? 1 : kXW][kXQ];   // (before the pipeline starts: also the tile's maxima, below)
     __shared__ int32_t scnt[COUNT ? kXQB : 1];   // (only the counting mode: the modes used per search keep 4 workgroups per CU)
     // the tile prologue's per-wave maxima share the drain histograms' storage:
     // every read of them completes before the pipeline's first barrier, and
@@ -138,6 +164,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     const bool has_dense = A.words != nullptr;
     const bool has_lab = LAB && A.sigs != nullptr;
     const bool narrow = SLOTS && has_lab && A.lslots == kMaxLabels;
+    const int nfree = has_lab && A.wbits <= 24 ? 32 - A.wbits : 0;   // (fewer than 8 bits refuse little)
     const bool l2 = A.metric == 0;
     const float qnan = __builtin_nanf("");
     const float inf = __builtin_huge_valf();
@@ -150,6 +177,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     uint32_t my_sel = 0, my_mask = 0, my_val = 1;   // a lane without a query never matches
     float my_tf = qnan, qa = 0.0f, qb = 0.0f;
     uint64_t my_tk = ~0ull;   // seed: the shared bound key at the tile's start
+    int32_t my_nlab = 0;      // seed: the query's label constraints
     uint64_t my_lsig = 0;     // signature bits of the query's label constraints
     bool my_or = false;       // the query is a disjunction: its terms' dense fields and signatures
     uint32_t tm[DISJ ? kMaxTerms : 1], tv[DISJ ? kMaxTerms : 1];
@@ -167,11 +195,18 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         my_sel = A.esel ? A.esel[dsc.y + qi] : A.sel[my_slot];   // (in entry order: one coalesced read)
         if constexpr (LAB) {
             const QDesc qd = A.qd[my_qq];
-            my_mask = qd.dmask;
-            my_val = qd.dval;
+            const uint32_t fold = fold_sig(qd.lsig, A.wbits, nfree);
+            my_mask = qd.dmask | fold;
+            my_val = qd.dval | fold;
             my_lsig = qd.lsig;
             my_or = DISJ && (qd.flags & kQOr) != 0;
-            if (g == 0) qds[qi] = qd;   // (read by this wave only)
+            if constexpr (SLOTS) {
+                my_nlab = qd.nlab;
+                const uint16_t *l = qd.lab;   // (read by this wave only)
+                if (g == 0)
+                    qlab[qi] = make_uint4(l[0] | (uint32_t)l[1] << 16, l[2] | (uint32_t)l[3] << 16,
+                                          l[4] | (uint32_t)l[5] << 16, l[6] | (uint32_t)l[7] << 16);
+            }
             if (DISJ && my_or) {
 #pragma unroll
                 for (int i = 0; i < kMaxTerms; i++) {
@@ -216,10 +251,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         lvw[w] = lv;
     }
     if constexpr (COUNT) {
-        if (w == 0) {
-            scnt[lane] = 0;
-            scnt[lane + 64] = 0;
-        }
+        if (w < kXQB / 64) scnt[t] = 0;
     }
     // level bounds, one per lane: lane j holds the start of level j, lane
     // h + 1 the end of the partition (read out by lane index, no memory wait)
@@ -248,116 +280,121 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     // power of two and 2s + g = 2s | g)
     const uint32_t xo = (uint32_t)(c32 * ROWB + 16 * (g ^ ((c32 / RPL) & SWZ)));
 
-    // chunk cursors (wave-uniform): level j, first row c0, end of the level;
-    // past the last level j = h + 1
-    auto next_level = [&](int &j, int32_t &c0, int32_t &end) {
-        const uint32_t rest = lv >> (j + 1);   // j + 1 <= h + 1 <= 16
-        if (!rest) {
-            j = h + 1;
-            return;
-        }
-        j += 1 + __builtin_ctz(rest);
-        c0 = __builtin_amdgcn_readlane(spv, j);
-        end = __builtin_amdgcn_readlane(spv, j + 1);
+    // The tile's chunks: each selected level in steps of kXCH rows, numbered
+    // through; with several shares this one's are share, share + nshare, ...
+    // Lane L keeps chunk cb + L (first row; level | rows << 8, or 0 past the
+    // last), laid out 64 at a time by all lanes at once: a step reads its
+    // chunks out by lane index and runs no cursor of its own.
+    int32_t ccnt = lane <= h && ((lv >> lane) & 1u) ? (spn - spv + kXCH - 1) / kXCH : 0;
+    const int32_t ccum = wave_incl_scan(ccnt);
+    int cb = 0;
+    int32_t vc0 = 0;
+    uint32_t vjc = 0;
+    auto plan = [&](int base) {
+        cb = base;
+        const int x = share + nshare * (base + lane);
+        int j = 0;
+        for (int e = 0; e <= h; e++) j += __builtin_amdgcn_readlane(ccum, e) <= x ? 1 : 0;
+        const int jj = min(j, h);
+        const int c0 = __shfl(spv, jj, 64) + kXCH * (x - __shfl(ccum - ccnt, jj, 64));
+        const int end = __shfl(spn, jj, 64);
+        vc0 = c0;
+        vjc = j <= h ? (uint32_t)(j | min(kXCH, end - c0) << 8) : 0u;
     };
-    auto advance1 = [&](int &j, int32_t &c0, int32_t &end) {
-        c0 += kXCH;
-        if (c0 >= end) next_level(j, c0, end);
-    };
-    auto advance = [&](int &j, int32_t &c0, int32_t &end) {
-        advance1(j, c0, end);
-        for (int i = 1; i < nshare; i++) advance1(j, c0, end);
-    };
+    auto chunk0 = [&](int x) -> int32_t { return __builtin_amdgcn_readlane(vc0, x - cb); };
+    auto chunkj = [&](int x) -> uint32_t { return __builtin_amdgcn_readlane(vjc, x - cb); };
 
-    // Staging.  Every wave issues the same loads per chunk (UPW row loads
-    // and one or two per-point loads), always, so that one wait count holds for all
-    // waves and every path (a missing chunk loads row 0 into the unused
-    // buffer instead).  Row load i, lane L fills tile bytes 1024 i + 16 L:
-    // row (64 i + L) / V16, piece (64 i + L) % V16, which holds global piece
-    // piece ^ swizzle of the row; rows past the level's end load its last row
-    // and are masked by a NaN point term; loads past NDMA (short rows) repeat
-    // load i - NDMA.  Per-point load of wave w, lane L: input w (squared
-    // norm, error norms, packed dense word) of row c0 + min(L, cn - 1), L < 32;
-    // second load: wave 0 the FP8 scales alike, the other waves (or all) the
-    // signatures, lane L word L % 2 of row c0 + min(L / 2, cn - 1) (the waves
-    // write the same values).
+    // Staging of a step's kXG chunks.  Row load i (1 KB), lane L fills bytes
+    // 1024 i + 16 L of the buffer: row (64 i + L) / V16, piece (64 i + L) %
+    // V16, which holds global piece piece ^ swizzle of the row; rows past the
+    // level's end load its last row and are masked by a NaN point term.
     uint32_t voff[UPW];
     int vrow[UPW];
 #pragma unroll
     for (int u = 0; u < UPW; u++) {
-        const int i = (w + kXW * u) % NDMA;
-        const int slot = 64 * i + lane;
+        const int slot = 64 * ((w + kXW * u) % NDMA) + lane;
         const int row = slot / V16;
         vrow[u] = row;
         voff[u] = (uint32_t)(row * ROWB + 16 * ((slot % V16) ^ ((row / RPL) & SWZ)));
     }
-    constexpr int OPC = UPW + 1 + (PTS2 ? 1 : 0) + (SLOTS ? 1 : 0);   // loads per wave per chunk
+    // per-point loads: wave w input w % 4 (squared norm, error norms, packed
+    // dense word) of the chunks 2 (w / 4) and 2 (w / 4) + 1, 32 lanes each;
+    // the FP8 scales alike by the waves from kXG on, the signatures of chunk w
+    // by the first kXG waves, lane L word L % 2 of row L / 2
     const uint32_t *wsrc = has_dense ? A.words : reinterpret_cast<const uint32_t *>(A.xnorm);
-    const float *psrc = w == 0   ? A.xnorm
-                        : w == 1 ? A.lerr
-                        : w == 2 ? A.lnrm
-                                 : reinterpret_cast<const float *>(wsrc);
-    // (seed pass with labels: also the slots of rows 8w..8w+7, 16 bytes each;
-    // wide rows load the start of the copy in their place)
-    auto fetch_rows = [&](bool real, int32_t c0, int cn, uint8_t *dst, uint16_t *sdst) {
-        const uint8_t *base = real ? A.lvecs + (int64_t)c0 * ROWB : A.lvecs;
+    const float *psrc = (w & 3) == 0   ? A.xnorm
+                        : (w & 3) == 1 ? A.lerr
+                        : (w & 3) == 2 ? A.lnrm
+                                       : reinterpret_cast<const float *>(wsrc);
+    auto fetch_rows = [&](int x, uint8_t *dst, uint16_t *sdst) {   // of chunks x, x + 1, ...
 #pragma unroll
         for (int u = 0; u < UPW; u++) {
-            const int i = (w + kXW * u) % NDMA;
-            uint32_t off = real ? voff[u] : 0u;
-            if (real && cn < kXCH) off -= (uint32_t)(max(vrow[u] - (cn - 1), 0) * ROWB);
-            __builtin_amdgcn_global_load_lds(base + off, (__attribute__((address_space(3))) void *)(dst + 1024 * i), 16,
-                                             0, 0);
+            const int i = w + kXW * u;
+            if (i >= kXG * NDMA) break;
+            const uint32_t jc = chunkj(x + i / NDMA);
+            if (!jc) break;
+            const int cn = (int)(jc >> 8);
+            uint32_t off = voff[u];
+            if (cn < kXCH) off -= (uint32_t)(max(vrow[u] - (cn - 1), 0) * ROWB);
+            __builtin_amdgcn_global_load_lds(A.lvecs + (int64_t)chunk0(x + i / NDMA) * ROWB + off,
+                                             (__attribute__((address_space(3))) void *)(dst + 1024 * i), 16, 0, 0);
         }
-        if constexpr (SLOTS) {
-            if (lane < 8) {
-                const int64_t row = c0 + min(8 * w + lane, cn - 1);
-                const void *src = real && narrow ? (const void *)(A.slots + row * kMaxLabels) : (const void *)A.lvecs;
-                __builtin_amdgcn_global_load_lds(
-                    src, (__attribute__((address_space(3))) void *)(sdst + 8 * w * kMaxLabels), 16, 0, 0);
+        if constexpr (SLOTS) {   // the label slots of narrow rows: 16 rows a wave, 16 bytes each
+            const uint32_t jc = chunkj(x + w / 2);
+            if (narrow && jc && lane < 16) {
+                const int64_t row = chunk0(x + w / 2) + min(16 * (w & 1) + lane, (int)(jc >> 8) - 1);
+                __builtin_amdgcn_global_load_lds(A.slots + row * kMaxLabels,
+                                                 (__attribute__((address_space(3))) void *)(sdst + 16 * w * kMaxLabels),
+                                                 16, 0, 0);
             }
         }
     };
-    auto fetch_points = [&](bool real, int32_t c0, int cn, float (*raw)[kXCH], Raw2 raw2) {
-        // lanes 0..31 (lane L fills raw[w][L]; every wave has them active, so
-        // the load is issued on every path)
-        if (lane < kXCH) {
-            const int64_t row = real ? c0 + min(lane, cn - 1) : 0;
-            __builtin_amdgcn_global_load_lds(psrc + row, (__attribute__((address_space(3))) void *)raw[w], 4, 0, 0);
-        }
-        if constexpr (PTS2) {
-            // wave-uniform: scales (32 lanes, third array), else signatures
-            // (64 lanes, the first two); without labels the FP8 scales from every
-            // wave, or (disjunctions without labels) the norms as a stand-in
-            if (F8 && (w == 0 || !has_lab)) {
-                if (lane < kXCH) {
-                    const int64_t row = real ? c0 + min(lane, cn - 1) : 0;
-                    __builtin_amdgcn_global_load_lds(A.lscale + row, (__attribute__((address_space(3))) void *)raw2[2], 4,
-                                                     0, 0);
-                }
-            } else {
-                const int64_t row = real ? c0 + min(has_lab ? lane >> 1 : lane & 31, cn - 1) : 0;
-                const uint32_t *src = has_lab ? reinterpret_cast<const uint32_t *>(A.sigs) + 2 * row + (lane & 1)
-                                              : reinterpret_cast<const uint32_t *>(A.xnorm) + row;
-                __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)raw2[0], 4, 0, 0);
+    auto fetch_points = [&](int x, float (*raw)[GR], uint32_t *rsig, float *rsc) {
+        const bool scales = F8 && w >= kXG && w < kXG + kXG / 2;
+        // lane L: row L % 32 of chunk x + 2 (w / 4) + L / 32 (the first one's again if there is no second)
+        auto pair_row = [&](int c) -> int64_t {
+            const uint32_t ja = chunkj(c), jb = chunkj(c + 1);
+            const int32_t ra = chunk0(c) + min(c32, (int)(ja >> 8) - 1);
+            const int32_t rb = chunk0(c + 1) + min(c32, (int)(jb >> 8) - 1);
+            return g && jb ? rb : ra;
+        };
+        const int c = x + 2 * (w >> 2);
+        const int in = w & 3;
+        if ((!APPROX || in == 0 || in == 3) && chunkj(c))
+            __builtin_amdgcn_global_load_lds(psrc + pair_row(c),
+                                             (__attribute__((address_space(3))) void *)(raw[min(in, PRE - 1)] + 2 * kXCH * (w >> 2)),
+                                             4, 0, 0);
+        if (scales && chunkj(x + 2 * (w - kXG)))
+            __builtin_amdgcn_global_load_lds(A.lscale + pair_row(x + 2 * (w - kXG)),
+                                             (__attribute__((address_space(3))) void *)(rsc + 2 * kXCH * (w - kXG)), 4, 0, 0);
+        if (LAB && has_lab && w < kXG) {
+            const uint32_t jc = chunkj(x + w);
+            if (jc) {
+                const int64_t row = chunk0(x + w) + min(lane >> 1, (int)(jc >> 8) - 1);
+                __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t *>(A.sigs) + 2 * row + (lane & 1),
+                                                 (__attribute__((address_space(3))) void *)(rsig + 2 * kXCH * w), 4, 0, 0);
             }
         }
     };
-    // the point terms of a chunk whose per-point inputs have landed (one
-    // wave per chunk, in turn)
-    auto point_terms = [&](float (*raw)[kXCH], Raw2 raw2, int cn, int pb) {
-        const float nx = raw[0][c32];
-        const float slack = fmaf(raw[1][c32], qa, raw[2][c32] * qb) * (1.0f + 0x1p-20f);
-        float pt = l2 ? fmaf(-A.eta, nx, fmaf(-2.0f, slack, nx)) : fmaf(-A.eta, nx, -slack);
-        if (!(fabsf(pt) < inf)) pt = -inf;
-        if (APPROX) pt = l2 ? nx : 0.0f;   // approximate keys: the plain point term
+    // the point terms of chunk ci of a step whose per-point inputs have landed
+    // (one wave per chunk)
+    auto point_terms = [&](float (*raw)[GR], const uint32_t *rsig, const float *rsc, const int ci, int cn, int pb) {
+        const int at = kXCH * ci + c32;
+        const float nx = raw[0][at];
+        float pt = l2 ? nx : 0.0f;   // approximate keys: the plain point term
+        if constexpr (!APPROX) {
+            const float slack = fmaf(raw[1][at], qa, raw[2][at] * qb) * (1.0f + 0x1p-20f);
+            pt = l2 ? fmaf(-A.eta, nx, fmaf(-2.0f, slack, nx)) : fmaf(-A.eta, nx, -slack);
+            if (!(fabsf(pt) < inf)) pt = -inf;
+        }
         if constexpr (LAB) {   // (without labels every query's signature, 0, is a subset)
-            reinterpret_cast<uint32_t *>(xsig[pb])[lane] = raw2[lane >> 5][c32];
+            reinterpret_cast<uint32_t *>(xsig[pb])[2 * kXCH * ci + lane] = rsig[2 * kXCH * ci + lane];
         }
-        if constexpr (F8) xsc[pb][c32] = __uint_as_float(raw2[2][c32]);
-        xn[pb][c32] = c32 < cn ? pt : qnan;   // (lanes l and l + 32 write alike)
-        const uint32_t wd = has_dense ? __float_as_uint(raw[3][c32]) : 0u;
-        xw[pb][c32] = wd;
+        if constexpr (F8) xsc[pb][at] = rsc[at];
+        xn[pb][at] = c32 < cn ? pt : qnan;   // (lanes l and l + 32 write alike)
+        uint32_t wd = has_dense ? __float_as_uint(raw[PRE - 1][at]) : 0u;
+        if constexpr (LAB) wd |= fold_sig(((const uint64_t *)rsig)[at], A.wbits, nfree);
+        xw[pb][at] = wd;
         // the chunk's summary for the skip test: AND and OR of its rows'
         // words, reduced inside each 16-lane row by rotations (DPP row_ror
         // 1, 2, 4, 8), then rows 0 and 1 (lanes 0..31 hold the chunk's rows)
@@ -375,20 +412,20 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         const uint32_t sa = (uint32_t)(__builtin_amdgcn_readlane(wa, 0) & __builtin_amdgcn_readlane(wa, 16));
         const uint32_t so = (uint32_t)(__builtin_amdgcn_readlane(wo, 0) | __builtin_amdgcn_readlane(wo, 16));
         if (lane == 0) {
-            xsum[pb][0] = sa;
-            xsum[pb][1] = so;
+            xsum[pb][ci][0] = sa;
+            xsum[pb][ci][1] = so;
         }
     };
 
     // The exact test of a pair's labels: the query's in the point's slots (its
     // dense constraints were tested on the staged words), or each term of a
     // disjunction in full.
-    auto rest_passes = [&](int qj, uint32_t pos) -> bool {
-        const QDesc &qd = qds[kXQ * w + qj];
+    auto rest_passes = [&](int32_t qq, uint32_t pos) -> bool {
+        const QDesc &qd = A.qd[qq];
         const uint64_t sg = A.sigs[pos];
         const uint16_t *sl = A.slots + (int64_t)pos * A.lslots;
         if (DISJ && (qd.flags & kQOr))
-            return query_passes(qd, A.qterms + (int64_t)(ent[kXQ * w + qj] / A.m) * kMaxTerms, has_dense, true,
+            return query_passes(qd, A.qterms + (int64_t)qq * kMaxTerms, has_dense, true,
                                 has_dense ? A.words[pos] : 0u, sg, sl, A.lslots);
         return point_passes(qd, false, true, 0u, sg, sl, A.lslots);
     };
@@ -412,10 +449,10 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
     // 64, appended to their queries' lists when a ballot's pairs would not
     // fit (per-query ranks from an LDS histogram, one returning atomic per
     // query); a query whose list is full is flagged for the rescue pass
-    uint32_t *ring_pos = ring[w][0];
-    uint32_t *ring_row = ring[w][1];
-    uint32_t *ring_key = ring[w][SEED ? 1 : 2];   // the pair's ordered score (not in the seed mode)
-    int32_t *hist = dhist[w];
+    uint32_t *ring_pos = ring[SEED ? 0 : w][0];
+    uint8_t *ring_row = rrow[SEED ? 0 : w];
+    uint32_t *ring_key = ring[SEED ? 0 : w][1];   // the pair's ordered score (not in the seed mode)
+    int32_t *hist = dhist[SEED ? 0 : w];
     int vhead = 0, vtail = 0;
     auto drain = [&](int n) {
         wave_sync();
@@ -425,8 +462,9 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         const int qj = v ? (int)ring_row[slot] : 0;
         const uint32_t pkey = v ? ring_key[slot] : 0u;
         vtail += n;
+        const int32_t qq = __shfl(my_qq, qj, 64);
         if constexpr (LAB) {
-            if (v && has_lab) v = rest_passes(qj, pos);   // (dense terms only: tested)
+            if (v && has_lab) v = rest_passes(qq, pos);   // (dense terms only: tested)
         }
         if (lane < kXQ) hist[lane] = 0;
         wave_sync();
@@ -436,21 +474,16 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         int base = 0;
         if (cnt > 0) base = atomicAdd(A.dcnt + my_qq, cnt);
         const int at = __shfl(base, qj, 64) + rank;
-        const int32_t qq = __shfl(my_qq, qj, 64);
         if (v && at < A.dcap) A.dpos[(int64_t)qq * A.dcap + at] = ((uint64_t)pkey << 32) | pos;
         if (v && at >= A.dcap) A.oflow[qq] = 1;
     };
 
-    // ---- pipeline.  Fetch F_c = rows of chunk c into buffer c % 4 and the
-    // per-point inputs of chunk c + 1 into slot (c + 1) % 4.  Step k waits
-    // for F_k (two later fetches may stay in flight), passes the barrier,
-    // issues F_{k+3}, lets wave k % 4 turn the inputs of chunk k + 1 into its
-    // point terms, and scores chunk k.
-    int cj = -1;
-    int32_t cc0 = 0, cend = 0;
-    next_level(cj, cc0, cend);
-    for (int i = 0; i < share; i++) advance1(cj, cc0, cend);
-    if (cj > h) {   // nothing to scan
+    // ---- pipeline.  Step k scores group k (kXG chunks): it waits for the
+    // group's rows (fetched during step k - 1), passes the barrier, fetches the
+    // rows of group k + 1 and the per-point inputs of group k + 2 and has one
+    // wave per chunk turn the inputs of group k + 1 into point terms.
+    plan(0);
+    if (!chunkj(0)) {   // nothing to scan
         if (SEED && g == 0 && own) {
             if (share == 0) A.pcnt[my_slot] = nshare > 1 ? 2 * MH * nshare : 0;
             if (nshare > 1)
@@ -458,51 +491,26 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         }
         return;
     }
-    // fetch cursor (chunk of the rows of the next fetch) and the chunk after it
-    int fj = cj, rj = cj;
-    int32_t fc0 = cc0, fend = cend, rc0 = cc0, rend = cend;
-    advance(rj, rc0, rend);
-    auto fetch_next = [&](uint8_t *dst, uint16_t *sdst, float (*raw)[kXCH], Raw2 raw2) {
-        const bool fr = fj <= h, rr = rj <= h;
-        fetch_rows(fr, fc0, fr ? min(kXCH, fend - fc0) : 1, dst, sdst);
-        fetch_points(rr, rc0, rr ? min(kXCH, rend - rc0) : 1, raw, raw2);
-        if (fr) advance(fj, fc0, fend);
-        if (rr) advance(rj, rc0, rend);
-    };
-    fetch_points(true, cc0, min(kXCH, cend - cc0), rw0, rg0);   // the inputs of chunk 0
-    fetch_next(xb0, xl0, rw1, rg1);
-    fetch_next(xb1, xl1, rw2, rg2);
-    fetch_next(xb2, xl2, rw3, rg3);
-    // the first three chunks have landed on every wave (waiting for all of
-    // them lets the compiler's own wait tracking enter the loop with nothing
-    // in flight)
-    __builtin_amdgcn_s_waitcnt(0xC07F & 0x0F70);   // vmcnt(0) lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    if (w == 0) point_terms(rw0, rg0, min(kXCH, cend - cc0), 0);
+    int x = 0;   // first chunk of the scored group
+    fetch_points(0, rw0, rg0, rs0);
+    fetch_rows(0, xb0, xl0);
+    fetch_points(kXG, rw1, rg1, rs1);
+    // (waiting for all of them lets the compiler's own wait tracking enter the
+    // loop with nothing in flight)
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    lds_barrier();
+    if (w < kXG && chunkj(w)) point_terms(rw0, rg0, rs0, w, (int)(chunkj(w) >> 8), 0);
     int lj = -1;
     float tfj = qnan;
     uint64_t lst[SEED ? MH : 1];   // seed: the lane's best keys, ascending (~0: empty)
 #pragma unroll
     for (int i = 0; i < (SEED ? MH : 1); i++) lst[i] = ~0ull;
 
-    // Chunk k from buffer `cur` (point arrays `pb`); `nraw` holds the inputs
-    // of chunk k + 1, whose point terms wave `ptw` (k % 4) computes; F_{k+3}
-    // goes to `nxt` and `fraw`.  Returns whether another chunk follows.
-    auto step = [&](const uint8_t *cur, uint8_t *nxt, const uint16_t *scur, uint16_t *snxt, const int pb, float (*nraw)[kXCH], Raw2 nraw2,
-                    float (*fraw)[kXCH], Raw2 fraw2, const int ptw) -> bool {
-        const int j = cj;
-        const int32_t c0 = cc0;
-        const int cn = min(kXCH, cend - c0);
-        // F_k has landed once at most the two later fetches are outstanding
-        // (stores and atomics issued since only make the wait stricter); the
-        // point terms wave 0 wrote are complete
-        __builtin_amdgcn_s_waitcnt(0xC07F & (0x0F70 | ((2 * OPC) & 15) | (((2 * OPC) >> 4) << 14)));
-        __builtin_amdgcn_s_barrier();
-        advance(cj, cc0, cend);
-        const bool more = cj <= h;
-        fetch_next(nxt, snxt, fraw, fraw2);
-        if (w == ptw && more) point_terms(nraw, nraw2, min(kXCH, cend - cc0), pb ^ 1);
-        if (kXQ * w >= nqt) return more;   // a wave without queries (small batches) only stages
+    // One chunk (ci of group buffer `pb`): its products and tests.
+    auto score = [&](const uint8_t *cur, const uint16_t *scur, const int pb, const int ci, const int32_t c0, const int j,
+                     const int cn) {
+        cur += ci * kXCH * ROWB;
+        const int rb0 = ci * kXCH;
         {
             // A row passes (w & M) == V only if every bit of V is set in the
             // OR of the chunk's words and every other bit of M is clear in
@@ -510,7 +518,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
             // chunk, its products and tests are skipped (the queries of a
             // wave share constraints and a sub-partition's rows are grouped
             // by their values, so this is common)
-            const uint32_t wa = xsum[pb][0], wo = xsum[pb][1];
+            const uint32_t wa = xsum[pb][ci][0], wo = xsum[pb][ci][1];
             uint32_t miss = (my_val & ~wo) | (~my_val & my_mask & wa) | (((my_sel >> j) & 1u) ^ 1u);
             if (any_or) {   // a disjunction: some term may pass
                 bool some = !my_or;
@@ -519,7 +527,24 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
                     some |= ((tv[i] & ~wo) | (~tv[i] & tm[i] & wa)) == 0u;
                 if (!some) miss = 1u;
             }
-            if (!__builtin_amdgcn_ballot_w64(miss == 0u)) return more;
+            if (!__builtin_amdgcn_ballot_w64(miss == 0u)) return;
+            if constexpr (!LAB) {
+                // then each row against each query, still before the products:
+                // the least difference is 0 where a row passes.  (With labels
+                // too few blocks go without a pass: 2.60 against 2.42 ms.)
+                uint32_t diff = ~0u;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; q4++) {
+                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + 8 * q4 + 4 * g]);
+                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) diff = min(diff, (wv[e] & my_mask) ^ my_val);
+                }
+                if (!__builtin_amdgcn_ballot_w64((miss | diff) == 0u)) return;
+                // (the words are read again below: kept in registers across
+                // the products they spilled others, 2.49 ms against 1.61)
+                wave_sync();
+            }
         }
 
         f32x16 acc = {};
@@ -534,7 +559,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
         if constexpr (F8) {   // both scales
 #pragma unroll
             for (int q4 = 0; q4 < 4; q4++) {
-                const float4 ps = *reinterpret_cast<const float4 *>(&xsc[pb][8 * q4 + 4 * g]);
+                const float4 ps = *reinterpret_cast<const float4 *>(&xsc[pb][rb0 + 8 * q4 + 4 * g]);
                 const float sv[4] = {ps.x, ps.y, ps.z, ps.w};
 #pragma unroll
                 for (int e = 0; e < 4; e++) acc[4 * q4 + e] = acc[4 * q4 + e] * sv[e] * my_qs;
@@ -560,119 +585,207 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(FILT ?
                 }
                 tfj = bound_score(lst[MH - 1] < my_tk ? lst[MH - 1] : my_tk);
             };
-            uint32_t cand = 0;   // label variant: elements that passed the score, dense and signature tests
+            if constexpr (!LAB && MH > 1) {   // several keys a lane: element by element
 #pragma unroll
-            for (int q4 = 0; q4 < 4; q4++) {
-                const int rb = 8 * q4 + 4 * g;
-                const float4 pn = *reinterpret_cast<const float4 *>(&xn[pb][rb]);
-                const float pv[4] = {pn.x, pn.y, pn.z, pn.w};
-                uint64_t hit[4];
+                for (int q4 = 0; q4 < 4; q4++) {
+                    const int rb = 8 * q4 + 4 * g;
+                    const float4 pn = *reinterpret_cast<const float4 *>(&xn[pb][rb0 + rb]);
+                    const float pv[4] = {pn.x, pn.y, pn.z, pn.w};
+                    uint64_t hit[4];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    acc[4 * q4 + e] = fmaf(cm, acc[4 * q4 + e], pv[e]);
-                    hit[e] = __builtin_amdgcn_ballot_w64(acc[4 * q4 + e] <= tfj);
-                }
-                if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
-                const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb]);
-                const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
+                    for (int e = 0; e < 4; e++) {
+                        acc[4 * q4 + e] = fmaf(cm, acc[4 * q4 + e], pv[e]);
+                        hit[e] = __builtin_amdgcn_ballot_w64(acc[4 * q4 + e] <= tfj);
+                    }
+                    if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
+                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + rb]);
+                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    if (!((hit[e] >> lane) & 1ull) || (wv[e] & my_mask) != my_val) continue;
-                    if constexpr (LAB) {
-                        if (staged_passes(wv[e], !DISJ || has_lab ? xsig[pb][rb + e] : ~0ull)) cand |= 1u << (4 * q4 + e);
-                    } else {
+                    for (int e = 0; e < 4; e++) {
+                        if (!((hit[e] >> lane) & 1ull) || (wv[e] & my_mask) != my_val) continue;
                         const uint64_t key = ((uint64_t)f2ord(canon0(acc[4 * q4 + e])) << 32) | (uint32_t)(c0 + rb + e);
                         if (key < lst[MH - 1]) offer(key);
                     }
                 }
+                return;
             }
-            if constexpr (LAB) {   // their labels (or terms), in one copy of the code
-                while (cand) {
-                    const int r = __builtin_ctz(cand);
-                    cand &= cand - 1u;
-                    float sc = acc[0];
+            // the elements at or below the bound whose packed words pass, as a mask
+            uint32_t cand = 0;
+            float least = inf;   // one key a lane: the least passing score
 #pragma unroll
-                    for (int e = 1; e < 16; e++) sc = r == e ? acc[e] : sc;
-                    const uint32_t pos = (uint32_t)(c0 + 8 * (r >> 2) + 4 * g + (r & 3));
-                    const uint64_t key = ((uint64_t)f2ord(canon0(sc)) << 32) | pos;
-                    if (!(key < lst[MH - 1])) continue;
-                    bool ok;
-                    if (!has_lab) {
-                        ok = true;   // (dense terms only: tested)
-                    } else if (narrow && !my_or) {   // the labels against the staged slots
-                        const uint16_t *sl = scur + (pos - c0) * kMaxLabels;
-                        const QDesc &qd = qds[kXQ * w + c32];
-                        ok = true;
-                        for (int i = 0; i < qd.nlab; i++) ok &= slots_hold(sl, kMaxLabels, qd.lab[i]);
-                    } else {
-                        ok = rest_passes(c32, pos);
-                    }
-                    if (ok) offer(key);
+            for (int q4 = 0; q4 < 4; q4++) {
+                const int rb = rb0 + 8 * q4 + 4 * g;
+                const float4 pn = *reinterpret_cast<const float4 *>(&xn[pb][rb]);
+                const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb]);
+                const float pv[4] = {pn.x, pn.y, pn.z, pn.w};
+                const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const float sc = fmaf(cm, acc[4 * q4 + e], pv[e]);
+                    acc[4 * q4 + e] = sc;
+                    const bool in = sc <= tfj && (wv[e] & my_mask) == my_val;
+                    cand |= in ? 1u << (4 * q4 + e) : 0u;
+                    if (!LAB && MH == 1) least = fminf(least, in ? sc : inf);
                 }
+            }
+            if constexpr (LAB && !DISJ) {
+                // the signatures of all sixteen at once: until a lane's list is
+                // full every score passes, and one at a time the lane with
+                // most candidates keeps the wave waiting
+                uint32_t sok = 0;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; q4++) {
+                    const uint64_t *sg = &xsig[pb][rb0 + 8 * q4 + 4 * g];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) sok |= (my_lsig & ~sg[e]) == 0 ? 1u << (4 * q4 + e) : 0u;
+                }
+                cand &= sok;
+            } else if constexpr (LAB) {   // the signatures and the terms of disjunctions
+                for (uint32_t c = cand; c; c &= c - 1u) {
+                    const int i = __builtin_ctz(c), row = rb0 + 8 * (i >> 2) + 4 * g + (i & 3);
+                    if (!staged_passes(DISJ ? xw[pb][row] : 0u, !DISJ || has_lab ? xsig[pb][row] : ~0ull))
+                        cand &= ~(1u << i);
+                }
+            } else if constexpr (MH == 1) {   // only the first of the least elements can enter
+                uint32_t first = 0;
+#pragma unroll
+                for (int e = 0; e < 16; e++) first |= acc[e] == least ? 1u << e : 0u;
+                cand &= first;
+                cand &= 0u - cand;
+            }
+            while (cand) {
+                const int r = __builtin_ctz(cand);
+                cand &= cand - 1u;
+                float sc = acc[0];
+#pragma unroll
+                for (int e = 1; e < 16; e++) sc = r == e ? acc[e] : sc;
+                if (!LAB && MH == 1) sc = least;
+                const uint32_t pos = (uint32_t)(c0 + 8 * (r >> 2) + 4 * g + (r & 3));
+                const uint64_t key = ((uint64_t)f2ord(canon0(sc)) << 32) | pos;
+                if (!(key < lst[MH - 1])) continue;
+                if constexpr (LAB) {
+                    if (has_lab && narrow && !my_or) {   // the labels against the staged slots
+                        const uint4 sl = *reinterpret_cast<const uint4 *>(scur + (rb0 + pos - c0) * kMaxLabels);
+                        uint4 ql = qlab[kXQ * w + c32];
+                        bool ok = true;
+                        for (int i = 0; i < my_nlab; i++) {   // (two labels a word)
+                            const uint32_t v = (ql.x & 0xFFFFu) * 0x10001u;
+                            const uint32_t x0 = sl.x ^ v, x1 = sl.y ^ v, x2 = sl.z ^ v, x3 = sl.w ^ v;
+                            const uint32_t lo = min(min(x0 & 0xFFFFu, x1 & 0xFFFFu), min(x2 & 0xFFFFu, x3 & 0xFFFFu));
+                            const uint32_t hi = min(min(x0 >> 16, x1 >> 16), min(x2 >> 16, x3 >> 16));
+                            ok &= min(lo, hi) == 0u;
+                            ql.x = ql.x >> 16 | ql.y << 16;
+                            ql.y = ql.y >> 16 | ql.z << 16;
+                            ql.z = ql.z >> 16 | ql.w << 16;
+                            ql.w >>= 16;
+                        }
+                        if (!ok) continue;
+                    } else if (has_lab && !rest_passes(my_qq, pos)) {   // (dense terms only: tested)
+                        continue;
+                    }
+                }
+                offer(key);
             }
         } else {
             if (j != lj) {   // level changed: the query's bound if it selects the level, NaN if not
                 lj = j;
                 tfj = ((my_sel >> j) & 1u) ? my_tf : qnan;
             }
-            const bool sj = (my_sel >> j) & 1u;
-            // point terms of the next group read while this one is scored
-            float4 pnx = *reinterpret_cast<const float4 *>(&xn[pb][4 * g]);
+            if constexpr (COUNT) {   // survivors of the exact filter (statistics only)
+                int c = 0;
+                if ((my_sel >> j) & 1u)
+                    for (int i = 0; i < 16; i++) {
+                        const int row = 8 * (i >> 2) + 4 * g + (i & 3);
+                        c += (row < cn && (xw[pb][rb0 + row] & my_mask) == my_val) ? 1 : 0;
+                    }
+                if (c) atomicAdd(&scnt[qi], c);
+            }
+            // The elements whose score passes the bound and whose packed word
+            // passes the query's test, as a mask.  With labels nearly every
+            // block has some; without, whether any score passes is found first.
+            uint32_t cand = 0;
+            float best = inf;   // (a NaN, of a masked row, is never the least)
 #pragma unroll
             for (int q4 = 0; q4 < 4; q4++) {   // points 8 q4 + 4 g + e of the chunk, e < 4
-                const int rb = 8 * q4 + 4 * g;
-                const float4 pn = pnx;
-                if (q4 < 3) pnx = *reinterpret_cast<const float4 *>(&xn[pb][rb + 8]);
+                const float4 pn = *reinterpret_cast<const float4 *>(&xn[pb][rb0 + 8 * q4 + 4 * g]);
+                const uint4 pw = LAB ? *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + 8 * q4 + 4 * g]) : uint4{};
                 const float pv[4] = {pn.x, pn.y, pn.z, pn.w};
-                uint64_t hit[4];
-                float sc[4];   // the element test's scores (deferred with their pairs)
+                const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    sc[e] = fmaf(cm, acc[4 * q4 + e], pv[e]);
-                    hit[e] = __builtin_amdgcn_ballot_w64(sc[e] <= tfj);
-                }
-                if constexpr (COUNT) {   // survivors of the exact filter (statistics only)
-                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb]);
-                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
-                    int c = 0;
-#pragma unroll
-                    for (int e = 0; e < 4; e++) c += (sj && rb + e < cn && (wv[e] & my_mask) == my_val) ? 1 : 0;
-                    if (c) atomicAdd(&scnt[qi], c);
-                }
-                if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
-                {   // the packed dense test where a score passed
-                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb]);
-                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
-#pragma unroll
-                    for (int e = 0; e < 4; e++) hit[e] &= __builtin_amdgcn_ballot_w64((wv[e] & my_mask) == my_val);
-                    if constexpr (LAB) {   // then the label signatures
-                        if (!(hit[0] | hit[1] | hit[2] | hit[3])) continue;
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-                            hit[e] &= __builtin_amdgcn_ballot_w64(
-                                staged_passes(wv[e], !DISJ || has_lab ? xsig[pb][rb + e] : ~0ull));
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const uint64_t hm = hit[e];
-                    if (!hm) continue;
-                    const int n = __popcll(hm);   // at most 64
-                    if (vhead - vtail + n > kXRing) drain(vhead - vtail);
-                    if ((hm >> lane) & 1ull) {
-                        const int sl = (vhead + __popcll(hm & lanemask_lt())) & (kXRing - 1);
-                        ring_pos[sl] = (uint32_t)(c0 + rb + e);
-                        ring_row[sl] = (uint32_t)c32;
-                        ring_key[sl] = f2ord(canon0(sc[e]));
-                    }
-                    vhead += n;
+                for (int e = 0; e < 4; e++) {   // the element test's scores (deferred with their pairs)
+                    const float sc = fmaf(cm, acc[4 * q4 + e], pv[e]);
+                    acc[4 * q4 + e] = sc;
+                    const uint32_t diff = (wv[e] & my_mask) ^ my_val;
+                    if (LAB) cand |= sc <= tfj && diff == 0u ? 1u << (4 * q4 + e) : 0u;
+                    else best = fminf(best, sc);
                 }
             }
+            if (!LAB) {
+                if (!__builtin_amdgcn_ballot_w64(best <= tfj)) return;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; q4++) {
+                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + 8 * q4 + 4 * g]);
+                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        cand |= acc[4 * q4 + e] <= tfj && (wv[e] & my_mask) == my_val ? 1u << (4 * q4 + e) : 0u;
+                }
+            }
+            // then lane by lane the lowest one at a time (few blocks have more
+            // than one pass): the label signatures, and the ring
+            if constexpr (LAB) {
+                for (uint32_t c = cand; c; c &= c - 1u) {
+                    const int i = __builtin_ctz(c), row = rb0 + 8 * (i >> 2) + 4 * g + (i & 3);
+                    if (!staged_passes(DISJ ? xw[pb][row] : 0u, !DISJ || has_lab ? xsig[pb][row] : ~0ull))
+                        cand &= ~(1u << i);
+                }
+            }
+            for (uint64_t hm; (hm = __builtin_amdgcn_ballot_w64(cand != 0u)) != 0;) {
+                const int n = __popcll(hm);   // at most 64
+                if (vhead - vtail + n > kXRing) drain(vhead - vtail);
+                if (cand) {
+                    const int i = __builtin_ctz(cand);
+                    cand &= cand - 1u;
+                    float sc = acc[0];
+#pragma unroll
+                    for (int e = 1; e < 16; e++) sc = i == e ? acc[e] : sc;
+                    const int sl = (vhead + __popcll(hm & lanemask_lt())) & (kXRing - 1);
+                    ring_pos[sl] = (uint32_t)(c0 + 8 * (i >> 2) + 4 * g + (i & 3));
+                    ring_row[sl] = (uint8_t)c32;
+                    ring_key[sl] = f2ord(canon0(sc));
+                }
+                vhead += n;
+            }
         }
-        return more;
     };
-    while (step(xb0, xb3, xl0, xl3, 0, rw1, rg1, rw0, rg0, 0) && step(xb1, xb0, xl1, xl0, 1, rw2, rg2, rw1, rg1, 1) &&
-           step(xb2, xb1, xl2, xl1, 0, rw3, rg3, rw2, rg2, 2) && step(xb3, xb2, xl3, xl2, 1, rw0, rg0, rw3, rg3, 3)) {
+    auto step = [&](const uint8_t *cur, uint8_t *nxt, const uint16_t *scur, uint16_t *snxt, const int pb,
+                    float (*nraw)[GR], const uint32_t *nsig, const float *nsc, float (*fraw)[GR], uint32_t *fsig,
+                    float *fsc) -> bool {
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the group's rows
+        lds_barrier();
+        if (x + 3 * kXG > cb + 64) plan(x);
+        fetch_rows(x + kXG, nxt, snxt);
+        fetch_points(x + 2 * kXG, fraw, fsig, fsc);
+        {
+            const int ci = pb ? w - kXG : w;   // the waves take turns
+            if (ci >= 0 && ci < kXG) {
+                const uint32_t jc = chunkj(x + kXG + ci);
+                if (jc) point_terms(nraw, nsig, nsc, ci, (int)(jc >> 8), pb ^ 1);
+            }
+        }
+        if (kXQ * w < nqt) {   // a wave without queries (small batches) only stages
+#pragma unroll 1
+            for (int i = 0; i < kXG; i++) {
+                const uint32_t jc = chunkj(x + i);
+                if (!jc) break;
+                score(cur, scur, pb, i, chunk0(x + i), (int)(jc & 255u), (int)(jc >> 8));
+            }
+        }
+        x += kXG;
+        return chunkj(x) != 0;
+    };
+    while (step(xb0, xb1, xl0, xl1, 0, rw1, rg1, rs1, rw0, rg0, rs0) &&
+           step(xb1, xb0, xl1, xl0, 1, rw0, rg0, rs0, rw1, rg1, rs1)) {
     }
     if constexpr (SEED) {
         // the slot's list: the keys of half 0, then those of half 1 (2 MH <= r
