@@ -22,8 +22,9 @@
 //    (label slots, terms of disjunctions; global reads) when it drains a wave's
 //    ring of pairs, one pair per lane, so that one round trip to memory serves
 //    up to 64 pairs.
-// What bounds it: the chain of waits of a step, with four waves per SIMD (matrix
-// cores busy 18 % of the time, vector units 36 %).  Before the steps of two
+// What bounds it: the chain of waits of a step, with four waves per SIMD (BF16
+// main pass: matrix cores busy 14 % of the time, vector units about 60 %, 54 %
+// of the wave time waiting).  Before the steps of two
 // chunks, the masks of passing elements (instead of branches per element) and
 // the folded signatures: main pass of 10k queries x 1M x 128 BF16 1.73 ms, now
 // 1.63; 4k queries, labels, 96-d FP8 3.16, now 2.46; 8k queries, dense values
@@ -91,10 +92,11 @@ __device__ inline uint32_t fold_sig(uint64_t sig, int at, int nfree) {
 // (LDS operands, products, tests), so a fourth wave beats the registers it
 // costs: FP8 labels 2.46 against 3.04 ms in the main pass and 0.56 against
 // 0.65 ms in the seed pass although 22 registers spill there, FP16 labels 5.03
-// against 5.47 ms.  Disjunctions (their terms in registers) and seed lists of
-// four keys with labels stay at three.
+// against 5.47 ms.  Disjunctions (their terms in registers), seed lists of
+// four keys with labels and the counting pass (12 registers would spill) stay
+// at three.
 constexpr int x32_waves(int mode, int mh, int filt) {
-    return filt == 2 || (filt == 1 && mode == 2 && mh > 1) ? 3 : 4;
+    return filt == 2 || mode == 1 || (filt == 1 && mode == 2 && mh > 1) ? 3 : 4;
 }
 
 template <int PREC, int NS, int MODE, int MH, int FILT>
@@ -693,12 +695,17 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
             }
             if constexpr (COUNT) {   // survivors of the exact filter (statistics only)
                 int c = 0;
-                if ((my_sel >> j) & 1u)
-                    for (int i = 0; i < 16; i++) {
-                        const int row = 8 * (i >> 2) + 4 * g + (i & 3);
-                        c += (row < cn && (xw[pb][rb0 + row] & my_mask) == my_val) ? 1 : 0;
-                    }
+#pragma unroll
+                for (int q4 = 0; q4 < 4; q4++) {
+                    const int rb = 8 * q4 + 4 * g;
+                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + rb]);
+                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) c += rb + e < cn && (wv[e] & my_mask) == my_val ? 1 : 0;
+                }
+                if (!((my_sel >> j) & 1u)) c = 0;
                 if (c) atomicAdd(&scnt[qi], c);
+                wave_sync();   // (the words are read again below)
             }
             // The elements whose score passes the bound and whose packed word
             // passes the query's test, as a mask.  With labels nearly every

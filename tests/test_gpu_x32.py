@@ -96,3 +96,25 @@ def test_approximate_deferral(caps, orc, case):
         assert np.array_equal(ids[i, :n], perm[cand][o]) and np.all(ids[i, n:] == -1), i
         assert np.array_equal(dist[i, :n], dd[o].astype(np.float32)), i
     ix.close()
+
+
+LONG = [
+    # seed, prec, d, vocabs, label_vocab: partitions of about 3,000 rows, more than the 64 chunks laid out at once
+    (640, "fp8", 32, (), 40),              # signatures folded into 32 bits of the packed word
+    (641, "fp16", 96, (4096, 4096), 40),   # into 8 bits
+    (642, "bf16", 128, (5000, 5000), 40),  # 6 bits left: not folded
+    (643, "bf16", 64, (3,), 0),            # no labels
+]
+
+
+@pytest.mark.parametrize("case", LONG)
+def test_long_partitions(caps, orc, case):
+    seed, prec, d, voc, lv = case
+    w = synth.make_tiny(seed, n=9001, d=d, n_q=290, vocabs=voc, label_vocab=lv, b=3, h=2, cmin=0, cmax=2)
+    oi = orc.build_from_workload(w, iters=1)
+    ix = caps.Index.from_workload(w, kmeans_iters=1, precision=prec)
+    r = orc.search(oi, w.q, w.con_off, w.con_attr, w.con_val, 10, 3)
+    got = ix.search(w.q, w.con_off, w.con_attr, w.con_val, 10, 3)
+    assert np.array_equal(got[0].cpu().numpy(), r.ids)
+    assert np.array_equal(got[1].cpu().numpy().view(np.uint32), r.dist.view(np.uint32))
+    ix.close()
