@@ -535,14 +535,20 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
                 // the least difference is 0 where a row passes.  (With labels
                 // too few blocks go without a pass: 2.60 against 2.42 ms.)
                 uint32_t diff = ~0u;
+                int cnt = 0;   // survivors of the exact filter (the counting mode)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; q4++) {
                     const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + 8 * q4 + 4 * g]);
                     const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
 #pragma unroll
-                    for (int e = 0; e < 4; e++) diff = min(diff, (wv[e] & my_mask) ^ my_val);
+                    for (int e = 0; e < 4; e++) {
+                        const uint32_t x = (wv[e] & my_mask) ^ my_val;
+                        diff = min(diff, x);
+                        if (COUNT) cnt += 8 * q4 + 4 * g + e < cn && x == 0u ? 1 : 0;
+                    }
                 }
                 if (!__builtin_amdgcn_ballot_w64((miss | diff) == 0u)) return;
+                if (COUNT && ((my_sel >> j) & 1u) && cnt) atomicAdd(&scnt[qi], cnt);
                 // (the words are read again below: kept in registers across
                 // the products they spilled others, 2.49 ms against 1.61)
                 wave_sync();
@@ -692,20 +698,6 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
             if (j != lj) {   // level changed: the query's bound if it selects the level, NaN if not
                 lj = j;
                 tfj = ((my_sel >> j) & 1u) ? my_tf : qnan;
-            }
-            if constexpr (COUNT) {   // survivors of the exact filter (statistics only)
-                int c = 0;
-#pragma unroll
-                for (int q4 = 0; q4 < 4; q4++) {
-                    const int rb = 8 * q4 + 4 * g;
-                    const uint4 pw = *reinterpret_cast<const uint4 *>(&xw[pb][rb0 + rb]);
-                    const uint32_t wv[4] = {pw.x, pw.y, pw.z, pw.w};
-#pragma unroll
-                    for (int e = 0; e < 4; e++) c += rb + e < cn && (wv[e] & my_mask) == my_val ? 1 : 0;
-                }
-                if (!((my_sel >> j) & 1u)) c = 0;
-                if (c) atomicAdd(&scnt[qi], c);
-                wave_sync();   // (the words are read again below)
             }
             // The elements whose score passes the bound and whose packed word
             // passes the query's test, as a mask.  With labels nearly every
