@@ -61,11 +61,11 @@ FLUSH_BYTES = 512 << 20
 # factor 1.00).  Valid only for the kernel sources they were taken on (SHA-256 of the three
 # files below) and that workload; otherwise the line reports null.
 MAIN_PASS_TRAFFIC = {
-    "sources_sha256": "139280d2db82017a0defe899b3d63cc66878e92f93dbae2b9c2b51a77b1957bf",
+    "sources_sha256": "e33a52f67b2fc1d60130fd1e38907d2995374a09bd7ba14f7d9502586deb51d5",
     "nprobe": 624, "n_queries": 10_000,
-    "fetch_kib": 404_327, "write_kib": 57_964, "read_factor": 2.00, "write_factor": 1.00,
+    "fetch_kib": 424_617, "write_kib": 57_826, "read_factor": 2.00, "write_factor": 1.00,
 }
-SCAN_SOURCES = ("paper_2308_15014_amd/csrc/caps_mfma.h", "paper_2308_15014_amd/csrc/caps_scan_inst.hip",
+SCAN_SOURCES = ("paper_2308_15014_amd/csrc/caps_mfma.h", "paper_2308_15014_amd/csrc/caps_x32.h",
                 "paper_2308_15014_amd/csrc/caps_search.hip")   # the kernel and the entry lists it reads
 
 
@@ -956,12 +956,9 @@ def main():
         pn = {"bf16": "BF16", "fp16": "FP16", "fp8": "FP8"}[args.precision]
         kern = ("k_scan_fp32 (filter + exact FP32 squared-L2 scan + per-partition top-k)" if mode == 2 else
                 (f"k_scan_x32<{args.precision}> exact main pass ({pn} lower bounds on 32x32 MFMA blocks, exact "
-                 "filter where a score passes, passing pairs deferred to the FP32 rescoring merge)"
-                 if args.precision != "fp8" else
-                 f"k_scan_mfma<{args.precision}> exact main pass ({pn} lower bounds on MFMA, exact filter "
-                 "epilogue, passing pairs deferred to the FP32 rescoring merge)") if mode == 0 else
-                f"k_scan_mfma<{args.precision}> approximate keys ({pn} scores on MFMA, exact filter, "
-                "per-query top-4k)")
+                 "filter where a score passes, passing pairs deferred to the FP32 rescoring merge)") if mode == 0 else
+                f"k_scan_x32<{args.precision}> approximate main pass ({pn} scores on 32x32 MFMA blocks, pairs within "
+                "the seed bound deferred to the exact rerank; below 32 probes k_scan_mfma approximate keys)")
         roof = {"kernel": kern, "avg_launch_ms": round(scan_avg_s * 1e3, 4),
                 "method_flops": {"per_launch": flops_method,
                                  "tflops": round(flops_method / scan_avg_s / 1e12, 3),

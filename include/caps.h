@@ -171,7 +171,11 @@ typedef struct {
                          a rounding margin); pairs whose bound cannot beat the
                          query's current k-th key are skipped and the others
                          are rescored exactly, so the results equal the plain
-                         scan's.  1: approximate: the copy is scanned with
+                         scan's.  Without a copy a large search (n_q nprobe / b of
+                         64 or more, times n d 10^9 or more) rounds the rows
+                         to BF16 in its workspace and prunes with those, where
+                         they take at most half the workspace budget.  1:
+                         approximate: the copy is scanned with
                          matrix cores (FP32 accumulation), each query keeps its
                          best `rerank` candidates under the approximate score
                          (L2: |x|^2 - 2 x~.q~ with the FP32 |x|^2; IP: -x~.q~),
