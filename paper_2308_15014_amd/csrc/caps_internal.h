@@ -177,7 +177,7 @@ caps_status build_lowp_centroids(Index *ix, hipStream_t st);
 // copy; with a row list, score row r belongs to query rows[r], r < *nrows
 caps_status lowp_route(const Index *ix, const void *qlow, const float *qscale, int32_t nb, float *scores,
                        hipStream_t st, const int32_t *rows = nullptr, const int32_t *nrows = nullptr);
-caps_status lowp_qquant(const Index *ix, const float *q, int32_t nb, void *qlow, float *qscale, float *qaux,
+caps_status lowp_qquant(const Index *ix, const float *q, int32_t nb, bool exact, void *qlow, float *qscale, float *qaux,
                         hipStream_t st);
 // low-precision rows (and their FP32 norms and error norms) of n FP32 rows
 caps_status quantize_rows(const Index *ix, const float *x, int64_t n, void *lvec, float *scale, float *xnorm,

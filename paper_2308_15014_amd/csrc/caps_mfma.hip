@@ -232,12 +232,11 @@ caps_status build_lowp(Index *ix, hipStream_t st) {
 // ------------------------------------------------------------------ queries
 // One wave per query.
 __global__ __launch_bounds__(256) void k_qquant(const float *__restrict__ q, int32_t nq, int32_t d, int32_t dpad,
-                                                int32_t prec, void *__restrict__ out, float *__restrict__ scale,
-                                                float *__restrict__ qaux) {
-    const int lane = threadIdx.x & 63;
+                                                int32_t prec, bool exact, void *__restrict__ out,
+                                                float *__restrict__ scale, float *__restrict__ qaux) {
     const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= nq) return;
-    qquant_row(q + i * d, i, d, dpad, prec, out, scale, qaux);
+    qquant_row(q + i * d, i, d, dpad, prec, exact, out, scale, qaux);
 }
 
 // ------------------------------------------------------------------ routing
@@ -332,11 +331,12 @@ caps_status lowp_route(const Index *ix, const void *qlow, const float *qscale, i
 }
 
 // Rounds the queries of a sub-batch into the index's copy format (codes,
-// FP8 scale, error norms) for the matrix-core kernels.
-caps_status lowp_qquant(const Index *ix, const float *q, int32_t nb, void *qlow, float *qscale, float *qaux,
+// FP8 scale, error norms) for the matrix-core kernels of the exact or the
+// approximate search.
+caps_status lowp_qquant(const Index *ix, const float *q, int32_t nb, bool exact, void *qlow, float *qscale, float *qaux,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_qquant, dim3((nb + 3) / 4), dim3(256), 0, st, q, nb, ix->d, ix->dpad, ix->prec, qlow, qscale,
-                       qaux);
+    hipLaunchKernelGGL(k_qquant, dim3((nb + 3) / 4), dim3(256), 0, st, q, nb, ix->d, ix->dpad, ix->prec, exact, qlow,
+                       qscale, qaux);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;
 }

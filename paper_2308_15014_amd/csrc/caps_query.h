@@ -183,15 +183,19 @@ __device__ inline float f32_down(double v) {
 // relative slack covering the FP64 sums and square roots of the error norms
 constexpr double kNormSlack = 1.0 + 0x1p-40;
 
-// Above this |x|^2 (FP32 overflow is near) a row or query gets zero codes and
-// infinite error norms: its pairs always pass the bound and are rescored.
+// Above this |x|^2 (FP32 overflow is near) a query of an exact search, or a row
+// of the BF16 copy that a search makes for itself, gets zero codes and infinite
+// error norms: its pairs always pass the bound and are rescored.  (Not the rows
+// of an index's own copy, nor the queries of the approximate search, whose
+// scores have no bound to fall back on.)
 constexpr float kNormMax = 1e37f;
 
 // One wave, query row r (the i-th): rounded copy (the codes of k_quantize, element by
 // element), FP8 scale and qaux = {|q| (up), |q|^2 (down), |q - q~| (up),
 // |q~| (up)}; the FP64 sums are reduced across the wave (their order does
-// not matter: kNormSlack covers any order).
-__device__ inline void qquant_row(const float *__restrict__ r, int64_t i, int32_t d, int32_t dpad, int32_t prec,
+// not matter: kNormSlack covers any order).  exact: for the exact search's
+// bound; the approximate search keeps the codes of every query.
+__device__ inline void qquant_row(const float *__restrict__ r, int64_t i, int32_t d, int32_t dpad, int32_t prec, bool exact,
                                   void *__restrict__ out, float *__restrict__ scale, float *__restrict__ qaux) {
     const int lane = threadIdx.x & 63;
     float s = 1.0f;
@@ -232,7 +236,7 @@ __device__ inline void qquant_row(const float *__restrict__ r, int64_t i, int32_
     // near FP32 overflow: zero codes and an infinite error norm, as for a row of
     // that size (an infinite code times a zero would make a NaN score, which
     // never passes)
-    if (!(n2 < (double)kNormMax && a2 < (double)kNormMax)) {
+    if (exact && !(n2 < (double)kNormMax && a2 < (double)kNormMax)) {
         for (int j = lane; j < dpad; j += 64) {
             if (prec == CAPS_PREC_FP8)
                 reinterpret_cast<uint8_t *>(out)[i * dpad + j] = 0;

@@ -1805,7 +1805,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             if (small) {
                 prof_begin(CAPS_STAGE_ROUTE, st);
                 if (lowp) {   // precision mode: centroid scores from the rounded queries
-                    caps_status rs = lowp_qquant(ix, q, nb, W.qlow, W.qscale, W.qaux, st);
+                    caps_status rs = lowp_qquant(ix, q, nb, false, W.qlow, W.qscale, W.qaux, st);
                     if (rs == CAPS_OK) rs = lowp_route(ix, W.qlow, W.qscale, nb, scores, st);
                     if (rs != CAPS_OK) return rs;
                 }
@@ -1856,7 +1856,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                                con_val, n_con, nb, ix->sch, (int32_t)disj, qd, W.qterms);
             hipLaunchKernelGGL(k_qcheck, dim3(nblocks(nb, 4)), dim3(256), 0, st, q + (int64_t)q0 * d, nb, d, qd, W.bad);
             if (mfma) {   // the rounded queries of the matrix-core kernels (routing in mode 1, the scans)
-                const caps_status qs = lowp_qquant(ix, q + (int64_t)q0 * d, nb, W.qlow, W.qscale, W.qaux, st);
+                const caps_status qs = lowp_qquant(ix, q + (int64_t)q0 * d, nb, !lowp, W.qlow, W.qscale, W.qaux, st);
                 if (qs != CAPS_OK) return qs;
             }
             prof_end(CAPS_STAGE_PREP, st);

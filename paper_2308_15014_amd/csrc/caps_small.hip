@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kFrontNT) void k_front(FrontArgs A) {
             bad_s = 1;
             atomicAdd(A.bad, 1);
         }
-        if (A.qlow) qquant_row(qg, q, d, A.dpad, A.prec, A.qlow, A.qscale, A.qaux);
+        if (A.qlow) qquant_row(qg, q, d, A.dpad, A.prec, true, A.qlow, A.qscale, A.qaux);
     }
 
     // ---- centroid scores
