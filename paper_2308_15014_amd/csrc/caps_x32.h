@@ -44,7 +44,11 @@
 // a two-byte row's 16-element step and multiplied as two K = 16 products (low
 // and high halves): queries and points use the same order of the elements,
 // and a dot product does not depend on it beyond its rounding, which the
-// bound's margin covers for any order.
+// bound's margin covers for any order.  Approximate scores are results of
+// their own (which candidates are rescored, and ties among them, follow from
+// their rounding), so those modes exchange halves between the lanes of a pair
+// first (fp8_ascend): the products then sum ascending elements, bit for bit as
+// k_scan_mfma's 16 x 16 x 32 products do.  (So do the two-byte formats'.)
 #pragma once
 
 #include "caps_mfma.h"
@@ -75,6 +79,15 @@ __device__ inline f32x16 mma32(uint4 a, uint4 b, f32x16 c) {
         c = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a0, b0, c, 0, 0, 0);
         return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(a1, b1, c, 0, 0, 0);
     }
+}
+
+// Lane l holds bytes 16 g.. of a row's 32-byte block (g = l / 32); afterwards
+// its first half holds bytes 8 g.. and its second half bytes 16 + 8 g.., the
+// operands of two products over ascending elements.
+__device__ inline uint4 fp8_ascend(uint4 v) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(v.x, v.z, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(v.y, v.w, false, false);
+    return make_uint4(lo[0], hi[0], lo[1], hi[1]);
 }
 
 // A label signature folded into the bits of the packed word that no dense field
@@ -276,6 +289,10 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
 #pragma unroll
         for (int s = 0; s < KS; s++)
             bq[s] = own ? *reinterpret_cast<const uint4 *>(src + 32 * s) : make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (F8 && APPROX) {
+#pragma unroll
+            for (int s = 0; s < KS; s++) bq[s] = fp8_ascend(bq[s]);
+        }
     }
     // MFMA A operands: row c32 of a staged chunk, K slice 8g of step s at
     // c32 ROWB + 16 ((2s + g) ^ swizzle) = xo ^ 32s (the row's bytes are a
@@ -562,7 +579,8 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
 #pragma unroll
             for (int s = s0; s < s0 + 2 && s < KS; s++) a[s - s0] = *reinterpret_cast<const uint4 *>(cur + (xo ^ (32u * s)));
 #pragma unroll
-            for (int s = s0; s < s0 + 2 && s < KS; s++) acc = mma32<PREC>(a[s - s0], bq[s], acc);
+            for (int s = s0; s < s0 + 2 && s < KS; s++)
+                acc = mma32<PREC>(F8 && APPROX ? fp8_ascend(a[s - s0]) : a[s - s0], bq[s], acc);
         }
         if constexpr (F8) {   // both scales
 #pragma unroll
