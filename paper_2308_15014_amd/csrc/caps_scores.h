@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TB == 2 ? 2
     };
     float4 px[NU], pc[NU];
     float pn = 0.0f;
-    const float cm = metric == 0 ? -2.0f : -1.0f;   // score = |c|^2 + cm x.c (2 x.c is exact: one rounding)
+    const float cm = metric == 0 ? -2.0f : -1.0f;   // score = |c|^2 + (cm x.c), the product rounded (2 x.c may overflow)
     auto fetch = [&](int it) {
         const int c0 = (ct0 + it / nk) * kSM, j = it % nk * kSK + sc;
         if (it % nk == 0 && t < kSM) pn = c0 + t >= b ? __builtin_huge_valf() : metric == 0 ? cn[c0 + t] : 0.0f;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TB == 2 ? 2
                     for (int e = 0; e < 4; e++)
 #pragma unroll
                         for (int i = 0; i < TB; i++) {
-                            const float s = fmaf(cm, acc[i][k][4 * r4 + e], nc[e]);
+                            const float s = nc[e] + cm * acc[i][k][4 * r4 + e];
                             const bool lt = s < best[i];
                             best[i] = lt ? s : best[i];
                             bestc[i] = lt ? c0 + cl + e : bestc[i];
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TB == 2 ? 2
                     for (int r = 0; r < 16; r++) {
                         const int64_t row = r0 + wr + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3);
                         if (row < n)
-                            out_scores[row * b + c] = canon0(fmaf(cm, acc[i][k][r], nc));
+                            out_scores[row * b + c] = canon0(nc + cm * acc[i][k][r]);
                     }
             }
         }

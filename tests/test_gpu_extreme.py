@@ -38,3 +38,25 @@ def test_approximate_search_does_not_depend_on_query_scale(caps, prec, d, label_
             pa, pb = (ix.probes(q, *args, m, mode=1)[0].cpu().numpy() for q in (w.q[:n], w.q[:n] * big))
             assert np.array_equal(pa, pb)
     ix.close()
+
+
+def test_overflowing_centroid_scores(caps, orc):
+    """|c|^2 - 2 x.c with the product doubled before the subtraction: where it
+    overflows alone the score is -inf, as the oracle computes it, and ties go to
+    the smaller partition (assignment and routing, large and small batches)."""
+    w = synth.make_tiny(1210, n=4000, d=8, n_q=300, vocabs=(3,), b=30, h=1, cmin=0, cmax=1)
+    for t in (w.x, w.q):
+        t[:, 0] = np.where(t[:, 0] < 0, -1.0, 1.0) * (1.35e19 + 1e17 * np.abs(t[:, 0]))   # (x.c)^2 < 3.4e38 < 2 x.c
+    ids = np.arange(30, dtype=np.int32)
+    oi = orc.build_from_workload(w, iters=0, init=ids)
+    ix = caps.Index.build(w.x, w.dense, w.dense_vocab, metric=0, n_partitions=30, kmeans_iters=0, aft_height=1, init_ids=ids)
+    assert len(np.unique(oi.assign)) < 30   # (scores of -inf tie)
+    assert np.array_equal(ix.export()["assign"], oi.assign)
+    for m in (1, 4):
+        r = orc.search(oi, w.q, w.con_off, w.con_attr, w.con_val, 5, m)
+        for n in (20, 300):
+            pr = ix.probes(w.q[:n], w.con_off[:n + 1], w.con_attr, w.con_val, m)[0].cpu().numpy()
+            assert np.array_equal(pr, r.probes[:n])
+            got = ix.search(w.q[:n], w.con_off[:n + 1], w.con_attr, w.con_val, 5, m)
+            assert np.array_equal(got[0].cpu().numpy(), r.ids[:n])
+    ix.close()
