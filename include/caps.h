@@ -485,7 +485,9 @@ typedef struct {
     int64_t workspace_bytes;  /* device memory the search workspaces of all
                                  batches in flight share: a batch is sized to
                                  what the others leave free (and waits when
-                                 not one query fits); 0: no budget */
+                                 not one query fits), and takes no more than
+                                 1/streams of it unless it needs more; 0: no
+                                 budget */
     double batch_window_us;   /* wait up to this long for a batch to fill once a
                                  slot is free (0: launch what is waiting) */
 } caps_server_params;

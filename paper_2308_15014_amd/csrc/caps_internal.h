@@ -136,10 +136,10 @@ caps_status build_index(Index *ix, const float *x, int64_t n, int32_t d, const u
                         const caps_build_params *p, hipStream_t st);
 
 // ---- search (caps_search.hip)
-// internal bit of caps_search_params.flags: batches in flight share a budget
-// (the server sets it): no BF16 copy of an FP32 index in the workspace, no
-// large tables of the small-batch path
-constexpr int32_t kSearchTightWs = 1 << 30;
+// internal bit of caps_search_params.flags: the least workspace (no BF16 copy of
+// an FP32 index, no tables of small batches, short deferred lists); results are
+// the same
+constexpr int32_t kSearchLean = 1 << 30;
 struct SearchExtra {
     uint64_t *surv_mask = nullptr;   // debug: per query, survivor bits over CSR positions (device)
     void *ws = nullptr;              // caller workspace: the search allocates nothing

@@ -1105,6 +1105,7 @@ struct Deferred {
 // most queries defer 600..1900 pairs; with lists of 512 the rescue pass took
 // 2.71 ms of a 7.0 ms search).
 inline int32_t defer_cap(int32_t prec, int32_t k) { return prec == CAPS_PREC_FP8 || k > 16 ? 2048 : 1024; }
+constexpr int32_t kDeferLean = 512;   // (where the workspace counts)
 // Pairs rescored first (those with the smallest test scores): k and half
 // again, at least 16, at most 64 (one per lane).
 __device__ inline int merge_first(int k) { return min(64, max(16, k + (k >> 1))); }
@@ -1526,6 +1527,7 @@ struct SearchPlan {
     int32_t prec, dpad;   // the scanned copy's format (an index without one: BF16 where the search makes its own)
     int64_t copy_n;       // rows of the search's own copy (0: none)
     bool small, direct;   // the small-batch path, without tiles
+    bool lean;            // the least workspace
     int32_t defer;   // deferred pairs kept per query (0: no deferral)
     int32_t s_seed;  // probes of the seed round
     int32_t r, sb;
@@ -1549,7 +1551,7 @@ static int32_t copy_dpad(int32_t d) {
 }
 static size_t copy_bytes(const Index *ix) { return (size_t)ix->n * (2 * (size_t)copy_dpad(ix->d) + 12) + 2048; }
 static bool wants_copy(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget) {
-    if (ix->prec != CAPS_PREC_NONE || sp->mode != 0 || ix->d > 256 || (sp->flags & kSearchTightWs)) return false;
+    if (ix->prec != CAPS_PREC_NONE || sp->mode != 0 || ix->d > 256) return false;
     const double visits = (double)nq * sp->nprobe / ix->b;
     return visits >= 64.0 && visits * (double)ix->n * ix->d >= 1e9 && copy_bytes(ix) <= budget / 2;
 }
@@ -1558,13 +1560,15 @@ static bool wants_copy(const Index *ix, const caps_search_params *sp, int32_t nq
 static int32_t seed_probes(int32_t m, int32_t part) { return m >= 32 ? std::max(8, m / part) : m; }
 
 static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int32_t nq, size_t budget,
-                              bool may_copy) {
+                              bool may_copy, bool lean = false) {
     const int32_t b = ix->b, m = sp->nprobe, k = sp->k;
     SearchPlan P;
+    lean = lean || (sp->flags & kSearchLean);
+    P.lean = lean;
     P.prec = ix->prec;
     P.dpad = ix->dpad;
     P.copy_n = 0;
-    if (may_copy && wants_copy(ix, sp, nq, budget)) {
+    if (may_copy && !lean && wants_copy(ix, sp, nq, budget)) {
         P.prec = CAPS_PREC_BF16;
         P.dpad = copy_dpad(ix->d);
         P.copy_n = ix->n;
@@ -1579,8 +1583,8 @@ static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int
     P.r = P.lowp ? (sp->rerank > 0 ? sp->rerank : std::min(4 * k, kMaxK)) : k;
     const bool filt = ix->sch.label_vocab > 0 || (sp->flags & CAPS_SEARCH_DISJUNCTIVE);
     P.defer = !P.mfma  ? 0
-              : !P.lowp ? defer_cap(P.prec, k)
-                        : m >= 32 && lowp_approx_x32(P.dpad, filt, P.r, seed_probes(m, 16)) ? 2048 : 0;
+              : !P.lowp ? (lean ? kDeferLean : defer_cap(P.prec, k))
+                        : !lean && m >= 32 && lowp_approx_x32(P.dpad, filt, P.r, seed_probes(m, 16)) ? 2048 : 0;
     P.s_seed = seed_probes(m, P.defer && !P.lowp ? 24 : 16);
     P.router = sp->routing == 1 ? ix->router : nullptr;
     P.qlow_row = P.mfma ? (size_t)P.dpad * (P.prec == CAPS_PREC_FP8 ? 1 : 2) : 0;
@@ -1603,7 +1607,7 @@ static SearchPlan plan_search(const Index *ix, const caps_search_params *sp, int
     P.direct = P.small && !P.lowp && direct_fits(ix, nq, m);
     if (P.small && !P.direct) {
         const size_t tables = 2 * sizeof(int4) * (size_t)small_tile_cap(nq, b) + 8 * (size_t)nq * m;
-        P.small = tables <= budget / 8 && (!(sp->flags & kSearchTightWs) || tables <= (size_t)256 << 10);
+        P.small = !lean && tables <= budget / 8;
     }
     return P;
 }
@@ -1687,13 +1691,21 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     SearchPlan P = plan_search(ix, sp, nq, budget, !out_probes);
     size_t need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
     if (ex.ws) {
-        if (need > ex.ws_bytes && P.small) {   // (without the small-batch tables)
-            P.small = P.direct = false;
+        auto shrink = [&]() {
+            if (need > ex.ws_bytes && P.small) {   // (without the small-batch tables)
+                P.small = P.direct = false;
+                need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
+            }
+            while (need > ex.ws_bytes && P.sb > 1) {
+                P.sb = std::max<int32_t>(1, (int32_t)((double)P.sb * (double)ex.ws_bytes / (double)need * 0.95));
+                need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
+            }
+        };
+        shrink();
+        if (need > ex.ws_bytes && !P.lean) {   // not even one query beside the copy or with the long lists
+            P = plan_search(ix, sp, nq, budget, false, true);
             need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
-        }
-        while (need > ex.ws_bytes && P.sb > 1) {
-            P.sb = std::max<int32_t>(1, (int32_t)((double)P.sb * (double)ex.ws_bytes / (double)need * 0.95));
-            need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
+            shrink();
         }
         if (need > ex.ws_bytes) {
             set_error("caps_search: one query needs %zu bytes of workspace, more than the %zu available", need,
@@ -1707,9 +1719,9 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
         ar.base = reinterpret_cast<char *>(ex.ws);
     } else {
         caps_status as = ws_alloc((void **)&ar.base, need, ix->device, st);
-        if (as == CAPS_ENOMEM && P.copy_n) {   // no room for the copy: the plain scan
+        if (as == CAPS_ENOMEM && !P.lean) {   // no room for the copy or the long lists
             (void)hipGetLastError();
-            P = plan_search(ix, sp, nq, budget, false);
+            P = plan_search(ix, sp, nq, budget, false, true);
             need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
             as = ws_alloc((void **)&ar.base, need, ix->device, st);
         }

@@ -15,9 +15,11 @@
 // Admission: submit refuses (EBUSY) beyond `queue_slots` waiting requests
 // and rejects non-finite query rows (EINVAL).  Device memory: the search
 // workspaces of all batches in flight share `workspace_bytes`; a batch is
-// sized to the largest count whose workspace (exact bytes of the search's
+// sized to the largest count whose least workspace (exact bytes of the search's
 // own layout) fits what the batches in flight leave free, and waits for a
-// retirement when not even one query fits.  A query's result does not
+// retirement when not even one query fits.  Where its slot's share of the
+// budget holds the search's usual workspace (longer lists, the tables of small
+// batches, a BF16 copy of an FP32 index), it gets that.  A query's result does not
 // depend on the batch it lands in: every search kernel is batch invariant.
 #include <math.h>
 #include <string.h>
@@ -89,6 +91,7 @@ struct SrvSlot {
     bool busy = false;
     caps_status status = CAPS_OK;
     size_t ws_bytes = 0;                   // workspace reserved by the batch in flight
+    bool lean = false;                     // the least workspace, not the usual one
     std::vector<uint64_t> tickets;         // the batch in flight
     std::vector<Clock::time_point> t0s;
     float *hq = nullptr, *hdist = nullptr, *dq = nullptr, *ddist = nullptr;
@@ -188,8 +191,10 @@ static void launch(Server *S, SrvSlot &sl, int32_t ncon) {
     if (e == hipSuccess && ncon > 0)
         e = hipMemcpyAsync(sl.dval, sl.hval, sizeof(int32_t) * (size_t)ncon, hipMemcpyHostToDevice, sl.st);
     if (e != hipSuccess) s = CAPS_EDEVICE;
+    caps_search_params sp = S->sp;
+    if (sl.lean) sp.flags |= kSearchLean;
     if (s == CAPS_OK)
-        s = search(S->ix, &S->sp, sl.dq, nb, sl.doff, sl.dattr, sl.dval, ncon, sl.dids, sl.ddist, nullptr, nullptr,
+        s = search(S->ix, &sp, sl.dq, nb, sl.doff, sl.dattr, sl.dval, ncon, sl.dids, sl.ddist, nullptr, nullptr,
                    nullptr, nullptr, sl.st);
     if (s == CAPS_OK) {
         e = hipMemcpyAsync(sl.hids, sl.dids, sizeof(int32_t) * (size_t)nb * k, hipMemcpyDeviceToHost, sl.st);
@@ -216,25 +221,43 @@ static void launch(Server *S, SrvSlot &sl, int32_t ncon) {
     }
 }
 
-// Largest batch of at most `want` queries whose search workspace fits the
-// budget the batches in flight leave free (0: none fits); *ws receives its
-// bytes.  Without a budget every batch fits.
-static int32_t admit(Server *S, int32_t want, size_t *ws) {
-    if (S->p.workspace_bytes <= 0) {
-        *ws = 0;
-        return want;
-    }
-    const size_t budget = (size_t)S->p.workspace_bytes;
-    const size_t avail = budget > S->inflight ? budget - S->inflight : 0;
-    if (search_workspace_bytes(S->ix, &S->sp, 1) > avail) return 0;
+// Least workspace of a batch of n queries (it grows with n).
+static size_t lean_bytes(const Server *S, int32_t n) {
+    caps_search_params sp = S->sp;
+    sp.flags |= kSearchLean;
+    return search_workspace_bytes(S->ix, &sp, n);
+}
+
+// Largest batch of at most `want` queries whose least workspace fits `avail`
+// (0: none fits).
+static int32_t largest_batch(const Server *S, int32_t want, size_t avail) {
+    if (lean_bytes(S, 1) > avail) return 0;
     int32_t lo = 1, hi = want;
     while (lo < hi) {
         const int32_t mid = lo + (hi - lo + 1) / 2;
-        if (search_workspace_bytes(S->ix, &S->sp, mid) <= avail) lo = mid;
+        if (lean_bytes(S, mid) <= avail) lo = mid;
         else hi = mid - 1;
     }
-    *ws = search_workspace_bytes(S->ix, &S->sp, lo);
     return lo;
+}
+
+// Largest batch of at most `want` queries that the budget the batches in flight
+// leave free admits (0: none); *ws receives the bytes it reserves, *lean whether
+// those are the least.  Without a budget every batch fits.
+static int32_t admit(Server *S, int32_t want, size_t *ws, bool *lean) {
+    *ws = 0;
+    *lean = false;
+    if (S->p.workspace_bytes <= 0) return want;
+    const size_t budget = (size_t)S->p.workspace_bytes;
+    const size_t avail = budget > S->inflight ? budget - S->inflight : 0;
+    const int32_t n = largest_batch(S, want, avail);
+    if (n == 0) return 0;
+    *ws = search_workspace_bytes(S->ix, &S->sp, n);
+    if (*ws > std::min(avail, budget / S->slots.size())) {
+        *lean = true;
+        *ws = lean_bytes(S, n);
+    }
+    return n;
 }
 
 static void run(Server *S) {
@@ -273,10 +296,12 @@ static void run(Server *S) {
                                   Clock::now() - S->pending.t0[S->pending.head] < window;
                 if (!fill) {
                     size_t ws = 0;
-                    const int32_t nb = admit(S, (int32_t)std::min((size_t)S->cap, S->pending.size()), &ws);
+                    bool lean = false;
+                    const int32_t nb = admit(S, (int32_t)std::min((size_t)S->cap, S->pending.size()), &ws, &lean);
                     if (nb > 0) {   // else wait for a batch in flight to free its workspace
                         ncon = take_batch(S, *free_slot, (size_t)nb);
                         free_slot->ws_bytes = ws;
+                        free_slot->lean = lean;
                         S->inflight += ws;
                         taken = true;
                     }
@@ -404,24 +429,17 @@ extern "C" caps_status caps_server_create(const caps_index *idx, const caps_serv
     S->sp.rerank = p->rerank;
     S->sp.routing = p->routing;
     S->sp.flags = p->flags & CAPS_SEARCH_DISJUNCTIVE;   // (the budget is the server's own: not a sub-batch cap)
-    if (p->workspace_bytes > 0) S->sp.flags |= kSearchTightWs;   // (batches in flight share it)
     S->d = ix.d;
     S->k = p->k;
-    // batch cap: largest size whose search workspace fits the budget
+    // batch cap: largest size whose least workspace fits the budget
     int32_t cap = p->max_batch;
     if (p->workspace_bytes > 0) {
-        int32_t lo = 1, hi = p->max_batch;
-        if (search_workspace_bytes(&ix, &S->sp, 1) > (size_t)p->workspace_bytes) {
+        cap = largest_batch(S, p->max_batch, (size_t)p->workspace_bytes);
+        if (cap == 0) {
             delete S;
             set_error("caps_server_create: workspace_bytes below one query's search workspace");
             return CAPS_EINVAL;
         }
-        while (lo < hi) {
-            const int32_t mid = lo + (hi - lo + 1) / 2;
-            if (search_workspace_bytes(&ix, &S->sp, mid) <= (size_t)p->workspace_bytes) lo = mid;
-            else hi = mid - 1;
-        }
-        cap = lo;
     }
     S->cap = cap;
     const size_t mc = (size_t)std::max(1, cap * p->max_constraints);
