@@ -406,7 +406,8 @@ __global__ __launch_bounds__(kTilesNT) void k_small_tiles(const uint32_t *__rest
 caps_status small_tiles(const uint32_t *pmask, int32_t nq, int32_t b, int32_t m, const SmallRound &r0,
                         const SmallRound &r1, int32_t *cursor, int device, hipStream_t st) {
     const size_t lds = sizeof(uint32_t) * 65 * (size_t)nq;
-    const caps_status ls = set_kernel_lds((const void *)k_small_tiles, lds, device);
+    // (the largest batch's, once: a setting costs 0.2 ms, and batch sizes vary)
+    const caps_status ls = set_kernel_lds((const void *)k_small_tiles, sizeof(uint32_t) * 65 * kSmallQ, device);
     if (ls != CAPS_OK) return ls;
     hipLaunchKernelGGL(k_small_tiles, dim3((unsigned)((b + 63) / 64)), dim3(kTilesNT), lds, st, pmask, nq, b, m, r0, r1,
                        cursor);
