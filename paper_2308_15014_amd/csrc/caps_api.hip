@@ -36,6 +36,7 @@ void release_index(Index &ix) {
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     router_free(ix.router);
+    router_free(ix.spare);
     ix = Index{};
 }
 

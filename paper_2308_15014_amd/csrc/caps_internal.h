@@ -93,6 +93,7 @@ struct IndexData {
     void *clow = nullptr;       // b x dpad centroid copy in the same format (precision-mode routing)
     float *cscale = nullptr;    // b per-centroid FP8 scales
     struct Router *router = nullptr;   // learned router (owned), if trained or set
+    struct Router *spare = nullptr;    // the one before it, if of its shape: the next training's buffers
 };
 struct Index : IndexData {
     std::vector<int32_t> h_offs;

@@ -928,14 +928,16 @@ __global__ void k_router_draw(float *__restrict__ p, uint64_t seed, int32_t din,
     p[i] = w;
 }
 
-// Allocates a router for the index with zeroed moments; w1/b1/w2/b2 from
-// host arrays, or (when null) drawn.  A router of the same shape is filled
-// again in place.
+// Gives the index a router with zeroed moments; w1/b1/w2/b2 from host arrays, or
+// (when null) drawn.  Allocating and freeing one takes 0.25 ms, so the router
+// that a drawn one replaces is kept and filled by the training after it.  After
+// an error the index has the router it had.
 static caps_status router_alloc(Index *ix, int32_t hid, float in_scale, float in_shift, float fb_prob, uint64_t seed,
                                 const float *w1, const float *b1, const float *w2, const float *b2) {
-    Router *old = ix->router;
-    const bool reuse = !w1 && old && old->hid == hid && old->nout == ix->b && old->din == ix->d + kEmbed;
-    Router *R = reuse ? old : new Router;
+    Router *old = ix->router, *kept = ix->spare;
+    auto fits = [&](const Router *r) { return r && r->hid == hid && r->nout == ix->b && r->din == ix->d + kEmbed; };
+    const bool reuse = !w1 && fits(kept);
+    Router *R = reuse ? kept : new Router;
     R->din = ix->d + kEmbed;
     R->dpad = (R->din + 31) / 32 * 32;
     R->hid = hid;
@@ -984,10 +986,10 @@ static caps_status router_alloc(Index *ix, int32_t hid, float in_scale, float in
     hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)nblk((int64_t)R->nout * hid, 256)), dim3(256), 0, 0,
                        R->param + R->o_w2, (int64_t)R->nout * hid, R->w2h);
     if ((e = hipDeviceSynchronize()) != hipSuccess) return fail_free(e);
-    if (!reuse) {
-        router_free(ix->router);
-        ix->router = R;
-    }
+    if (!reuse) router_free(kept);
+    ix->spare = !w1 && fits(old) ? old : nullptr;
+    if (!ix->spare) router_free(old);
+    ix->router = R;
     return CAPS_OK;
 }
 
