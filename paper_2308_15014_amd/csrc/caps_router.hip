@@ -993,6 +993,11 @@ static caps_status router_alloc(Index *ix, int32_t hid, float in_scale, float in
     return CAPS_OK;
 }
 
+// Training workspaces up to this come from the library's pool (100k queries at
+// B = hidden = 1024, batches of 4096: 180 MB); with the default pool a free
+// costs 1.7 ms of host time.
+constexpr size_t kTrainPool = (size_t)256 << 20;
+
 // Workspace of one training / gradient batch of up to bs rows.
 struct BatchWs {
     uint16_t *Xb, *Hb, *dZ16, *dH16;
@@ -1296,7 +1301,12 @@ extern "C" caps_status caps_router_train(caps_index *idx, const caps_router_para
     const size_t off_batch = al(off_perm + sizeof(int32_t) * (size_t)n);
     const size_t total = off_batch + batch_ws(R, bs, n_labels, nullptr, nullptr);
     uint8_t *base = nullptr;
-    s = ws_alloc((void **)&base, total, ix.device, st);   // (the library's pool: the free keeps it)
+    // (a usual one from the library's pool, whose free keeps it; a large one is
+    // given back)
+    if (total <= kTrainPool)
+        s = ws_alloc((void **)&base, total, ix.device, st);
+    else
+        CAPS_HIP(hipMallocAsync((void **)&base, total, st));
     if (s != CAPS_OK) return s;
     uint16_t *X = reinterpret_cast<uint16_t *>(base);
     int32_t *perm = reinterpret_cast<int32_t *>(base + off_perm);
