@@ -156,7 +156,8 @@ __device__ inline float bound_score(uint64_t t) {
 // coordinates of the plain scan (L2: sum (x_j - q_j)^2; IP: -sum x_j q_j).
 // Rows of a multiple of 4 go in batches of XB float4 loads per row, all
 // issued before the batch is summed, so one pair costs d / (4 XB) memory
-// round trips instead of d / 4; the summation order is unchanged.
+// round trips instead of d / 4; other rows in batches of 2 XB floats.  The
+// summation order is unchanged.
 template <int XB>
 __device__ inline float exact_score(const float *__restrict__ xr, const float *__restrict__ qr, int d, bool l2) {
     float acc = 0.0f;
@@ -194,15 +195,27 @@ __device__ inline float exact_score(const float *__restrict__ xr, const float *_
         }
         for (; j < d4; j++) add4(x4[j], q4[j]);
     } else {
-        for (int j = 0; j < d; j++) {
+        auto add1 = [&](const float xv, const float qv) {
             if (l2) {
-                const float t0 = xr[j] - qr[j];
+                const float t0 = xv - qv;
                 acc = fmaf(t0, t0, acc);
             } else {
-                acc = fmaf(xr[j], qr[j], acc);
+                acc = fmaf(xv, qv, acc);
             }
         }
+        };
+        int j = 0;
+        for (; j + 2 * XB <= d; j += 2 * XB) {
+            float xv[2 * XB], qv[2 * XB];
+#pragma unroll
+            for (int u = 0; u < 2 * XB; u++) {
+                xv[u] = xr[j + u];
+                qv[u] = qr[j + u];
+            }
+#pragma unroll
+            for (int u = 0; u < 2 * XB; u++) add1(xv[u], qv[u]);
     }
+        for (; j < d; j++) add1(xr[j], qr[j]);
     return canon0(l2 ? acc : -acc);
 }
 
