@@ -207,13 +207,14 @@ __device__ inline void buf_reduce(uint64_t *buf, int32_t *bcnt, uint64_t *tau, i
 // list array (slot_len keys per slot; `pcnt` gives the count per slot, or
 // lists are padded with ~0) into an LDS pool of capacity CAP, keeping the
 // best `keep` (<= 64) sorted at the front; returns the sum of cand[] over the
-// live slots (0 when cand is null).  Slots with sel == 0 hold nothing.
-template <int CAP>
+// live slots (0 when cand is null).  Slots with sel == 0 hold nothing.  SORTED:
+// the lists ascend, so that a turn without a key below the bound is the last.
+template <int CAP, bool SORTED = false>
 __device__ inline int gather_best(uint64_t *pool, int32_t *npool, const uint64_t *partials, const int32_t *pcnt,
                                   const uint32_t *sel, const int32_t *cand, int64_t slot0, int r0, int r1,
                                   int slot_len, int keep) {
     const int lane = threadIdx.x & 63;
-    uint64_t unused_bound = ~0ull;
+    uint64_t unused_tau = ~0ull, bound = ~0ull;   // bound: the keep-th key of the pool when last reduced
     if (lane == 0) *npool = 0;
     wave_sync();
     int nc = 0;
@@ -228,9 +229,16 @@ __device__ inline int gather_best(uint64_t *pool, int32_t *npool, const uint64_t
         for (int o = 32; o >= 1; o >>= 1) cmax = max(cmax, __shfl_xor(cmax, o, 64));
         for (int i = 0; i < cmax; i++) {
             const uint64_t key = i < c ? partials[slot * slot_len + i] : ~0ull;
-            const bool has = key != ~0ull;
+            const bool has = key < bound;
             const uint64_t bal = __ballot(has);
-            if (*npool + 64 > CAP) buf_reduce<CAP>(pool, npool, &unused_bound, 0, keep);
+            if (!bal) {
+                if (SORTED) break;
+                continue;
+            }
+            if (*npool + 64 > CAP) {
+                buf_reduce<CAP>(pool, npool, &unused_tau, 0, keep);
+                if (*npool == keep) bound = pool[keep - 1];
+            }
             const int n2 = *npool;
             if (has) pool[n2 + __popcll(bal & lanemask_lt())] = key;
             wave_sync();
@@ -240,7 +248,7 @@ __device__ inline int gather_best(uint64_t *pool, int32_t *npool, const uint64_t
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
-    buf_reduce<CAP>(pool, npool, &unused_bound, 0, keep);
+    buf_reduce<CAP>(pool, npool, &unused_tau, 0, keep);
     return nc;
 }
 

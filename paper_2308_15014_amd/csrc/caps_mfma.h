@@ -216,6 +216,7 @@ __device__ inline float exact_score(const float *__restrict__ xr, const float *_
             for (int u = 0; u < 2 * XB; u++) add1(xv[u], qv[u]);
     }
         for (; j < d; j++) add1(xr[j], qr[j]);
+    }
     return canon0(l2 ? acc : -acc);
 }
 
