@@ -202,7 +202,6 @@ __device__ inline float exact_score(const float *__restrict__ xr, const float *_
             } else {
                 acc = fmaf(xv, qv, acc);
             }
-        }
         };
         int j = 0;
         for (; j + 2 * XB <= d; j += 2 * XB) {
@@ -214,7 +213,7 @@ __device__ inline float exact_score(const float *__restrict__ xr, const float *_
             }
 #pragma unroll
             for (int u = 0; u < 2 * XB; u++) add1(xv[u], qv[u]);
-    }
+        }
         for (; j < d; j++) add1(xr[j], qr[j]);
     }
     return canon0(l2 ? acc : -acc);

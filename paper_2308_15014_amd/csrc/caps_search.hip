@@ -1189,7 +1189,7 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
     int32_t *npool = &npools[wq];
     uint64_t bound = ~0ull;   // k-th key of the pool when last reduced (lane 0 writes it)
     if (D.oflow[q]) {   // rescanned: the rescue pass's lists
-        const int nc = gather_best<kMergePool>(pool, npool, partials, pcnt, sel, cand, (int64_t)q * m, 0, m, k, k);
+        const int nc = gather_best<kMergePool, true>(pool, npool, partials, pcnt, sel, cand, (int64_t)q * m, 0, m, k, k);
         if (lane == 0) ncand[q] = nc;
     } else {
         const int n = min(D.cnt[q], D.cap);
