@@ -473,6 +473,8 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
     uint32_t *ring_key = ring[SEED ? 0 : w][1];   // the pair's ordered score (not in the seed mode)
     int32_t *hist = dhist[SEED ? 0 : w];
     int vhead = 0, vtail = 0;
+    int lj = -1;        // level of the last scored chunk, and the lane's bound there
+    float tfj = qnan;
     auto drain = [&](int n) {
         wave_sync();
         bool v = lane < n;
@@ -495,6 +497,11 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
         const int at = __shfl(base, qj, 64) + rank;
         if (v && at < A.dcap) A.dpos[(int64_t)qq * A.dcap + at] = ((uint64_t)pkey << 32) | pos;
         if (v && at >= A.dcap) A.oflow[qq] = 1;
+        // a query whose list is full is rescanned: no more pairs of it (a round
+        // trip to its counter for every 64 of them: 1.72 ms against 0.39 for 2141
+        // queries of which each has 6000)
+        const uint64_t full = __builtin_amdgcn_ballot_w64(cnt > 0 && base + cnt > A.dcap);
+        if ((full >> c32) & 1ull) my_tf = tfj = qnan;
     };
 
     // ---- pipeline.  Step k scores group k (kXG chunks): it waits for the
@@ -519,8 +526,6 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     lds_barrier();
     if (w < kXG && chunkj(w)) point_terms(rw0, rg0, rs0, w, (int)(chunkj(w) >> 8), 0);
-    int lj = -1;
-    float tfj = qnan;
     uint64_t lst[SEED ? MH : 1];   // seed: the lane's best keys, ascending (~0: empty)
 #pragma unroll
     for (int i = 0; i < (SEED ? MH : 1); i++) lst[i] = ~0ull;
