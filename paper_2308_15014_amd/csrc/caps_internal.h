@@ -197,6 +197,7 @@ struct LowpScan {
                                   // (approximate keys of the seed probes on 32 x 32 blocks), 5 approximate
                                   // rescue pass, 6 approximate main pass (32 x 32 blocks)
     int seed_mh;                  // kind 4: keys per lane (half of a probe's rows), 1 or 4
+    int split;                    // 32 x 32 kinds: workgroups that share each tile's rows
     int stage;                    // profiling stage of the launch (CAPS_STAGE_SCAN or _SEED)
     int64_t max_tiles;
     const int4 *tiles;            // per tile: partition, first entry, entries (0: none)

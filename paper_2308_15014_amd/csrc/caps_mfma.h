@@ -42,6 +42,7 @@ struct LowpArgs {
     int32_t *oflow;             // exact: per query flag, set when its pairs did not fit (rescue pass input)
     const int32_t *rlist, *rcount;   // rescue pass: tiles with a flagged query and their number (null: every tile)
     int32_t m, h, b, r, metric, d, dcap, ntiles;   // ntiles: length of `tiles` (the grid's tile range)
+    int32_t split;              // k_scan_x32: workgroups that share each tile's rows (1: as the tiles say)
     int32_t rhalves;            // rescue pass over 128-entry tiles: list entries are 2 tile + half
     float eta, gam;             // exact: relative rounding margin, MFMA accumulation bound
 };

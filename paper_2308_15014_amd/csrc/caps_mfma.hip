@@ -557,6 +557,7 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     A.dpos = S.dpos;
     A.dcnt = S.dcnt;
     A.dcap = S.dcap;
+    A.split = std::max(1, S.split);
     A.oflow = S.oflow;
     A.rlist = S.rlist;
     A.rcount = S.rcount;
@@ -594,7 +595,7 @@ caps_status lowp_scan(const Index *ix, const LowpScan &S, hipStream_t st) {
     }
     prof_begin(S.stage, st);
     // the rescue pass walks its (device-side) tile list with a bounded grid
-    const int64_t full = (S.max_tiles + kXcds - 1) / kXcds * kXcds;
+    const int64_t full = (S.max_tiles * (x32 ? A.split : 1) + kXcds - 1) / kXcds * kXcds;
     const int64_t rcap = S.rescue_grid > 0 ? S.rescue_grid : kRescueWgs;
     const int64_t grid = S.kind == 2 || S.kind == 5 ? std::min<int64_t>(full, rcap) : full;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(x32 ? kXW * 64 : kLNT), lds, st, A);
@@ -627,15 +628,22 @@ int lowp_qb_main(const Index *ix, bool disj, bool count) {
 
 // Keys each lane of the 32 x 32 seed pass keeps (half of a partition's rows
 // and one query), or 0 where the seed round runs k_scan_mfma's approximate
-// kind.  Lists of two keys per seed probe are enough when they hold twice k
+// kind; *split: in, how many workgroups may share a tile's rows; out, how many do
+// (each fills its own part of the lists of r keys).
+// Lists of two keys per seed probe are enough when they hold twice k
 // (longer lists cost more insertions than their tighter bound saved: 4 and 10
 // keys ran 0.34 and 0.44 ms per 10k-query step against 0.28 ms with the same
-// main pass); with fewer seed probes or a longer result list, lists of eight
-// keys where those can hold k; else the full lists of r.
-int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed) {
-    if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false)) return 0;
-    if (r >= 2 && s_seed >= k) return 1;
-    return r >= 8 && 8 * s_seed >= k ? 4 : 0;
+// main pass), also those of all workgroups of a tile together; with fewer seed
+// probes or a longer result list, lists of eight keys where those can hold k;
+// else the full lists of r.
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, int *split) {
+    const int want = *split;
+    *split = 1;
+    if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false) || r < 2) return 0;
+    const int s1 = std::max(1, std::min(want, r / 2));   // (two keys each)
+    const int mh = s1 * s_seed >= k ? 1 : r >= 8 && 8 * s_seed >= k ? 4 : 0;
+    if (mh) *split = mh == 1 ? s1 : std::max(1, std::min(want, r / 8));
+    return mh;
 }
 
 // The approximate search defers its pairs (32 x 32 blocks) where that scan has

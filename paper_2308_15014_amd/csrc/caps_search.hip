@@ -1418,7 +1418,7 @@ struct Arena {
 
 int lowp_qb();
 int lowp_qb_main(const Index *ix, bool disj, bool count);
-int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed);
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, int *split);
 
 struct SearchWs {
     uint8_t *qlow;
@@ -1992,29 +1992,33 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 prof_end(CAPS_STAGE_SELECT, st);
                 qord = W.qord;
             }
-            // tile width of a round: the exact main pass and the seed lists may
-            // run 128-entry tiles
-            const int seed_mh = seeded_exact ? lowp_seed_x32(ix, disj, r, k, s_seed) : deferred ? (r >= 8 ? 4 : 1) : 0;
-            int qbs[2], splits[2] = {1, 1};
+            // tile width of a round: the main pass of 32 x 32 blocks and the seed
+            // lists run 128-entry tiles.  Few tiles leave most of the chip idle:
+            // up to kSmallSplit workgroups share a tile's rows (in 32-row chunks,
+            // at least two each on average) until there are about four per compute
+            // unit.
+            int qbs[2], splits[2] = {1, 1}, seed_mh = 0;
             for (int round = 0; round < 2; round++) {
                 const bool seed_pass = deferred && round == 0;
-                qbs[round] = !mfma || (lowp && !deferred) || (seed_pass && !seed_mh) ? qb
-                                                                      : lowp_qb_main(ix, disj, !seed_pass && out_nsurv);
+                const int32_t nslot = round == 0 ? s_seed : deferred ? m : m - s_seed;
+                const int wide = deferred ? lowp_qb_main(ix, disj, !seed_pass && out_nsurv) : qb;
+                const int64_t pr = (int64_t)nb * nslot, whole = (int64_t)b * ((nb + wide - 1) / wide);
+                const int64_t tl = small ? std::min(whole, pr) : std::min(whole, pr / wide + std::min<int64_t>(b, pr));
+                int split = (int)std::max<int64_t>(1, std::min<int64_t>({1024 / std::max<int64_t>(1, tl), ix->n / b / 64, kSmallSplit}));
+                if (seed_pass && seeded_exact) {
+                    seed_mh = lowp_seed_x32(ix, disj, r, k, s_seed, &split);
+                } else if (seed_pass) {
+                    seed_mh = r >= 8 ? 4 : 1;
+                    split = std::min(split, r / (2 * seed_mh));
+                }
+                qbs[round] = seed_pass && !seed_mh ? qb : wide;
+                splits[round] = qbs[round] != qb ? split : 1;
             }
             if (small) {
-                // Few tiles leave most of the chip idle: up to kSmallSplit
-                // workgroups share a tile's rows (in 32-row chunks, at least two
-                // each on average) until there are about four per compute unit.
                 SmallRound R[2] = {};
                 for (int round = 0; round < 2; round++) {
-                    const bool seed_pass = deferred && round == 0;
                     const int32_t nslot = round == 0 ? s_seed : deferred ? m : m - s_seed;
                     if (nslot <= 0) continue;
-                    const bool x32 = seed_pass ? seed_mh > 0 : mfma && qbs[1] != qb;
-                    const int64_t tl = std::min<int64_t>((int64_t)b * ((nb + qbs[round] - 1) / qbs[round]), (int64_t)nb * nslot);
-                    int64_t split = std::min<int64_t>({1024 / std::max<int64_t>(1, tl), ix->n / b / 64, kSmallSplit});
-                    if (seed_pass) split = std::min<int64_t>(split, r / (2 * std::max(1, seed_mh)));
-                    splits[round] = x32 ? (int)std::max<int64_t>(1, split) : 1;
                     R[round].entries = round == 0 ? W.sent : entries;
                     R[round].esel = !deferred ? nullptr : round == 0 ? W.sesel : W.esel;
                     R[round].tiles = W.stiles[round];
@@ -2081,6 +2085,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                              : lowp || seed_pass     ? 0
                                                      : 1;
                     S.seed_mh = seed_mh;
+                    S.split = small ? 1 : splits[round];
                     S.stage = seed_pass ? CAPS_STAGE_SEED : CAPS_STAGE_SCAN;
                     S.max_tiles = grid;
                     S.tiles = tiles;

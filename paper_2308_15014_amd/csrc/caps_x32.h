@@ -162,17 +162,19 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
     float(*qmx)[kXW] = reinterpret_cast<float(*)[kXW]>(&dhist[0][0]);
     uint32_t *lvw = reinterpret_cast<uint32_t *>(&dhist[0][2 * kXW]);
 
-    const int tile = xcd_tile(blockIdx.x, A.ntiles);
-    if (tile < 0) return;
+    const int slot_i = xcd_tile(blockIdx.x, A.ntiles * A.split);
+    if (slot_i < 0) return;
+    const int tile = slot_i / A.split;
     const int4 dsc = A.tiles[tile];
     if (dsc.z <= 0) return;
     const int p = dsc.x;
     const int nqt = dsc.z;
     const int32_t *ent = A.entries + dsc.y;
     const int h = A.h;
-    // the tile's share of the rows: chunks share, share + nshare, ... (small
-    // batches; a whole tile has w = 0)
-    const int share = dsc.w & 255, nshare = max(1, dsc.w >> 8);
+    // the workgroup's share of the rows: chunks share, share + nshare, ... (the
+    // tiles of small batches name it themselves; a whole tile has w = 0)
+    const int share = A.split > 1 ? slot_i - tile * A.split : dsc.w & 255;
+    const int nshare = A.split > 1 ? A.split : max(1, dsc.w >> 8);
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // (wave-uniform: kept in a scalar register)
     const int g = lane >> 5, c32 = lane & 31;
