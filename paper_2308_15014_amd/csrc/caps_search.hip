@@ -1458,7 +1458,7 @@ struct SearchWs {
 // Tiles of one round of a small batch at most: 64-entry tiles, each shared by
 // up to kSmallSplit workgroups.
 constexpr int32_t kSmallSplit = 8;
-static int64_t small_tile_cap(int64_t nq, int64_t b) { return b * ((nq + 63) / 64) * kSmallSplit + kXcds; }
+static int64_t small_tile_cap(int64_t nq, int32_t b) { return (int64_t)small_padded(b) * ((nq + 63) / 64) * kSmallSplit; }
 
 // Tiles of one round at most: every (query, probe) entry in tiles of at
 // least 64 entries, plus one partial tile per partition, rounded up to the
@@ -2043,7 +2043,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 const int4 *tiles = W.tiles;
                 int64_t grid = 0;
                 if (small) {
-                    grid = (int64_t)b * ((nb + qbr - 1) / qbr) * splits[round];
+                    grid = (int64_t)small_padded(b) * ((nb + qbr - 1) / qbr) * splits[round];
                     ent = round == 0 ? W.sent : entries;
                     esel = round == 0 ? W.sesel : W.esel;
                     tiles = W.stiles[round];

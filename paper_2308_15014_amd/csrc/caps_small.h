@@ -6,6 +6,8 @@
 namespace caps {
 
 constexpr int kSmallQ = 256;                 // queries at most
+// partitions, rounded up to a whole number on each of the 8 XCDs
+__host__ __device__ constexpr int small_padded(int b) { return (b + 7) / 8 * 8; }
 constexpr uint32_t kSmallSeed = 1u << 30;    // word of a (query, partition): level mask, slot << 16, seed probe
 
 struct FrontArgs {
@@ -38,7 +40,7 @@ struct FrontArgs {
 struct SmallRound {
     int32_t *entries;             // up to nq x m (null: no such round)
     uint32_t *esel;
-    int4 *tiles;                  // b x ceil(nq / qb) x split
+    int4 *tiles;                  // small_padded(b) x ceil(nq / qb) x split
     int32_t which, qb, split;
 };
 
