@@ -693,10 +693,11 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
                 }
                 if (hit[0] | hit[1] | hit[2] | hit[3]) {
                     bool moved = false;
-                    // (rolled where the body holds the label tests or the drain: sixteen
-                    // copies of them over the blocks and rows ran 1.5x slower on small
-                    // label batches; the plain buffer update runs 5 % faster unrolled)
-                    constexpr int UR = HAS_LABELS || EXACT ? 1 : 4;
+                    // (rolled where the body holds the drain: sixteen copies of it over
+                    // the blocks and rows ran 1.5x slower on small label batches; the
+                    // buffer update runs faster unrolled, with the label tests 1 - 5 %
+                    // over 70 drawn approximate searches)
+                    constexpr int UR = EXACT ? 1 : 4;
 #pragma unroll UR
                     for (int rr = 0; rr < 4; rr++) {   // wave-uniform test per row group
                         const uint64_t hm = rr == 0 ? hit[0] : rr == 1 ? hit[1] : rr == 2 ? hit[2] : hit[3];
