@@ -164,17 +164,24 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
 
     const int slot_i = xcd_tile(blockIdx.x, A.ntiles * A.split);
     if (slot_i < 0) return;
-    const int tile = slot_i / A.split;
+    // the workgroup's share of the tile's rows: chunks share, share + nshare, ...
+    // (one of A.split, or what a small batch's tile names; a whole tile has w = 0)
+    int tile = slot_i, share = 0, nshare = 1;
+    if (A.split > 1) {
+        nshare = A.split;
+        tile = slot_i / nshare;
+        share = slot_i - tile * nshare;
+    }
     const int4 dsc = A.tiles[tile];
+    if (dsc.w) {
+        share = dsc.w & 255;
+        nshare = dsc.w >> 8;
+    }
     if (dsc.z <= 0) return;
     const int p = dsc.x;
     const int nqt = dsc.z;
     const int32_t *ent = A.entries + dsc.y;
     const int h = A.h;
-    // the workgroup's share of the rows: chunks share, share + nshare, ... (the
-    // tiles of small batches name it themselves; a whole tile has w = 0)
-    const int share = A.split > 1 ? slot_i - tile * A.split : dsc.w & 255;
-    const int nshare = A.split > 1 ? A.split : max(1, dsc.w >> 8);
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // (wave-uniform: kept in a scalar register)
     const int g = lane >> 5, c32 = lane & 31;
@@ -499,11 +506,15 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
         const int at = __shfl(base, qj, 64) + rank;
         if (v && at < A.dcap) A.dpos[(int64_t)qq * A.dcap + at] = ((uint64_t)pkey << 32) | pos;
         if (v && at >= A.dcap) A.oflow[qq] = 1;
-        // a query whose list is full is rescanned: no more pairs of it (a round
-        // trip to its counter for every 64 of them: 1.72 ms against 0.39 for 2141
-        // queries of which each has 6000)
-        const uint64_t full = __builtin_amdgcn_ballot_w64(cnt > 0 && base + cnt > A.dcap);
-        if ((full >> c32) & 1ull) my_tf = tfj = qnan;
+        if constexpr (F8) {
+            // a query whose list is full is rescanned: no more pairs of it (a
+            // round trip to its counter for every 64 of them: 1.72 ms against
+            // 0.39 for 2141 queries of which each has 6000).  The two-byte
+            // formats' bounds leave few such queries, and the two registers
+            // this takes cost their main pass 2 %.
+            const uint64_t full = __builtin_amdgcn_ballot_w64(cnt > 0 && base + cnt > A.dcap);
+            if ((full >> c32) & 1ull) my_tf = tfj = qnan;
+        }
     };
 
     // ---- pipeline.  Step k scores group k (kXG chunks): it waits for the
