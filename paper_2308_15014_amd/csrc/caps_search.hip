@@ -1272,13 +1272,14 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
             uint64_t *buf = mbuf[wq];
             const uint64_t lt = lanemask_lt();
             int n1 = 0;
+            uint32_t taken = 0;   // bit j: pair lane + 64 j
 #pragma unroll
             for (int j = 0; j < NP; j++) {
                 const bool s = e[j] != ~0ull && skey(e[j]) < T;
                 const uint64_t b = __ballot(s);
                 if (s) {
                     buf[n1 + __popcll(b & lt)] = e[j];
-                    e[j] = ~0ull;
+                    taken |= 1u << j;
                 }
                 n1 += __popcll(b);
             }
@@ -1289,7 +1290,7 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
                 const int at = n1 + __popcll(b & lt);
                 if (s && at < 64) {
                     buf[at] = e[j];
-                    e[j] = ~0ull;
+                    taken |= 1u << j;
                 }
                 n1 = min(64, n1 + __popcll(b));
             }
@@ -1306,20 +1307,31 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
                                                            : fmaf(D.eta, nq + fabsf(td), td) + 1e-37f;
             // (compacted through LDS, so that one round of row reads serves 64
             // of them: rescored register by register, the few pairs that pass
-            // cost up to NP dependent round trips)
+            // cost up to NP dependent round trips.  The pairs are read again,
+            // four at a time: a copy of this body for each of 32 registers was
+            // not unrolled, and the pairs went to scratch memory, 281 us for 369
+            // queries with 2000 pairs each of 200 coordinates)
             int np = 0;
+            for (int j0 = 0; j0 < NP && j0 * 64 < n; j0 += 4) {
+                uint64_t v[4];
 #pragma unroll
-            for (int j = 0; j < NP; j++) {
-                const bool s = e[j] != ~0ull && ord2f(skey(e[j])) <= tf;
-                const uint64_t b = __ballot(s);
-                if (s) buf[np + __popcll(b & lt)] = e[j];   // at most 63 + 64 entries
-                np += __popcll(b);
-                if (np >= 64) {
-                    wave_sync();
-                    const uint64_t key = score(buf[np - 64 + lane]);
-                    insert(key < K ? key : ~0ull);
-                    np -= 64;
-                    wave_sync();
+                for (int u = 0; u < 4; u++) {
+                    const int i = (j0 + u) * 64 + lane;
+                    v[u] = i < n && !((taken >> (j0 + u)) & 1u) ? src[i] : ~0ull;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const bool s = v[u] != ~0ull && ord2f(skey(v[u])) <= tf;
+                    const uint64_t b = __ballot(s);
+                    if (s) buf[np + __popcll(b & lt)] = v[u];   // at most 63 + 64 entries
+                    np += __popcll(b);
+                    if (np >= 64) {
+                        wave_sync();
+                        const uint64_t key = score(buf[np - 64 + lane]);
+                        insert(key < K ? key : ~0ull);
+                        np -= 64;
+                        wave_sync();
+                    }
                 }
             }
             wave_sync();
