@@ -75,6 +75,28 @@ __device__ inline void qd_summary(QDesc &r, const Schema &sch, const QDesc *tq, 
     r.nterm = nsat;
 }
 
+// The pairs [lo, hi) as a disjunction, terms separated by CAPS_OR: the
+// satisfiable terms go to tq, r (clear before) becomes their summary (one
+// satisfiable term: that term; none, or more than kMaxTerms terms:
+// unsatisfiable).  cur: scratch.
+__device__ inline void qd_disjunction(QDesc &r, QDesc &cur, QDesc *tq, const Schema &sch, const int32_t *attr,
+                                      const int32_t *val, int32_t lo, int32_t hi) {
+    qd_clear(cur);
+    int nt = 0, nsat = 0;
+    for (int32_t e = lo; e <= hi; e++) {
+        if (e < hi && attr[e] != CAPS_OR) {
+            qd_add(cur, sch, attr[e], val[e]);
+            continue;
+        }
+        if (++nt > kMaxTerms) break;
+        if (!(cur.flags & kQUnsat)) tq[nsat++] = cur;
+        qd_clear(cur);
+    }
+    if (nt > kMaxTerms || nsat == 0) r.flags |= kQUnsat;
+    else if (nsat == 1) r = tq[0];
+    else qd_summary(r, sch, tq, nsat);
+}
+
 // ------------------------------------------------------------------ sub-partition choice
 __device__ inline void tag_decode(const Schema &s, int32_t tok, int &attr, int32_t &val) {
     if (tok < s.dense_off[s.n_dense]) {

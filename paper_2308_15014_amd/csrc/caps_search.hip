@@ -56,26 +56,8 @@ __global__ __launch_bounds__(128) void k_qprep(const int32_t *__restrict__ con_o
         out[q] = r;
         return;
     }
-    QDesc *tq = terms + (int64_t)q * kMaxTerms;
     QDesc cur;
-    qd_clear(cur);
-    int nt = 0, nsat = 0;
-    for (int32_t e = lo; e <= hi; e++) {
-        if (e < hi && con_attr[e] != CAPS_OR) {
-            qd_add(cur, sch, con_attr[e], con_val[e]);
-            continue;
-        }
-        if (++nt > kMaxTerms) break;
-        if (!(cur.flags & kQUnsat)) tq[nsat++] = cur;
-        qd_clear(cur);
-    }
-    if (nt > kMaxTerms || nsat == 0) {
-        r.flags |= kQUnsat;
-    } else if (nsat == 1) {
-        r = tq[0];
-    } else {
-        qd_summary(r, sch, tq, nsat);
-    }
+    qd_disjunction(r, cur, terms + (int64_t)q * kMaxTerms, sch, con_attr, con_val, lo, hi);
     out[q] = r;
 }
 

@@ -148,24 +148,8 @@ __global__ __launch_bounds__(kFrontNT) void k_front(FrontArgs A) {
                     if (lane == 0) qd_add(qds, A.sch, ai, vi);
                 }
             }
-        } else {
-            QDesc *tq = A.qterms + q * kMaxTerms;
-            if (lane == 0) {
-                qd_clear(cur);
-                int nt = 0, nsat = 0;
-                for (int32_t e = lo; e <= hi; e++) {
-                    if (e < hi && A.con_attr[e] != CAPS_OR) {
-                        qd_add(cur, A.sch, A.con_attr[e], A.con_val[e]);
-                        continue;
-                    }
-                    if (++nt > kMaxTerms) break;
-                    if (!(cur.flags & kQUnsat)) tq[nsat++] = cur;
-                    qd_clear(cur);
-                }
-                if (nt > kMaxTerms || nsat == 0) qds.flags |= kQUnsat;
-                else if (nsat == 1) qds = tq[0];
-                else qd_summary(qds, A.sch, tq, nsat);
-            }
+        } else if (lane == 0) {
+            qd_disjunction(qds, cur, A.qterms + q * kMaxTerms, A.sch, A.con_attr, A.con_val, lo, hi);
         }
     }
     if (w == 1) {
