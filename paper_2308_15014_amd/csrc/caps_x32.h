@@ -107,7 +107,8 @@ __device__ inline uint32_t fold_sig(uint64_t sig, int at, int nfree) {
 // 0.65 ms in the seed pass although 22 registers spill there, FP16 labels 5.03
 // against 5.47 ms.  Disjunctions (their terms in registers), seed lists of
 // four keys with labels and the counting pass (12 registers would spill) stay
-// at three.
+// at three; so, by its LDS (41,120 bytes: the staged label slots), does the
+// seed pass with labels on two-byte rows of 128 elements.
 constexpr int x32_waves(int mode, int mh, int filt) {
     return filt == 2 || mode == 1 || (filt == 1 && mode == 2 && mh > 1) ? 3 : 4;
 }
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(kXW * 64) __attribute__((amdgpu_waves_per_eu(x32_wa
     __shared__ uint32_t ring[SEED ? 1 : kXW][2][SEED ? 1 : kXRing];
     __shared__ uint8_t rrow[SEED ? 1 : kXW][SEED ? 1 : kXRing];
     __shared__ int32_t dhist[SEED ? 1 : kXW][kXQ];   // (before the pipeline starts: also the tile's maxima, below)
-    __shared__ int32_t scnt[COUNT ? kXQB : 1];   // (only the counting mode: the modes used per search keep 4 workgroups per CU)
+    __shared__ int32_t scnt[COUNT ? kXQB : 1];   // (only the counting mode: the main passes keep 4 workgroups per CU)
     // the tile prologue's per-wave maxima share the drain histograms' storage:
     // every read of them completes before the pipeline's first barrier, and
     // no drain runs before it
