@@ -799,7 +799,10 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(NS >= 8 ||
         // the start of a tile and read until its end
         const int nr = A.rlist ? *A.rcount : A.ntiles * (A.rhalves ? 2 : 1);
         for (int i = blockIdx.x; i < nr; i += gridDim.x) {
-            const int e = A.rlist ? A.rlist[i] : i;
+            // (without a list: every tile, the second halves after the first ones,
+            // so that no workgroup has two full ones: 0.25 ms against 0.14 for 35
+            // queries over 245 of 513 partitions)
+            const int e = A.rlist ? A.rlist[i] : !A.rhalves ? i : i < A.ntiles ? 2 * i : 2 * (i - A.ntiles) + 1;
             int4 dsc = A.tiles[A.rhalves ? e >> 1 : e];
             if (dsc.w & 255) continue;   // a further share of a tile listed before
             if (A.rhalves) {   // the 64 entries of one half of a 128-entry tile
