@@ -1071,7 +1071,7 @@ struct Deferred {
     const uint64_t *pos;        // null: none
     const int32_t *cnt;
     const int32_t *oflow;       // queries rescanned by the rescue pass: deferred pairs ignored, partial lists read
-    int32_t cap, d;
+    int32_t cap, d, first;      // first: pairs rescored in round 1, at least k, at most 64
     const float *vecs, *q;      // FP32 CSR rows, the sub-batch's queries
     const int32_t *perm;
     const float *qaux;          // the scan's per-query terms (|q|^2 lower bound at 4 q + 1)
@@ -1088,9 +1088,10 @@ struct Deferred {
 // 2.71 ms of a 7.0 ms search).
 inline int32_t defer_cap(int32_t prec, int32_t k) { return prec == CAPS_PREC_FP8 || k > 16 ? 2048 : 1024; }
 constexpr int32_t kDeferLean = 512;   // (where the workspace counts)
-// Pairs rescored first (those with the smallest test scores): k and half
-// again, at least 16, at most 64 (one per lane).
-__device__ inline int merge_first(int k) { return min(64, max(16, k + (k >> 1))); }
+// Pairs rescored first (those with the smallest test scores, one per lane): k
+// and half again, at least 16, at most 64; all 64 in FP8, whose test scores say
+// little about the exact ones (the k-th of 16 left nearly every pair to round 2).
+inline int merge_first(int32_t prec, int k) { return prec == CAPS_PREC_FP8 ? 64 : std::min(64, std::max(16, k + (k >> 1))); }
 
 // Plain scan: partial lists padded with ~0; matrix-core lists are counted
 // (pcnt).  One wave per query, a sorted list of KM keys per lane.
@@ -1149,13 +1150,15 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ part
     }
 }
 
-// Deferred pairs of the exact matrix-core scan.  One wave per query; the exact
+// Deferred pairs of the exact matrix-core scan.  One wave per query, or W of them
+// where few queries have long lists: each finds the same bound K, rescores its
+// share of the other pairs, and the first joins their pools.  The exact
 // keys found collect in an LDS pool whose best k are kept by rank (a sorted
 // list of 16 to 64 keys in each lane's registers, and k wave-wide minima at
 // the end, took 96 us per 10k queries at k = 10 and 162 us for 777 at k = 50).
 // EP: pairs per lane of a full deferred list (cap / 64).
 constexpr int kMergePool = 256;
-template <int EP>
+template <int EP, int W>
 __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict__ partials,
                                                      const int32_t *__restrict__ pcnt,
                                                      const uint32_t *__restrict__ sel, const int32_t *__restrict__ cand,
@@ -1164,13 +1167,16 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
                                                      int32_t *__restrict__ ncand, Deferred D) {
     __shared__ uint64_t pools[4][kMergePool], mbuf[4][128];   // per wave: keys, pairs to rescore
     __shared__ int32_t npools[4];
+    static_assert(W == 1 || W == 4, "a query per wave or per workgroup");
     const int wq = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int q = blockIdx.x * 4 + wq;
+    const int q = W == 1 ? blockIdx.x * 4 + wq : blockIdx.x, part = W == 1 ? 0 : wq;
     if (q >= nq) return;
     uint64_t *pool = pools[wq];
     int32_t *npool = &npools[wq];
     uint64_t bound = ~0ull;   // k-th key of the pool when last reduced (lane 0 writes it)
-    if (D.oflow[q]) {   // rescanned: the rescue pass's lists
+    if (D.oflow[q] && part > 0) {
+        if (lane == 0) *npool = 0;
+    } else if (D.oflow[q]) {   // rescanned: the rescue pass's lists
         const int nc = gather_best<kMergePool, true>(pool, npool, partials, pcnt, sel, cand, (int64_t)q * m, 0, m, k, k);
         if (lane == 0) ncand[q] = nc;
     } else {
@@ -1199,9 +1205,9 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
             if (lane == 0) *npool = at + __popcll(b);
             wave_sync();
         };
-        const int first = merge_first(k);
+        const int first = D.first;
         if (n <= first) {
-            insert(lane < n ? score(src[lane]) : ~0ull);   // (n <= 64)
+            insert(part == 0 && lane < n ? score(src[lane]) : ~0ull);   // (n <= 64)
         } else {
             // Two rounds.  The scan deferred a pair when its test score passed the
             // row bound of the query's seed key; the same test at any bound tau
@@ -1280,13 +1286,20 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
             insert(lane < n1 ? score(buf[lane]) : ~0ull);
             // K: the k-th smallest of round 1's keys
             buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
-            const uint64_t K = *npool == k ? pool[k - 1] : ~0ull;
+            uint64_t K = *npool == k ? pool[k - 1] : ~0ull;
             // round 2: the row bound at K's score, as the scan computes it
-            const float td = bound_score(K);
             const float nq = D.qaux[4 * (int64_t)q + 1];
-            const float tf = !(td < __builtin_huge_valf()) ? __builtin_huge_valf()
-                             : metric == 0                 ? fmaf(D.eta, nq + td, td - nq) + 1e-37f
-                                                           : fmaf(D.eta, nq + fabsf(td), td) + 1e-37f;
+            auto row_bound = [&]() {
+                const float td = bound_score(K);
+                return !(td < __builtin_huge_valf()) ? __builtin_huge_valf()
+                       : metric == 0                 ? fmaf(D.eta, nq + td, td - nq) + 1e-37f
+                                                     : fmaf(D.eta, nq + fabsf(td), td) + 1e-37f;
+            };
+            float tf = row_bound();
+            if (part > 0) {   // (round 1's keys are in the first wave's pool)
+                if (lane == 0) *npool = 0;
+                wave_sync();
+            }
             // (compacted through LDS, so that one round of row reads serves 64
             // of them: rescored register by register, the few pairs that pass
             // cost up to NP dependent round trips.  The pairs are read again,
@@ -1294,7 +1307,7 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
             // not unrolled, and the pairs went to scratch memory, 281 us for 369
             // queries with 2000 pairs each of 200 coordinates)
             int np = 0;
-            for (int j0 = 0; j0 < NP && j0 * 64 < n; j0 += 4) {
+            for (int j0 = 4 * part; j0 < NP && j0 * 64 < n; j0 += 4 * W) {
                 uint64_t v[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
@@ -1312,6 +1325,11 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
                         const uint64_t key = score(buf[np - 64 + lane]);
                         insert(key < K ? key : ~0ull);
                         np -= 64;
+                        if (*npool >= 2 * k) {   // the k best so far bound the rest
+                            buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
+                            K = pool[k - 1];
+                            tf = row_bound();
+                        }
                         wave_sync();
                     }
                 }
@@ -1328,7 +1346,20 @@ __global__ __launch_bounds__(256) void k_merge_defer(const uint64_t *__restrict_
         buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) nc += __shfl_xor(nc, o, 64);
-        if (lane == 0) ncand[q] = nc;
+        if (lane == 0 && part == 0) ncand[q] = nc;
+    }
+    if (W > 1) {
+        __syncthreads();
+        if (part > 0) return;
+        int at = *npool;   // (at most k <= 64 keys in each)
+        for (int i = 1; i < W; i++) {
+            if (lane < npools[i]) pool[at + lane] = pools[i][lane];
+            at += npools[i];
+        }
+        wave_sync();
+        if (lane == 0) *npool = at;
+        wave_sync();
+        buf_reduce<kMergePool>(pool, npool, &bound, 0, k);
     }
     if (lane < k) {
         const int64_t o = (int64_t)q * k + lane;
@@ -2187,10 +2218,17 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 D.perm = ix->perm;
                 D.qaux = W.qaux;
                 D.eta = exact_eta(ix);
+                D.first = merge_first(P.prec, k);
             }
             if (P.defer) {
-                hipLaunchKernelGGL(P.defer > 1024 ? k_merge_defer<32> : k_merge_defer<16>, dim3(nblocks(nb, 4)), dim3(256),
-                                   0, st, partials, W.pcnt, sel, cand, nb, m, k, ix->metric, oi, od, ncand + q0, D);
+                // (FP8, whose bound leaves most of a list to round 2, and too few
+                // queries to fill the chip with a wave each: 369 queries with 2000
+                // pairs of 200 coordinates 138 us, with one wave 252; 777 queries on a
+                // BF16 copy, k = 50, 35 us, with one wave 27)
+                const bool wide = P.prec == CAPS_PREC_FP8 && P.defer > 1024 && nb <= 2048;
+                const auto merge_fn = wide ? k_merge_defer<32, 4> : P.defer > 1024 ? k_merge_defer<32, 1> : k_merge_defer<16, 1>;
+                hipLaunchKernelGGL(merge_fn, dim3(wide ? (unsigned)nb : nblocks(nb, 4)), dim3(256), 0, st, partials, W.pcnt,
+                                   sel, cand, nb, m, k, ix->metric, oi, od, ncand + q0, D);
             } else {
                 const auto merge_fn = k <= 16 ? k_merge<16> : k <= 32 ? k_merge<32> : k_merge<64>;
                 hipLaunchKernelGGL(merge_fn, dim3(nblocks(nb, 4)), dim3(256), 0, st, partials, sel, cand, nb, m, k,
