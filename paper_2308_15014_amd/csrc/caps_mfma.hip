@@ -641,18 +641,9 @@ int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, int *spl
     *split = 1;
     if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false) || r < 2) return 0;
     const int s1 = std::max(1, std::min(want, r / 2));   // (two keys each)
-    if (s1 * s_seed >= k) {
-        *split = s1;
-        return 1;
-    }
-    const int s4 = std::max(1, std::min(want, r / 8));
-    // (with label tests or disjunctions a workgroup alone inserts into lists of
-    // eight more slowly than k_scan_mfma into its smallest buffers: 0.36 ms against
-    // 0.26 for 2889 queries over 4 of 1843 partitions, d = 32 FP8, k = 10; faster
-    // than into larger ones, 1.37 against 1.43 ms for 1399 searches, k = 64)
-    if (r < 8 || 8 * s_seed < k || (s4 == 1 && r <= 16 && (ix->sch.label_vocab > 0 || disj))) return 0;
-    *split = s4;
-    return 4;
+    const int mh = s1 * s_seed >= k ? 1 : r >= 8 && 8 * s_seed >= k ? 4 : 0;
+    if (mh) *split = mh == 1 ? s1 : std::max(1, std::min(want, r / 8));
+    return mh;
 }
 
 // The approximate search defers its pairs (32 x 32 blocks) where that scan has
