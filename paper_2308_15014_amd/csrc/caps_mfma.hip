@@ -370,10 +370,12 @@ caps_status build_lowp_centroids(Index *ix, hipStream_t st) {
 // pairs (dpos: at most dcap pairs at or below the seed bound, whose r smallest
 // keys are found by bisection over their scores, then over the positions of
 // the tied ones) or, without those lists or where a query's did not fit
-// (oflow), from the per-probe lists.
+// (oflow), from the per-probe lists.  DEFER: there are deferred pairs (their 64
+// registers in the other kernel halved its waves: 6141 queries, r = 64, 66 us
+// against 49).
 constexpr int kMCap = 256;
 
-template <int METRIC>
+template <int METRIC, bool DEFER>
 __global__ __launch_bounds__(256) void k_merge_rerank(const uint64_t *__restrict__ partials,
                                                       const int32_t *__restrict__ pcnt,
                                                       const uint32_t *__restrict__ sel,
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(256) void k_merge_rerank(const uint64_t *__restrict
     uint64_t *pool = pool_all[wq];
     int32_t *npool = &npool_all[wq];
     int nr;   // <= r <= 64 candidates in the pool
-    if (!dpos || oflow[qq]) {
+    if (!DEFER || oflow[qq]) {
         const int nc = gather_best<kMCap>(pool, npool, partials, pcnt, sel, cand, (int64_t)qq * m, 0, m, r, r);
         if (lane == 0) ncand[qq] = nc;
         nr = *npool;
@@ -609,12 +611,10 @@ caps_status lowp_merge(const Index *ix, const float *q, int32_t nb, const uint32
                        int32_t *out_ids, float *out_dist, hipStream_t st, const uint64_t *dpos, const int32_t *dcnt,
                        const int32_t *oflow, int32_t dcap) {
     prof_begin(CAPS_STAGE_MERGE, st);
-    if (ix->metric == 0)
-        hipLaunchKernelGGL(k_merge_rerank<0>, dim3((nb + 3) / 4), dim3(256), 0, st, partials, pcnt, sel, cand, nb, m,
-                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand, dpos, dcnt, oflow, dcap);
-    else
-        hipLaunchKernelGGL(k_merge_rerank<1>, dim3((nb + 3) / 4), dim3(256), 0, st, partials, pcnt, sel, cand, nb, m,
-                           r, k, q, ix->d, ix->vecs, ix->perm, out_ids, out_dist, ncand, dpos, dcnt, oflow, dcap);
+    const auto fn = ix->metric == 0 ? (dpos ? k_merge_rerank<0, true> : k_merge_rerank<0, false>)
+                                    : (dpos ? k_merge_rerank<1, true> : k_merge_rerank<1, false>);
+    hipLaunchKernelGGL(fn, dim3((nb + 3) / 4), dim3(256), 0, st, partials, pcnt, sel, cand, nb, m, r, k, q, ix->d, ix->vecs,
+                       ix->perm, out_ids, out_dist, ncand, dpos, dcnt, oflow, dcap);
     prof_end(CAPS_STAGE_MERGE, st);
     CAPS_HIP(hipGetLastError());
     return CAPS_OK;
