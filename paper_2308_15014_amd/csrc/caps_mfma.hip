@@ -633,15 +633,22 @@ int lowp_qb_main(const Index *ix, bool disj, bool count) {
 // Lists of two keys per seed probe are enough when they hold twice k
 // (longer lists cost more insertions than their tighter bound saved: 4 and 10
 // keys ran 0.34 and 0.44 ms per 10k-query step against 0.28 ms with the same
-// main pass), also those of all workgroups of a tile together; with fewer seed
-// probes or a longer result list, lists of eight keys where those can hold k;
-// else the full lists of r.
-int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, int *split) {
+// main pass); with fewer seed probes or a longer result list, lists of eight
+// keys where those can hold k; else the full lists of r.  The lists of two of
+// all workgroups of a tile take the place of lists of eight where together they
+// hold 4 k, or, if every probe is a seed (all), 2 k with as many a probe as
+// those (or k): with fewer a query finds too few keys in the partitions that
+// hold its neighbours (5223 queries over 7 of 98 partitions, k = 10, two
+// workgroups a tile: 0.75 ms against 0.48 with lists of eight) or, selective
+// ones, fewer than k in all, and then no bound (65 queries over 74 of 97, k = 52:
+// 0.25 ms against 0.14).
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, bool all, int *split) {
     const int want = *split;
     *split = 1;
     if (!x32_kernel(ix->dpad / 32, ix->sch.label_vocab > 0 || disj, false) || r < 2) return 0;
     const int s1 = std::max(1, std::min(want, r / 2));   // (two keys each)
-    const int mh = s1 * s_seed >= k ? 1 : r >= 8 && 8 * s_seed >= k ? 4 : 0;
+    const bool two = s_seed >= k || s1 * s_seed >= 2 * k || (all && s1 * s_seed >= k && 2 * s1 >= std::min(8, k));
+    const int mh = two ? 1 : r >= 8 && 8 * s_seed >= k ? 4 : 0;
     if (mh) *split = mh == 1 ? s1 : std::max(1, std::min(want, r / 8));
     return mh;
 }

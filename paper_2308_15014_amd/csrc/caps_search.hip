@@ -1443,7 +1443,7 @@ struct Arena {
 
 int lowp_qb();
 int lowp_qb_main(const Index *ix, bool disj, bool count);
-int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, int *split);
+int lowp_seed_x32(const Index *ix, bool disj, int r, int k, int s_seed, bool all, int *split);
 
 struct SearchWs {
     uint8_t *qlow;
@@ -2031,7 +2031,7 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                 const int64_t tl = small ? std::min(whole, pr) : std::min(whole, pr / wide + std::min<int64_t>(b, pr));
                 int split = (int)std::max<int64_t>(1, std::min<int64_t>({1024 / std::max<int64_t>(1, tl), ix->n / b / 64, kSmallSplit}));
                 if (seed_pass && seeded_exact) {
-                    seed_mh = lowp_seed_x32(ix, disj, r, k, s_seed, &split);
+                    seed_mh = lowp_seed_x32(ix, disj, r, k, s_seed, s_seed == m, &split);
                 } else if (seed_pass) {
                     seed_mh = r >= 8 ? 4 : 1;
                     split = std::min(split, r / (2 * seed_mh));
