@@ -2223,9 +2223,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
             if (P.defer) {
                 // (FP8, whose bound leaves most of a list to round 2, and too few
                 // queries to fill the chip with a wave each: 369 queries with 2000
-                // pairs of 200 coordinates 138 us, with one wave 252; 777 queries on a
-                // BF16 copy, k = 50, 35 us, with one wave 27)
-                const bool wide = P.prec == CAPS_PREC_FP8 && P.defer > 1024 && nb <= 2048;
+                // pairs of 200 coordinates 138 us, with one wave 252; of 1646 queries
+                // 59 against 41; 777 queries on a BF16 copy, k = 50, 35 us, with one
+                // wave 27.  Between 1000 and 1700 either may win, by up to 36 us.)
+                const bool wide = P.prec == CAPS_PREC_FP8 && P.defer > 1024 && nb <= 1536;
                 const auto merge_fn = wide ? k_merge_defer<32, 4> : P.defer > 1024 ? k_merge_defer<32, 1> : k_merge_defer<16, 1>;
                 hipLaunchKernelGGL(merge_fn, dim3(wide ? (unsigned)nb : nblocks(nb, 4)), dim3(256), 0, st, partials, W.pcnt,
                                    sel, cand, nb, m, k, ix->metric, oi, od, ncand + q0, D);
