@@ -655,22 +655,47 @@ __global__ __launch_bounds__(1024) void k_rescue_init(const int32_t *__restrict_
 }
 
 // Tiles of the exact main pass that hold a flagged query: listed (in any
-// order) for the rescue pass, whose tiles hold up to `qr` entries.  Main-pass
-// tiles of 2 qr entries are listed by half (entry 2 t + half).  One thread
-// per tile.
+// order) for the rescue pass, whose tiles hold up to 64 entries.  Main-pass
+// tiles of 128 entries are listed by half (entry 2 t + half).  One wave per
+// kRescueTiles tiles, a lane per entry and one access to the list's counter (a
+// thread per tile, with its entries one after the other, took 44 us; a wave per
+// tile as long in the accesses to the counter where 18k tiles are listed).
+constexpr int kRescueTiles = 16;
 __global__ __launch_bounds__(256) void k_rescue_tiles(const int4 *__restrict__ tiles, int32_t ntiles,
                                                       const int32_t *__restrict__ entries, int32_t m,
-                                                      const int32_t *__restrict__ oflow, int32_t qr, int32_t halves,
+                                                      const int32_t *__restrict__ oflow, int32_t halves,
                                                       int32_t *__restrict__ rlist, int32_t *__restrict__ rcount) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntiles || rcount[1] == 0) return;
-    const int4 dsc = tiles[t];
-    for (int hf = 0; hf <= halves; hf++) {
-        const int i0 = hf * qr, i1 = halves ? min(dsc.z, i0 + qr) : dsc.z;
-        bool hit = false;
-        for (int i = i0; i < i1 && !hit; i++) hit = oflow[entries[dsc.y + i] / m] != 0;
-        if (hit) rlist[atomicAdd(rcount, 1)] = halves ? 2 * t + hf : t;
+    const int lane = threadIdx.x & 63, t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kRescueTiles;
+    if (t0 >= ntiles || rcount[1] == 0) return;
+    uint32_t hits = 0;   // bit 2 i + half of tile t0 + i
+    for (int u0 = 0; u0 < kRescueTiles; u0 += 4) {
+        int32_t q[4][2], f[4][2];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int t = t0 + u0 + u;
+            const int4 dsc = tiles[min(t, ntiles - 1)];
+            const int n = t < ntiles ? dsc.z : 0;
+#pragma unroll
+            for (int hf = 0; hf < 2; hf++) {
+                const int i = 64 * hf + lane;
+                q[u][hf] = hf <= halves && i < n ? entries[dsc.y + i] / m : -1;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+#pragma unroll
+            for (int hf = 0; hf < 2; hf++) f[u][hf] = q[u][hf] >= 0 ? oflow[q[u][hf]] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+#pragma unroll
+            for (int hf = 0; hf < 2; hf++) hits |= __ballot(f[u][hf] != 0) ? 1u << (2 * (u0 + u) + hf) : 0u;
     }
+    if (!hits) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(rcount, __popc(hits));
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (lane < 2 * kRescueTiles && ((hits >> lane) & 1u))
+        rlist[base + __popc(hits & ((1u << lane) - 1u))] = halves ? 2 * t0 + lane : t0 + (lane >> 1);
 }
 
 // ------------------------------------------------------------------ scan
@@ -2138,9 +2163,8 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
                     if (S.kind == 1 || S.kind == 6) {   // rescue pass over the tiles that hold a flagged query
                         if (!small) {   // (a small batch's few tiles are all looked at)
                             hipLaunchKernelGGL(k_rescue_init, dim3(1), dim3(1024), 0, st, W.oflow, nb, W.rcount);
-                            hipLaunchKernelGGL(k_rescue_tiles, dim3(nblocks(grid, 256)), dim3(256), 0, st, W.tiles,
-                                               (int32_t)grid, ent, m, W.oflow, qb, (int32_t)(qbr != qb), W.rlist,
-                                               W.rcount);
+                            hipLaunchKernelGGL(k_rescue_tiles, dim3(nblocks(grid, 4 * kRescueTiles)), dim3(256), 0, st, W.tiles,
+                                               (int32_t)grid, ent, m, W.oflow, (int32_t)(qbr != qb), W.rlist, W.rcount);
                         }
                         S.kind = S.kind == 1 ? 2 : 5;
                         S.rhalves = qbr != qb;
