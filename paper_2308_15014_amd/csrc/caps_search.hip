@@ -1738,10 +1738,14 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     // a caller workspace (no allocation) bounds the sub-batch: shrink it
     // until its layout fits
     const size_t budget = ex.ws ? ex.ws_bytes : default_budget(sp);
-    // (no copy where survivors of label tests are counted: k_scan_mfma's counting
-    // pass takes longer than the plain scan, 1.86 ms against 1.32 for 3135 queries
-    // x 48,834 x 100)
-    const bool may_copy = !out_probes && !(out_nsurv && (ix->sch.label_vocab > 0 || (sp->flags & CAPS_SEARCH_DISJUNCTIVE)));
+    // (Survivors of label tests or disjunctions are counted by k_scan_mfma.  With
+    // fewer than 32 probes, which the seed pass scans too, that takes longer than the
+    // plain scan: 2755 queries over 8 of 68 partitions, 83k x 128, 8.9 ms against 3.8;
+    // with more it takes less: 6246 queries over 415 of 476, 158k x 32, 3.9 against
+    // 12.2.  So it does for long result lists, which the plain scan keeps slowly:
+    // 2764 queries over 18 of 121, k = 52, 0.39 against 0.76.)
+    const bool counts_apart = out_nsurv && (ix->sch.label_vocab > 0 || (sp->flags & CAPS_SEARCH_DISJUNCTIVE));
+    const bool may_copy = !out_probes && !(counts_apart && m < 32 && k <= 16);
     SearchPlan P = plan_search(ix, sp, nq, budget, may_copy);
     size_t need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
     if (ex.ws) {
