@@ -1742,11 +1742,10 @@ caps_status search(const Index *ix, const caps_search_params *sp, const float *q
     // fewer than 32 probes, which the seed pass scans too, that takes longer than the
     // plain scan: 2755 queries over 8 of 68 partitions, 83k x 128, 8.9 ms against 3.8;
     // with more it takes less: 6246 queries over 415 of 476, 158k x 32, 3.9 against
-    // 12.2.  For long result lists, which the plain scan keeps slowly, the line
-    // lies lower: 2764 queries over 18 of 121, k = 52, 0.39 against 0.76; 2913 over 4
-    // of 19, k = 21, 4.7 against 1.7.)
+    // 12.2.  So it does for long result lists, which the plain scan keeps slowly:
+    // 2764 queries over 18 of 121, k = 52, 0.39 against 0.76.)
     const bool counts_apart = out_nsurv && (ix->sch.label_vocab > 0 || (sp->flags & CAPS_SEARCH_DISJUNCTIVE));
-    const bool may_copy = !out_probes && !(counts_apart && m < (k <= 16 ? 32 : 8));
+    const bool may_copy = !out_probes && !(counts_apart && m < 32 && k <= 16);
     SearchPlan P = plan_search(ix, sp, nq, budget, may_copy);
     size_t need = measure_ws(ix, sp, P, nq, P.sb, !out_ncand, !out_nsurv);
     if (ex.ws) {
